@@ -96,9 +96,37 @@ __device__ __forceinline__ IterArgs resolve_args(const IterArgs& in) {
 // the same launch: term[] is double-buffered by iteration parity, vnorm is
 // written on the second iteration only, when every workgroup computes it.
 // lds: kFuseLds doubles of the caller's LDS, free to reuse once this returns.
+//
+// Two halves, so that a kernel can put loads of its own between them: the
+// test's inputs all lie in memory that the previous launch wrote, each load is
+// a round trip of about a microsecond, and none depends on another, so
+// stop_loads issues them together (reading the slot after the sums instead
+// cost two more round trips in every iteration).
 constexpr int kFuseLds = 40;
-__device__ __forceinline__ bool iteration_stopped(const IterArgs& a, double* lds) {
-  if (!a.fused) return a.skip || (a.check_stop && load_stopped(a.slot));
+constexpr int kStopLoads = 4;  // partial sums per thread: kFuseMaxGrid over at least 256 threads
+struct StopLoads {
+  double w[kStopLoads], v[kStopLoads];
+  double vnorm, term;
+  int stopped;
+};
+__device__ __forceinline__ void stop_loads(const IterArgs& a, StopLoads& s) {
+  s.stopped = a.check_stop ? load_stopped(a.slot) : 0;
+  if (!a.fused || !a.check_stop) return;
+  const int n = a.prev_grid, nt = blockDim.x, tid = threadIdx.x;
+#pragma unroll
+  for (int u = 0; u < kStopLoads; ++u) s.w[u] = a.prev_partials[min(u * nt + tid, n - 1)];
+  s.vnorm = s.term = 0.0;
+  if (a.iter == 2) {  // the previous iteration was the substep's first
+#pragma unroll
+    for (int u = 0; u < kStopLoads; ++u) s.v[u] = a.prev_partials[n + min(u * nt + tid, n - 1)];
+  } else {
+    s.vnorm = a.slot->vnorm;
+    s.term = a.slot->term[a.iter & 1];  // iteration iter-2's term
+  }
+}
+
+__device__ __forceinline__ bool stop_verdict(const IterArgs& a, const StopLoads& s, double* lds) {
+  if (!a.fused) return a.skip || s.stopped;
   Slot* S = a.slot;
   const int tid = threadIdx.x;
   if (!a.check_stop) {  // a substep's first iteration: it always runs
@@ -109,33 +137,20 @@ __device__ __forceinline__ bool iteration_stopped(const IterArgs& a, double* lds
     }
     return false;
   }
-  // The partial sums are loaded before a replayed launch's record (which
-  // says whether the iteration is past its step's degree) is looked at, so
-  // the two latencies overlap; a skipped iteration discards the sums.
   double* fz_w = lds;       // per-wave sums (at most 16 waves)
   double* fz_v = lds + 16;
-  if (tid == 0) lds[32] = load_stopped(S) ? 1.0 : 0.0;
+  if (tid == 0) lds[32] = s.stopped ? 1.0 : 0.0;  // one thread's reading for all: workgroup 0 may be writing it
   const int n = a.prev_grid, nt = blockDim.x;
-  const bool vfirst = a.iter == 2;  // the previous iteration was the substep's first
-  const double* P = a.prev_partials;
-  constexpr int kU = 8;
+  const bool vfirst = a.iter == 2;
   double sw = 0.0, sv = 0.0;
-  for (int k0 = 0; k0 < n; k0 += kU * nt) {
-    double w[kU], v[kU];
 #pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int k = k0 + u * nt + tid;
-      w[u] = k < n ? P[k] : 0.0;
-      v[u] = (vfirst && k < n) ? P[n + k] : 0.0;
+  for (int u = 0; u < kStopLoads; ++u)
+    if (u * nt + tid < n) {
+      sw += s.w[u];
+      if (vfirst) sv += s.v[u];
     }
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      sw += w[u];
-      sv += v[u];
-    }
-  }
   sw = wave_sum(sw);
-  sv = wave_sum(sv);
+  if (vfirst) sv = wave_sum(sv);
   const int lane = tid & 63, wv = tid >> 6, nw = nt >> 6;
   if (lane == 0) {
     fz_w[wv] = sw;
@@ -150,8 +165,8 @@ __device__ __forceinline__ bool iteration_stopped(const IterArgs& a, double* lds
     tv += fz_v[w];
   }
   __syncthreads();  // every wave has read the sums: the caller may reuse lds
-  const double vn = vfirst ? sqrt(tv) : S->vnorm;
-  const double prev = vfirst ? a.d0abs * vn : S->term[a.iter & 1];  // iteration iter-2's term
+  const double vn = vfirst ? sqrt(tv) : s.vnorm;
+  const double prev = vfirst ? a.d0abs * vn : s.term;
   const double term = a.prev_dabs * sqrt(tw);
   const double est = term + prev;
   const bool bad = !isfinite(tw) || !isfinite(vn);
@@ -169,6 +184,12 @@ __device__ __forceinline__ bool iteration_stopped(const IterArgs& a, double* lds
     }
   }
   return stop;
+}
+
+__device__ __forceinline__ bool iteration_stopped(const IterArgs& a, double* lds) {
+  StopLoads s;
+  stop_loads(a, s);
+  return stop_verdict(a, s, lds);
 }
 
 }  // namespace dev
