@@ -155,7 +155,8 @@ typedef struct {
  * max_dim entries and batches of up to max_batch states (allocated here; later
  * allocations happen only in magnus_reserve_dense, magnus_dense_commutator,
  * magnus_dense_m6_prepare, magnus_csr_commutator and magnus_csr_m6_prepare;
- * about 8 vectors per state).  *out receives the
+ * about 8 vectors per state, and 184 bytes per row of max_dim for the coded
+ * form of CSR terms below).  *out receives the
  * context.  Calls on one context share its workspace: they must not run
  * concurrently from several host threads, and work they enqueue on different
  * streams must not overlap on the device (one stream per context, or the
@@ -336,6 +337,12 @@ int magnus_step_cf4_noalloc(const magnus_hamiltonian* h, double tau, double f1, 
  *               slot j receives psi after j*every_k steps (slot 0 = psi0), and
  *               the last slot psi after nsteps steps.
  *   every_k     checkpoint spacing (>= 1; ignored when checkpoints is NULL).
+ * Single CSR states on the grid path: when magnus_spectral_bounds (or the
+ * call's own first scan) found that the terms repeat few couplings, and the
+ * call is long enough for it, the call first rewrites them in a coded form in
+ * the context's workspace (one byte per entry) that its iterations read
+ * instead; results differ only in rounding (environment MAGNUS_CODED, read at
+ * magnus_create: 0 never, 2 in every call).  Nothing of it outlives the call.
  * CSR states of the product-of-exponentials methods run the whole call in one
  * persistent launch (one workgroup per state, vectors in LDS) when the
  * dimension is at most 1024, 2048 with 4 or more states, 4096 with 32 or more

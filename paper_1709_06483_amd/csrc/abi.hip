@@ -77,6 +77,16 @@ struct magnus_ctx {
   int sticky_status = 0;       // status bits of slots reset inside the current call
   ColParam* table = nullptr;   // kTableCap entries
   unsigned char* arena = nullptr;  // kArenaBytes
+  // coded CSR terms (kernels_coded.hip): the form that the current call's terms
+  // were rewritten in, for the Hamiltonian at coded_h while the call runs
+  magnus::CodedDev coded{};
+  magnus::CodeTerms coded_terms{};
+  const magnus_hamiltonian* coded_h = nullptr;
+  int coding = 1;   // MAGNUS_CODED: 0 reads the CSR arrays in every iteration, 2 codes the terms of every call
+  // term pairs found to fit the coded form when they were scanned: only a
+  // guess at what pays, since every call codes the arrays as they are then and
+  // reads a block that does not fit from them
+  std::set<std::tuple<const void*, const void*, const void*, const void*, int64_t>> codable;
   int persist = 1;  // MAGNUS_PERSIST: 0 never, 1 by size and state count, 2 every state of at most kSmallDim
   int fuse = 1;     // MAGNUS_FUSE: 0 a decide kernel after every iteration, 1 stop tests fused on small grids
   magnus::IterArgs fz_last{};  // the arguments of a final check of the last fused iteration
@@ -107,6 +117,7 @@ struct magnus_ctx {
   double2* kc_val = nullptr;
   int64_t kc_rows = 0, kc_cap = 0, kc_nnz = 0;
   std::tuple<const void*, const void*, const void*, const void*, int64_t> kc_key{nullptr, nullptr, nullptr, nullptr, 0};
+  bool kc_codable = false;  // H1, H2 and K were found to fit the coded form (a guess at what pays, as codable)
   // magnus_csr_m6_prepare: P_a = -i[H_a, K] (a = 1, 2) as CSR for the pair K
   // belongs to (valid while pm_key equals kc_key), their enclosures, and six
   // work vectors of pm_ws_dim entries for the M6 iteration (u_1..u_5, y0)
@@ -239,7 +250,10 @@ int csr_scan(magnus_ctx* ctx, const magnus_term& t, hipStream_t s, double* lo, d
   return MAGNUS_OK;
 }
 
+int note_codable(magnus_ctx* ctx, const magnus_hamiltonian* h, hipStream_t s);
+
 int ensure_valid(magnus_ctx* ctx, const magnus_hamiltonian* h, hipStream_t s) {
+  bool scanned = false;
   for (const magnus_term* t : {&h->H1, &h->H2}) {
     if (t->format != MAGNUS_CSR) continue;
     auto key = std::make_tuple((const void*)t->row_ptr, (const void*)t->col_idx, t->val, t->dim, t->nnz);
@@ -250,8 +264,9 @@ int ensure_valid(magnus_ctx* ctx, const magnus_hamiltonian* h, hipStream_t s) {
     double lo, hi;
     int rc = csr_scan(ctx, *t, s, &lo, &hi);
     if (rc) return rc;
+    scanned = true;
   }
-  return MAGNUS_OK;
+  return scanned ? note_codable(ctx, h, s) : MAGNUS_OK;
 }
 
 int dense_scan(magnus_ctx* ctx, const magnus_term& t, hipStream_t s, double* lo, double* hi) {
@@ -311,6 +326,71 @@ bool csr_m6_ready(const magnus_ctx* ctx, const magnus_hamiltonian* h) {
 bool dense_comm_ready(const magnus_ctx* ctx, const magnus_hamiltonian* h) {
   return ctx->comm && ctx->comm_h1 == h->H1.val && ctx->comm_h2 == h->H2.val && ctx->comm_n == h->H1.dim &&
          ctx->comm_ld == h->H1.ld;
+}
+
+auto pair_key(const magnus_hamiltonian* h) {
+  return std::make_tuple((const void*)h->H1.row_ptr, h->H1.val, (const void*)h->H2.row_ptr, h->H2.val, h->H1.dim);
+}
+
+CsrDev csr_dev(const magnus_term& t) {
+  return CsrDev{t.row_ptr, t.col_idx, reinterpret_cast<const double2*>(t.val)};
+}
+
+// Whether the context can hold CSR terms of this dimension in coded form.
+bool coding_possible(const magnus_ctx* ctx, const magnus_hamiltonian* h) {
+  return ctx->coding && ctx->coded.codes && h->H1.format == MAGNUS_CSR && h->H1.dim <= magnus::kCodeMaxDim;
+}
+
+// Code the terms once and say whether every block of rows fits (where they
+// have just been scanned or assembled; synchronous, as those are).
+int probe_coding(magnus_ctx* ctx, const magnus_hamiltonian* h, bool with_k, bool* fits, hipStream_t s) {
+  *fits = false;
+  ctx->coded_h = nullptr;
+  if (!coding_possible(ctx, h)) return MAGNUS_OK;
+  const int dim = (int)h->H1.dim;
+  magnus::CodeTerms T{2, {csr_dev(h->H1), csr_dev(h->H2)}};
+  if (with_k) T.m[T.n++] = CsrDev{ctx->kc_rp, ctx->kc_ci, ctx->kc_val};
+  ctx->coded.rows = magnus::code_rows(dim);
+  int bad = 0;
+  int* bad_dev = ctx->gctr + 1;
+  HIP_TRY(magnus::launch_step_set(bad_dev, 0, s));
+  HIP_TRY(magnus::launch_code_build(T, dim, ctx->coded, bad_dev, s));
+  HIP_TRY(hipMemcpyAsync(&bad, bad_dev, sizeof(int), hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipStreamSynchronize(s));
+  *fits = bad == 0;
+  return MAGNUS_OK;
+}
+
+int note_codable(magnus_ctx* ctx, const magnus_hamiltonian* h, hipStream_t s) {
+  bool fits = false;
+  ctx->codable.erase(pair_key(h));
+  if (int rc = probe_coding(ctx, h, false, &fits, s)) return rc;
+  if (fits) ctx->codable.insert(pair_key(h));
+  return MAGNUS_OK;
+}
+
+// At the start of a call on one CSR state: rewrite the terms in coded form
+// when the call's iterations pay for that.  `with_k`: its iterations apply the
+// assembled commutator too.
+int begin_coded(magnus_ctx* ctx, const magnus_hamiltonian* h, bool with_k, int64_t exponentials, hipStream_t s) {
+  ctx->coded_h = nullptr;
+  if (!coding_possible(ctx, h) || ctx->csr_variant) return MAGNUS_OK;
+  if (ctx->coding < 2) {
+    if (with_k ? !ctx->kc_codable : !ctx->codable.count(pair_key(h))) return MAGNUS_OK;
+    // Coding costs what about three iterations gain from 2^16 rows on (chains, us: coding, and an iteration on
+    // the CSR arrays / on the coded terms: n = 16 21, 15.8 / 8.1; n = 18 53, 35 / 15; n = 20 200, 151 / 47), about
+    // 20 below (n = 14 15, 6.8 / 6.0) and 45 at the smallest sizes (n = 12 13, 6.2 / 5.9); an exponential
+    // takes four iterations or more.
+    const int64_t dim = h->H1.dim, pays = dim >= 65536 ? 1 : dim >= 16384 ? 6 : 16;
+    if (exponentials < pays) return MAGNUS_OK;
+  }
+  magnus::CodeTerms T{2, {csr_dev(h->H1), csr_dev(h->H2)}};
+  if (with_k) T.m[T.n++] = CsrDev{ctx->kc_rp, ctx->kc_ci, ctx->kc_val};
+  ctx->coded.rows = magnus::code_rows((int)h->H1.dim);
+  HIP_TRY(magnus::launch_code_build(T, (int)h->H1.dim, ctx->coded, nullptr, s));
+  ctx->coded_terms = T;
+  ctx->coded_h = h;
+  return MAGNUS_OK;
 }
 
 // Row mapping of the single-state CSR iteration for a variant code (the
@@ -464,6 +544,42 @@ struct TableRef {
   const int* step;              // device step counter
 };
 
+// One Leja iteration on the coded terms (both passes for a commutator applied to vectors).
+int launch_coded(magnus_ctx* ctx, const ExpOp& op, const ExpPlan& P, int i, const double2* win, IterArgs a,
+                 hipStream_t s) {
+  const int dim = (int)op.h->H1.dim;
+  const int grid = magnus::code_grid(dim);
+  a.x1 = a.x2 = win;
+  if (int rc = setup_stop_test(ctx, P, i, grid, &a, s)) return rc;
+  const bool fused = a.fused;
+  magnus::CodeTerms T = ctx->coded_terms;
+  const bool with_k = op.kappa != 0.0 && T.n == 3;
+  if (!with_k) T.n = 2;
+  if (op.kappa != 0.0 && !with_k) {
+    // as on the streamed tiles: pass 1 writes U = a1 w + i k H2 w and V = a2 w - i k H1 w, pass 2 is H1 U + H2 V
+    IterArgs p1 = a;
+    p1.wout = ctx->vec(kU);
+    p1.pacc = ctx->vec(kV);
+    HIP_TRY(timed(ctx, MAGNUS_KERNEL_CSR_SPLIT, s, [&] {
+      return magnus::launch_coded_iter(magnus::kSplitComm, T, dim, ctx->coded, p1, 0.0, s);
+    }));
+    if (fused) {
+      a.fused = 0;
+      a.check_stop = 1;
+    }
+    a.x1 = ctx->vec(kU);
+    a.x2 = ctx->vec(kV);
+    a.a1 = a.a2 = 1.0;
+    a.unit_a = 1;
+  }
+  const int kind = op.kappa == 0.0 ? MAGNUS_KERNEL_CSR_LEJA : with_k ? MAGNUS_KERNEL_CSR_LEJA3 : MAGNUS_KERNEL_CSR_COMM;
+  HIP_TRY(timed(ctx, kind, s, [&] {
+    return magnus::launch_coded_iter(magnus::kLeja, T, dim, ctx->coded, a, P.scale * op.kappa, s);
+  }));
+  if (!fused) HIP_TRY(magnus::launch_leja_decide(a, grid, s));
+  return MAGNUS_OK;
+}
+
 int launch_iteration(magnus_ctx* ctx, const ExpOp& op, const ExpPlan& P, int i, const double2* win,
                      double2* wout, double2* pacc, double tol_sub, int early, hipStream_t s,
                      const TableRef* tab = nullptr) {
@@ -522,6 +638,7 @@ int launch_iteration(magnus_ctx* ctx, const ExpOp& op, const ExpPlan& P, int i, 
     if (!fused) HIP_TRY(magnus::launch_leja_decide(a, grid, s));
     return MAGNUS_OK;
   }
+  if (ctx->coded_h == h) return launch_coded(ctx, op, P, i, win, a, s);
   CsrDev t1{h->H1.row_ptr, h->H1.col_idx, reinterpret_cast<const double2*>(h->H1.val)};
   CsrDev t2{h->H2.row_ptr, h->H2.col_idx, reinterpret_cast<const double2*>(h->H2.val)};
   const int rpb = rows_per_block(ctx, h);
@@ -683,6 +800,7 @@ int begin_call(magnus_ctx* ctx, hipStream_t s) {
   HIP_TRY(hipSetDevice(ctx->device));
   ctx->sticky_status = 0;
   ctx->fz_pending = false;
+  ctx->coded_h = nullptr;
   HIP_TRY(magnus::launch_slot_reset(ctx->slots, ctx->nslots, s));
   return MAGNUS_OK;
 }
@@ -1005,6 +1123,17 @@ int group_for(magnus_ctx* ctx, const magnus_hamiltonian* h, int remaining) {
   if (h->H1.format == MAGNUS_DENSE) return remaining > 1 ? remaining : 1;
   auto it = ctx->tuned_group.find({(const void*)h->H1.row_ptr, h->H1.dim});
   return group_size(remaining, it == ctx->tuned_group.end() ? 32 : it->second);
+}
+
+// Whether a batch leaves a state to the single-state iteration (`grouped`: its states run in groups otherwise).
+bool single_left(magnus_ctx* ctx, const magnus_hamiltonian* h, int batch, bool grouped) {
+  if (!grouped) return true;
+  while (batch > 1) {
+    const int g = group_for(ctx, h, batch);
+    if (g <= 1) return true;
+    batch -= g;
+  }
+  return batch == 1;
 }
 
 // Plan one group exponential, assembling the dense exponent when all states share it.
@@ -1396,6 +1525,7 @@ bool graph_eligible(magnus_ctx* ctx, const magnus_hamiltonian* h, const magnus::
   if (!ctx->graph || !ctx->fuse || ctx->timing || h->H1.format != MAGNUS_CSR || S.sixth) return false;
   const int dim = (int)h->H1.dim;
   const int rpb = rows_per_block(ctx, h);
+  if (ctx->coded_h == h) return magnus::code_grid(dim) <= magnus::kFuseMaxGrid;
   int grid = magnus::csr2_grid(dim, rpb);
   if (S.commutator && csr_comm_ready(ctx, h)) grid = magnus::csr3_grid(dim, rpb == magnus::kStreamTile);
   return grid <= magnus::kFuseMaxGrid;
@@ -1686,6 +1816,19 @@ int magnus_create(magnus_ctx** out, int64_t max_dim, int32_t max_batch, int32_t 
   if (e == hipSuccess) e = hipMalloc(&c->partials, sizeof(double) * c->npartials);
   if (e == hipSuccess) e = hipMalloc(&c->scan, sizeof(double) * (size_t)c->scan_len);
   if (e == hipSuccess) e = hipMalloc(&c->gctr, 256);
+  if (const char* v = getenv("MAGNUS_CODED")) c->coding = atoi(v);
+  if (e == hipSuccess && c->coding && max_dim <= magnus::kCodeMaxDim) {
+    // the coded form of CSR terms: about 176 bytes per row (dimensions up to max_dim need at most these blocks)
+    const size_t slices = ((size_t)max_dim + 63) / 64 * 4;
+    const size_t blocks = (size_t)std::min<int64_t>(magnus::kFuseMaxGrid, (max_dim + 63) / 64);
+    c->coded.diag_stride = max_dim;
+    e = hipMalloc(&c->coded.codes, sizeof(unsigned) * 64 * magnus::kCodeAhead * slices);
+    if (e == hipSuccess) e = hipMalloc(&c->coded.more, sizeof(unsigned) * 64 * magnus::kCodeMore * slices);
+    if (e == hipSuccess) e = hipMalloc(&c->coded.head, sizeof(unsigned) * magnus::kCodeHead * slices);
+    if (e == hipSuccess) e = hipMalloc(&c->coded.dict, sizeof(magnus::CodeEntry) * (magnus::kCodeMax + 1) * blocks);
+    if (e == hipSuccess) e = hipMalloc(&c->coded.block, sizeof(int) * blocks);
+    if (e == hipSuccess) e = hipMalloc(&c->coded.diag, sizeof(double) * magnus::kCodeTerms * (size_t)max_dim);
+  }
   if (e == hipSuccess) e = hipMemset(c->slots, 0, sizeof(Slot) * c->nslots);
   if (e == hipSuccess) e = hipMemset(c->vecs, 0, sizeof(double2) * nvec);
   if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -1825,6 +1968,7 @@ int magnus_csr_commutator(magnus_ctx* ctx, magnus_hamiltonian* h, magnus_stream 
     return rc;
   h->k_min = lo;
   h->k_max = hi;
+  if ((rc = probe_coding(ctx, h, true, &ctx->kc_codable, s))) return rc;
   ctx->kc_key = std::make_tuple((const void*)h->H1.row_ptr, h->H1.val, (const void*)h->H2.row_ptr, h->H2.val, dim);
   return MAGNUS_OK;
 }
@@ -2142,6 +2286,12 @@ int magnus_destroy(magnus_ctx* ctx) {
   if (ctx->graph_done) (void)hipEventDestroy(ctx->graph_done);
   if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
   if (ctx->gctr) (void)hipFree(ctx->gctr);
+  if (ctx->coded.codes) (void)hipFree(ctx->coded.codes);
+  if (ctx->coded.more) (void)hipFree(ctx->coded.more);
+  if (ctx->coded.head) (void)hipFree(ctx->coded.head);
+  if (ctx->coded.dict) (void)hipFree(ctx->coded.dict);
+  if (ctx->coded.block) (void)hipFree(ctx->coded.block);
+  if (ctx->coded.diag) (void)hipFree(ctx->coded.diag);
   for (hipEvent_t e : ctx->pool) (void)hipEventDestroy(e);
   delete ctx;
   return MAGNUS_OK;
@@ -2182,6 +2332,8 @@ int magnus_spectral_bounds(magnus_ctx* ctx, magnus_hamiltonian* h, magnus_stream
     t->lam_min = lo;
     t->lam_max = hi;
   }
+  if (h->H1.format == MAGNUS_CSR && h->H2.format == MAGNUS_CSR)
+    if (int rc = note_codable(ctx, h, s)) return rc;
   const double n1 = std::fmax(std::fabs(h->H1.lam_min), std::fabs(h->H1.lam_max));
   const double n2 = std::fmax(std::fabs(h->H2.lam_min), std::fabs(h->H2.lam_max));
   h->k_min = -2.0 * n1 * n2;
@@ -2326,6 +2478,8 @@ int expmv_leja(magnus_ctx* ctx, const magnus_hamiltonian* h, double a, double b,
   if ((rc = ensure_valid(ctx, h, s))) return rc;
   const int64_t dim = h->H1.dim;
   const double tol_e = per_exp_tol(opts, 1);
+  if (single_left(ctx, h, batch, kappa == 0.0) && tau != 0.0)
+    if ((rc = begin_coded(ctx, h, kappa != 0.0 && csr_comm_ready(ctx, h), kappa == 0.0 ? 1 : batch, s))) return rc;
   Acc acc;
   acc.products_per_iter = kappa != 0.0 ? 4 : 2;
   const double2* vin = reinterpret_cast<const double2*>(v);
@@ -2362,6 +2516,8 @@ static int step_common(int method, magnus_ctx* ctx, const magnus_hamiltonian* h,
   magnus::method_scheme(method, &S);
   const double fv[2] = {f1, f2};
   const double tol_e = per_exp_tol(opts, S.nexp);
+  if (single_left(ctx, h, batch, !S.commutator) && tau != 0.0)
+    if ((rc = begin_coded(ctx, h, S.commutator && csr_comm_ready(ctx, h), S.commutator ? batch : S.nexp, s))) return rc;
   Acc acc;
   acc.products_per_iter = method == MAGNUS_M4 ? 4 : 2;
   const double2* in = reinterpret_cast<const double2*>(psi_in);
@@ -2455,6 +2611,8 @@ int propagate(magnus_ctx* ctx, const magnus_hamiltonian* h, int32_t method, doub
     const int64_t k = ((n / every_k) + 1) * every_k;
     return std::min(k, nsteps);
   };
+  if (!small && !S.sixth && tau != 0.0 && single_left(ctx, h, batch, grouped || batch == 1))
+    if ((rc = begin_coded(ctx, h, S.commutator && csr_comm_ready(ctx, h), exps * (S.commutator ? batch : 1), s))) return rc;
   // one state on the grid path with every stop test fused: one step captured,
   // replayed once per step
   GraphPlan G;
@@ -2695,6 +2853,8 @@ int magnus_propagate_adjoint(magnus_ctx* ctx, const magnus_hamiltonian* h, doubl
   if ((rc = begin_call(ctx, s))) return rc;
   if ((rc = ensure_valid(ctx, h, s))) return rc;
 
+  if (tau != 0.0)
+    if ((rc = begin_coded(ctx, h, false, 6 * nsteps, s))) return rc;
   const int64_t dim = h->H1.dim;
   const int64_t k = std::min<int64_t>(every_k, nsteps);
   const int64_t nck = (nsteps + k - 1) / k + 1;

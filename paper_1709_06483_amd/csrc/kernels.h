@@ -140,6 +140,49 @@ hipError_t launch_m6_stage_b(const M6Terms& T, const M6Vecs& V, double scale, in
                              hipStream_t s);
 int m6_grid(int dim);
 
+// ---- coded CSR terms (kernels_coded.hip) ----
+constexpr int kCodeMax = 255;     // (column - row, value) pairs per block of rows
+constexpr int kCodeRounds = 32;   // rounds of four entries per row, over all terms
+constexpr int kCodeAhead = 3;     // words of four rounds' codes that the iteration loads ahead (12 rounds)
+constexpr int kCodeMore = kCodeRounds / 4 - kCodeAhead;
+constexpr int kCodeHead = 8;      // header words per slice of 16 rows (one per term)
+constexpr int kCodeTerms = 5;
+constexpr int kCodeOneReal = 1 << 9;   // block flag: every term's values are all real or all imaginary
+constexpr int kCodeImag = 1 << 16;     // block flag, shifted by t: term t's values are imaginary
+constexpr int kCodeMaxDim = 1 << 26;   // byte offsets of a state's entries stay below 2^30
+constexpr int kNoEntry = 1 << 30;      // an offset past any state
+
+struct CodeTerms {
+  int n;
+  CsrDev m[kCodeTerms];
+};
+// One value of a block's dictionary: an entry at (row, row + offset / 16) of this term.
+struct alignas(32) CodeEntry {
+  double2 val;
+  int offset;
+  int term;
+  int pad[2];
+};
+struct CodedDev {
+  // Lane 16 q + r of a slice of 16 rows takes row r's entries 4 i + q in round i of each term, the
+  // terms' rounds in turn; byte k of its word g is the code of round 4 g + k (0: no entry).
+  unsigned* codes;   // [slice][lane][kCodeAhead]: words 0 .. kCodeAhead - 1
+  unsigned* more;    // [slice][kCodeMore][lane]: the words after them
+  unsigned* head;    // [slice][kCodeHead]: per term the end of its rounds | diagonal present << 8
+  CodeEntry* dict;   // [block][kCodeMax + 1]; entry 0 is unused
+  int* block;        // per block: dictionary entries | flags below, or -1 (not coded)
+  double* diag;      // per term, diag_stride apart
+  long long diag_stride;
+  int rows;          // rows per block (a multiple of 64)
+};
+int code_rows(int dim);
+int code_grid(int dim);
+// Code T's terms into C; *bad_blocks (if not null) grows by the blocks that could not be.
+hipError_t launch_code_build(const CodeTerms& T, int dim, const CodedDev& C, int* bad_blocks, hipStream_t s);
+// One Leja iteration on a1 T0 x1 + a2 T1 x2 (+ a3 T2 x1), or mode kSplitComm, on code_grid(dim) workgroups.
+hipError_t launch_coded_iter(int mode, const CodeTerms& T, int dim, const CodedDev& C, const IterArgs& a, double a3,
+                             hipStream_t s);
+
 // The streaming kernel (kernels_stream.hip).
 hipError_t launch_csr2_stream(int mode, const CsrDev& t1, const CsrDev& t2, int dim, const IterArgs& a,
                               hipStream_t s);
