@@ -80,8 +80,13 @@ struct magnus_ctx {
   // coded CSR terms (kernels_coded.hip): the form that the current call's terms
   // were rewritten in, for the Hamiltonian at coded_h while the call runs
   magnus::CodedDev coded{};
+  size_t coded_slices = 0, coded_blocks = 0;  // what its buffers hold
   magnus::CodeTerms coded_terms{};
   const magnus_hamiltonian* coded_h = nullptr;
+  bool coded_pairs = false;      // the states of the current call's batch run as interleaved pairs
+  magnus::PairArgs pair_last{};  // the last launch of pairs, for the check of its norms
+  bool pair_pending = false;
+  double* dots = nullptr;        // per-workgroup sums of dot products, and a result (inside partials)
   int coding = 1;   // MAGNUS_CODED: 0 reads the CSR arrays in every iteration, 2 codes the terms of every call
   // term pairs found to fit the coded form when they were scanned: only a
   // guess at what pays, since every call codes the arrays as they are then and
@@ -369,27 +374,42 @@ int note_codable(magnus_ctx* ctx, const magnus_hamiltonian* h, hipStream_t s) {
   return MAGNUS_OK;
 }
 
-// At the start of a call on one CSR state: rewrite the terms in coded form
+// The norm partials of pairs lie behind those of single states (two halves by
+// iteration parity each): 4 doubles per pair and block of rows.
+size_t pair_partials_at(const magnus_ctx* ctx) { return 4 * (size_t)ctx->max_grid; }
+bool pair_partials_fit(const magnus_ctx* ctx, int64_t pair_blocks) {
+  return pair_partials_at(ctx) + 8 * (size_t)pair_blocks <= ctx->npartials;
+}
+
+// At the start of a call on CSR terms: rewrite the terms in coded form
 // when the call's iterations pay for that.  `with_k`: its iterations apply the
 // assembled commutator too.
-int begin_coded(magnus_ctx* ctx, const magnus_hamiltonian* h, bool with_k, int64_t exponentials, hipStream_t s) {
+// npairs > 0: the call's states run as that many pairs (and perhaps one more).
+int begin_coded(magnus_ctx* ctx, const magnus_hamiltonian* h, bool with_k, int64_t exponentials, int npairs,
+                hipStream_t s) {
   ctx->coded_h = nullptr;
+  ctx->coded_pairs = false;
   if (!coding_possible(ctx, h) || ctx->csr_variant) return MAGNUS_OK;
+  const int64_t dim = h->H1.dim;
+  const int rows = npairs > 0 ? magnus::code_pair_rows((int)dim, npairs, 64) : magnus::code_rows((int)dim);
+  if (npairs > 0 && (!ctx->fuse || !pair_partials_fit(ctx, (int64_t)magnus::code_grid((int)dim, rows) * npairs)))
+    return MAGNUS_OK;
   if (ctx->coding < 2) {
     if (with_k ? !ctx->kc_codable : !ctx->codable.count(pair_key(h))) return MAGNUS_OK;
     // Coding costs what about three iterations gain from 2^16 rows on (chains, us: coding, and an iteration on
     // the CSR arrays / on the coded terms: n = 16 21, 15.8 / 8.1; n = 18 53, 35 / 15; n = 20 200, 151 / 47), about
     // 20 below (n = 14 15, 6.8 / 6.0) and 45 at the smallest sizes (n = 12 13, 6.2 / 5.9); an exponential
-    // takes four iterations or more.
-    const int64_t dim = h->H1.dim, pays = dim >= 65536 ? 1 : dim >= 16384 ? 6 : 16;
+    // takes four iterations or more.  Pairs gain a decide kernel in every iteration too.
+    const int64_t pays = dim >= 65536 ? 1 : npairs > 0 ? 2 : dim >= 16384 ? 6 : 16;
     if (exponentials < pays) return MAGNUS_OK;
   }
   magnus::CodeTerms T{2, {csr_dev(h->H1), csr_dev(h->H2)}};
   if (with_k) T.m[T.n++] = CsrDev{ctx->kc_rp, ctx->kc_ci, ctx->kc_val};
-  ctx->coded.rows = magnus::code_rows((int)h->H1.dim);
-  HIP_TRY(magnus::launch_code_build(T, (int)h->H1.dim, ctx->coded, nullptr, s));
+  ctx->coded.rows = rows;
+  HIP_TRY(magnus::launch_code_build(T, (int)dim, ctx->coded, nullptr, s));
   ctx->coded_terms = T;
   ctx->coded_h = h;
+  ctx->coded_pairs = npairs > 0;
   return MAGNUS_OK;
 }
 
@@ -479,6 +499,14 @@ int flush_fused_check(magnus_ctx* ctx, hipStream_t s) {
   return MAGNUS_OK;
 }
 
+// Likewise for the last launch of pairs (at the end of a group of states, and of the call).
+int flush_pair_check(magnus_ctx* ctx, hipStream_t s) {
+  if (!ctx->pair_pending) return MAGNUS_OK;
+  ctx->pair_pending = false;
+  HIP_TRY(magnus::launch_coded_pairs_check(ctx->pair_last, s));
+  return MAGNUS_OK;
+}
+
 // Launch one Leja iteration (both passes for a commutator exponent).
 // One Leja iteration of Method M6 on CSR terms, the exponent's nested
 // commutators applied to vectors.  With K = i[H1,H2], P_a = -i[H_a,K] assembled
@@ -548,7 +576,7 @@ struct TableRef {
 int launch_coded(magnus_ctx* ctx, const ExpOp& op, const ExpPlan& P, int i, const double2* win, IterArgs a,
                  hipStream_t s) {
   const int dim = (int)op.h->H1.dim;
-  const int grid = magnus::code_grid(dim);
+  const int grid = magnus::code_grid(dim, ctx->coded.rows);
   a.x1 = a.x2 = win;
   if (int rc = setup_stop_test(ctx, P, i, grid, &a, s)) return rc;
   const bool fused = a.fused;
@@ -800,7 +828,9 @@ int begin_call(magnus_ctx* ctx, hipStream_t s) {
   HIP_TRY(hipSetDevice(ctx->device));
   ctx->sticky_status = 0;
   ctx->fz_pending = false;
+  ctx->pair_pending = false;
   ctx->coded_h = nullptr;
+  ctx->coded_pairs = false;
   HIP_TRY(magnus::launch_slot_reset(ctx->slots, ctx->nslots, s));
   return MAGNUS_OK;
 }
@@ -821,6 +851,7 @@ int read_slots(magnus_ctx* ctx, hipStream_t s, long long* iters, int* status) {
 
 int end_call(magnus_ctx* ctx, const Acc& acc, double tol_e, magnus_stats* st, hipStream_t s) {
   if (int rc = flush_fused_check(ctx, s)) return rc;
+  if (int rc = flush_pair_check(ctx, s)) return rc;
   if (!st) return MAGNUS_OK;
   long long iters = 0;
   int status = 0;
@@ -1048,10 +1079,102 @@ int upload_table(magnus_ctx* ctx, const std::vector<ColParam>& table, hipStream_
   return MAGNUS_OK;
 }
 
+// Pairs of states of one problem on its coded terms: npairs pairs back to back
+// in every buffer, w in w0 / w1, the Newton sums of substeps in s0 / s1.
+struct PairWork {
+  const magnus_hamiltonian* h;
+  magnus::CodedDev C;
+  int npairs;
+  double2 *w0, *w1, *s0, *s1;
+  int slot0;    // first control slot
+  size_t poff;  // offset of its norm partials in a half
+};
+
+// The iterations of one planned exponential of every problem (E[q] of problem
+// q), one launch per iteration for all of them.
+int launch_pairs_exp(magnus_ctx* ctx, const std::vector<PairWork>& R, const std::vector<MultiExp>& E, double tol_e,
+                     int early, bool frechet, hipStream_t s) {
+  const size_t np = R.size();
+  std::vector<const double2*> cur(np);
+  std::vector<double2*> pbuf(np);
+  int max_s = 1;
+  size_t half = 0;
+  for (size_t q = 0; q < np; ++q) {
+    cur[q] = E[q].src;
+    max_s = std::max(max_s, E[q].s);
+    half = std::max(half, R[q].poff + 4 * (size_t)R[q].npairs * magnus::code_grid((int)R[q].h->H1.dim, R[q].C.rows));
+  }
+  double* base = ctx->partials + pair_partials_at(ctx);
+  if (pair_partials_at(ctx) + 2 * half > ctx->npartials) return fail(MAGNUS_ENOMEM, "per-workgroup partial sums exceed the context's buffer");
+  for (int sub = 0; sub < max_s; ++sub) {
+    int max_m = 0;
+    for (size_t q = 0; q < np; ++q) {
+      if (sub >= E[q].s) continue;
+      const bool last = sub == E[q].s - 1;
+      if (last && E[q].dst != cur[q]) pbuf[q] = E[q].dst;
+      else pbuf[q] = cur[q] == R[q].s0 ? R[q].s1 : R[q].s0;
+      max_m = std::max(max_m, E[q].m);
+    }
+    for (int i = 1; i <= max_m; ++i) {
+      magnus::PairArgs A{};
+      for (size_t q = 0; q < np; ++q) {
+        if (sub >= E[q].s || i > E[q].m) continue;
+        magnus::PairProblem& P = A.p[A.np++];
+        P.t1 = csr_dev(R[q].h->H1);
+        P.t2 = csr_dev(R[q].h->H2);
+        P.C = R[q].C;
+        P.dim = (int)R[q].h->H1.dim;
+        P.npairs = R[q].npairs;
+        P.x = (i == 1) ? cur[q] : ((i - 1) % 2 == 1 ? R[q].w0 : R[q].w1);
+        P.wout = (i % 2 == 1) ? R[q].w0 : R[q].w1;
+        P.pacc = pbuf[q];
+        P.slots = ctx->slots + R[q].slot0;
+        P.partials = base + (size_t)(i & 1) * half + R[q].poff;
+        P.prev_partials = base + (size_t)((i - 1) & 1) * half + R[q].poff;
+        P.prm = ctx->table + E[q].table_off + (size_t)(i - 1) * E[q].B;
+        P.prev = i > 1 ? P.prm - E[q].B : P.prm;
+        P.first = (i == 1);
+        P.iter = i;
+        P.early = early;
+        P.tol = tol_e / (2.0 * E[q].s);
+      }
+      HIP_TRY(timed(ctx, MAGNUS_KERNEL_CSR_MULTI, s, [&] { return magnus::launch_coded_pairs(frechet, A, s); }));
+      ctx->pair_last = A;
+      ctx->pair_pending = true;
+    }
+    for (size_t q = 0; q < np; ++q)
+      if (sub < E[q].s) cur[q] = pbuf[q];
+  }
+  for (size_t q = 0; q < np; ++q)
+    if (cur[q] != E[q].dst) HIP_TRY(magnus::launch_copy(cur[q], E[q].dst, (long long)R[q].h->H1.dim * E[q].B, s));
+  return MAGNUS_OK;
+}
+
+// States into and out of the layout a group's iterations use: interleaved, or
+// interleaved pairs when the group runs on coded terms.
+int pack_group(magnus_ctx* ctx, const magnus_hamiltonian* h, const double2* src, double2* dst, int B, hipStream_t s) {
+  if (ctx->coded_h == h && ctx->coded_pairs) HIP_TRY(magnus::launch_pack_pairs(src, dst, (int)h->H1.dim, B / 2, s));
+  else HIP_TRY(magnus::launch_pack(src, dst, (int)h->H1.dim, B, s));
+  return MAGNUS_OK;
+}
+int unpack_group(magnus_ctx* ctx, const magnus_hamiltonian* h, const double2* src, double2* dst, int B, hipStream_t s) {
+  if (ctx->coded_h == h && ctx->coded_pairs) {
+    if (int rc = flush_pair_check(ctx, s)) return rc;
+    HIP_TRY(magnus::launch_unpack_pairs(src, dst, (int)h->H1.dim, B / 2, s));
+  } else {
+    HIP_TRY(magnus::launch_unpack(src, dst, (int)h->H1.dim, B, s));
+  }
+  return MAGNUS_OK;
+}
+
 // Launch the iterations of one planned multi-state exponential.
 int launch_multi(magnus_ctx* ctx, const magnus_hamiltonian* h, const MultiExp& E, double tol_e, int early,
                  hipStream_t s) {
   if (int rc = flush_fused_check(ctx, s)) return rc;
+  if (ctx->coded_h == h && ctx->coded_pairs && !E.frechet) {
+    const PairWork W{h, ctx->coded, E.B / 2, ctx->vec(kA), ctx->vec(kB), ctx->vec(kS0), ctx->vec(kS1), 0, 0};
+    return launch_pairs_exp(ctx, {W}, {E}, tol_e, early, false, s);
+  }
   const int dim = (int)h->H1.dim;
   const int B = E.B;
   const size_t n = (size_t)dim * B;
@@ -1121,19 +1244,10 @@ bool multi_ok(const magnus_hamiltonian* h, double kappa) { return kappa == 0.0; 
 // (at most the autotuned group size).
 int group_for(magnus_ctx* ctx, const magnus_hamiltonian* h, int remaining) {
   if (h->H1.format == MAGNUS_DENSE) return remaining > 1 ? remaining : 1;
+  // on coded terms: any number of pairs, up to 32 states as below (a group shares its largest substep count)
+  if (ctx->coded_h == h && ctx->coded_pairs) return remaining > 1 ? std::min(remaining & ~1, 32) : 1;
   auto it = ctx->tuned_group.find({(const void*)h->H1.row_ptr, h->H1.dim});
   return group_size(remaining, it == ctx->tuned_group.end() ? 32 : it->second);
-}
-
-// Whether a batch leaves a state to the single-state iteration (`grouped`: its states run in groups otherwise).
-bool single_left(magnus_ctx* ctx, const magnus_hamiltonian* h, int batch, bool grouped) {
-  if (!grouped) return true;
-  while (batch > 1) {
-    const int g = group_for(ctx, h, batch);
-    if (g <= 1) return true;
-    batch -= g;
-  }
-  return batch == 1;
 }
 
 // Plan one group exponential, assembling the dense exponent when all states share it.
@@ -1157,19 +1271,18 @@ int plan_group(magnus_ctx* ctx, const magnus_hamiltonian* h, const double* acoef
 int multi_expmv_group(magnus_ctx* ctx, const magnus_hamiltonian* h, int B, const double* acoef,
                       const double* bcoef, double tau, const double2* src, double2* dst, double tol_e,
                       const magnus_leja_opts* o, Acc* acc, hipStream_t s) {
-  const int dim = (int)h->H1.dim;
   double2* Y = ctx->vec(kY);
-  HIP_TRY(magnus::launch_pack(src, Y, dim, B, s));
+  int rc = pack_group(ctx, h, src, Y, B, s);
+  if (rc) return rc;
   std::vector<ColParam> table;
   MultiExp E;
-  int rc = plan_group(ctx, h, acoef, bcoef, B, tau, tol_e, o, &table, &E, acc);
+  rc = plan_group(ctx, h, acoef, bcoef, B, tau, tol_e, o, &table, &E, acc);
   if (rc) return rc;
   if ((rc = upload_table(ctx, table, s))) return rc;
   E.src = Y;
   E.dst = Y;
   if ((rc = launch_multi(ctx, h, E, tol_e, o->early_termination, s))) return rc;
-  HIP_TRY(magnus::launch_unpack(Y, dst, dim, B, s));
-  return MAGNUS_OK;
+  return unpack_group(ctx, h, Y, dst, B, s);
 }
 
 // Product-of-exponentials steps for a group of B states held interleaved in
@@ -1229,6 +1342,7 @@ int multi_cf_steps(magnus_ctx* ctx, const magnus_hamiltonian* h, const magnus::S
 // ---------------------------------------------------------------------------
 struct RagProblem {
   const magnus_problem* P;
+  magnus::CodedDev C;  // its coded terms, when the problems run as pairs
   int c0;         // first of its states in the problem (a group of B states)
   size_t voff;    // offset of its slice inside every workspace vector
   int slot0;      // its first control slot
@@ -1292,11 +1406,72 @@ int launch_ragged_exp(magnus_ctx* ctx, const std::vector<RagProblem>& R, const s
   return MAGNUS_OK;
 }
 
+// Code the terms of a ragged batch's large problems and lay out their slices of
+// the workspace, when they can run together as pairs: CSR terms found to fit the
+// form, one even batch, everything within the context's buffers.  *out stays
+// empty otherwise.
+int code_ragged(magnus_ctx* ctx, const magnus_problem* probs, const std::vector<int>& big, const magnus::Scheme& S,
+                int64_t nsteps, int small_states, std::vector<RagProblem>* out, hipStream_t s) {
+  const int batch = probs[big[0]].batch;
+  if (!ctx->fuse || ctx->csr_variant || batch < 2 || batch % 2 || batch > ctx->max_batch ||
+      big.size() > (size_t)magnus::kMaxPairProblems)
+    return MAGNUS_OK;
+  const int npairs = batch / 2;
+  // several rows of slices to a wave where problems of several sizes share a launch
+  const int min_rows = big.size() > 1 ? 256 : 64;
+  size_t slices = 0, blocks = 0, rows = 0, voff = 0, poff = 0;
+  int slot0 = small_states;
+  std::vector<RagProblem> R;
+  for (int i : big) {
+    const magnus_problem& P = probs[i];
+    const magnus_hamiltonian* h = &P.h;
+    if (P.batch != batch || !coding_possible(ctx, h)) return MAGNUS_OK;
+    if (ctx->coding < 2 && (!ctx->codable.count(pair_key(h)) || (h->H1.dim < 65536 && S.nexp * nsteps < 2))) return MAGNUS_OK;
+    const int dim = (int)h->H1.dim;
+    magnus::CodedDev C = ctx->coded;
+    C.rows = magnus::code_pair_rows(dim, npairs, min_rows);
+    C.codes += slices * 64 * magnus::kCodeAhead;
+    C.more += slices * 64 * magnus::kCodeMore;
+    C.head += slices * magnus::kCodeHead;
+    C.dict += blocks * (magnus::kCodeMax + 1);
+    C.block += blocks;
+    C.diag += rows;
+    R.push_back(RagProblem{&P, C, 0, voff, slot0, poff});
+    const size_t grid = (size_t)magnus::code_grid(dim, C.rows);
+    slices += ((size_t)dim + 63) / 64 * 4;
+    blocks += grid;
+    rows += (size_t)dim;
+    voff += (size_t)dim * batch;
+    poff += 4 * (size_t)npairs * grid;
+    slot0 += batch;
+  }
+  if (slices > ctx->coded_slices || blocks > ctx->coded_blocks || rows > (size_t)ctx->max_dim ||
+      voff > (size_t)ctx->max_dim * (size_t)ctx->max_batch || pair_partials_at(ctx) + 2 * poff > ctx->npartials ||
+      slot0 > ctx->nslots)
+    return MAGNUS_OK;
+  for (RagProblem& q : R) {
+    const magnus::CodeTerms T{2, {csr_dev(q.P->h.H1), csr_dev(q.P->h.H2)}};
+    HIP_TRY(magnus::launch_code_build(T, (int)q.P->h.H1.dim, q.C, nullptr, s));
+  }
+  *out = std::move(R);
+  return MAGNUS_OK;
+}
+
 // Product-of-exponentials steps of the ragged batch's large problems (all of
 // batch B, B a group size), packed interleaved into their workspace slices.
 int ragged_joint_steps(magnus_ctx* ctx, std::vector<RagProblem>& R, const magnus::Scheme& S, int B, double tau,
                        int64_t nsteps, double tol_e, const magnus_leja_opts* o, Acc* acc, hipStream_t s) {
-  for (const RagProblem& q : R) HIP_TRY(magnus::launch_pack(q.psi(), q.v(ctx, kY), (int)q.P->h.H1.dim, B, s));
+  const bool pairs = R[0].C.codes != nullptr;
+  std::vector<PairWork> W;
+  for (const RagProblem& q : R) {
+    const int dim = (int)q.P->h.H1.dim;
+    if (pairs) {
+      HIP_TRY(magnus::launch_pack_pairs(q.psi(), q.v(ctx, kY), dim, B / 2, s));
+      W.push_back(PairWork{&q.P->h, q.C, B / 2, q.v(ctx, kA), q.v(ctx, kB), q.v(ctx, kS0), q.v(ctx, kS1), q.slot0, q.poff});
+    } else {
+      HIP_TRY(magnus::launch_pack(q.psi(), q.v(ctx, kY), dim, B, s));
+    }
+  }
   std::vector<double> av(B), bv(B), fv(S.q);
   int64_t n = 0;
   while (n < nsteps) {
@@ -1336,12 +1511,19 @@ int ragged_joint_steps(magnus_ctx* ctx, std::vector<RagProblem>& R, const magnus
     }
     int rc = upload_table(ctx, table, s);
     if (rc) return rc;
-    for (const auto& E : steps)
-      if ((rc = launch_ragged_exp(ctx, R, E, B, tol_e, o->early_termination, s))) return rc;
+    for (const auto& E : steps) {
+      rc = pairs ? launch_pairs_exp(ctx, W, E, tol_e, o->early_termination, false, s)
+                 : launch_ragged_exp(ctx, R, E, B, tol_e, o->early_termination, s);
+      if (rc) return rc;
+    }
     n = k;
   }
-  for (const RagProblem& q : R) HIP_TRY(magnus::launch_unpack(q.v(ctx, kY), q.psi(), (int)q.P->h.H1.dim, B, s));
-  return MAGNUS_OK;
+  for (const RagProblem& q : R) {
+    const int dim = (int)q.P->h.H1.dim;
+    if (pairs) HIP_TRY(magnus::launch_unpack_pairs(q.v(ctx, kY), q.psi(), dim, B / 2, s));
+    else HIP_TRY(magnus::launch_unpack(q.v(ctx, kY), q.psi(), dim, B, s));
+  }
+  return flush_pair_check(ctx, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -1525,7 +1707,7 @@ bool graph_eligible(magnus_ctx* ctx, const magnus_hamiltonian* h, const magnus::
   if (!ctx->graph || !ctx->fuse || ctx->timing || h->H1.format != MAGNUS_CSR || S.sixth) return false;
   const int dim = (int)h->H1.dim;
   const int rpb = rows_per_block(ctx, h);
-  if (ctx->coded_h == h) return magnus::code_grid(dim) <= magnus::kFuseMaxGrid;
+  if (ctx->coded_h == h) return magnus::code_grid(dim, ctx->coded.rows) <= magnus::kFuseMaxGrid;
   int grid = magnus::csr2_grid(dim, rpb);
   if (S.commutator && csr_comm_ready(ctx, h)) grid = magnus::csr3_grid(dim, rpb == magnus::kStreamTile);
   return grid <= magnus::kFuseMaxGrid;
@@ -1813,14 +1995,16 @@ int magnus_create(magnus_ctx** out, int64_t max_dim, int32_t max_batch, int32_t 
                  (size_t)max_dim * (size_t)std::max(1, max_batch) / 8 + (size_t)max_dim + 64;
   // the dot-product kernel's per-workgroup pairs, whatever the dimension
   c->npartials = std::max(c->npartials, (size_t)magnus::kDotPartials + 64);
-  if (e == hipSuccess) e = hipMalloc(&c->partials, sizeof(double) * c->npartials);
+  const size_t with_dots = c->npartials + magnus::kDotPartials + 64;
+  if (e == hipSuccess) e = hipMalloc(&c->partials, sizeof(double) * with_dots);
+  c->dots = c->partials + c->npartials;
   if (e == hipSuccess) e = hipMalloc(&c->scan, sizeof(double) * (size_t)c->scan_len);
   if (e == hipSuccess) e = hipMalloc(&c->gctr, 256);
   if (const char* v = getenv("MAGNUS_CODED")) c->coding = atoi(v);
   if (e == hipSuccess && c->coding && max_dim <= magnus::kCodeMaxDim) {
     // the coded form of CSR terms: about 176 bytes per row (dimensions up to max_dim need at most these blocks)
-    const size_t slices = ((size_t)max_dim + 63) / 64 * 4;
-    const size_t blocks = (size_t)std::min<int64_t>(magnus::kFuseMaxGrid, (max_dim + 63) / 64);
+    const size_t slices = c->coded_slices = ((size_t)max_dim + 63) / 64 * 4;
+    const size_t blocks = c->coded_blocks = (size_t)std::min<int64_t>(magnus::kFuseMaxGrid, (max_dim + 63) / 64);
     c->coded.diag_stride = max_dim;
     e = hipMalloc(&c->coded.codes, sizeof(unsigned) * 64 * magnus::kCodeAhead * slices);
     if (e == hipSuccess) e = hipMalloc(&c->coded.more, sizeof(unsigned) * 64 * magnus::kCodeMore * slices);
@@ -2366,9 +2550,8 @@ int apply_term(magnus_ctx* ctx, const magnus_term& t, const double2* x, double2*
 
 // Re(x^H y) on the host (one device dot product and a wait).
 int dot_re(magnus_ctx* ctx, const double2* x, const double2* y, int64_t n, double* out, hipStream_t s) {
-  double2* dev_out = reinterpret_cast<double2*>(ctx->partials + magnus::kDotPartials);
-  if (int rc = flush_fused_check(ctx, s)) return rc;
-  HIP_TRY(magnus::launch_cdot(x, 1, y, 1, n, ctx->partials, dev_out, s));
+  double2* dev_out = reinterpret_cast<double2*>(ctx->dots + magnus::kDotPartials);
+  HIP_TRY(magnus::launch_cdot(x, 1, y, 1, n, ctx->dots, dev_out, s));
   double2 h;
   HIP_TRY(hipMemcpyAsync(&h, dev_out, sizeof(double2), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
@@ -2478,8 +2661,10 @@ int expmv_leja(magnus_ctx* ctx, const magnus_hamiltonian* h, double a, double b,
   if ((rc = ensure_valid(ctx, h, s))) return rc;
   const int64_t dim = h->H1.dim;
   const double tol_e = per_exp_tol(opts, 1);
-  if (single_left(ctx, h, batch, kappa == 0.0) && tau != 0.0)
-    if ((rc = begin_coded(ctx, h, kappa != 0.0 && csr_comm_ready(ctx, h), kappa == 0.0 ? 1 : batch, s))) return rc;
+  if (tau != 0.0)
+    if ((rc = begin_coded(ctx, h, kappa != 0.0 && csr_comm_ready(ctx, h), kappa == 0.0 ? 1 : batch,
+                          kappa == 0.0 ? std::min(batch / 2, 16) : 0, s)))
+      return rc;
   Acc acc;
   acc.products_per_iter = kappa != 0.0 ? 4 : 2;
   const double2* vin = reinterpret_cast<const double2*>(v);
@@ -2516,8 +2701,10 @@ static int step_common(int method, magnus_ctx* ctx, const magnus_hamiltonian* h,
   magnus::method_scheme(method, &S);
   const double fv[2] = {f1, f2};
   const double tol_e = per_exp_tol(opts, S.nexp);
-  if (single_left(ctx, h, batch, !S.commutator) && tau != 0.0)
-    if ((rc = begin_coded(ctx, h, S.commutator && csr_comm_ready(ctx, h), S.commutator ? batch : S.nexp, s))) return rc;
+  if (tau != 0.0)
+    if ((rc = begin_coded(ctx, h, S.commutator && csr_comm_ready(ctx, h), S.commutator ? batch : S.nexp,
+                          S.commutator ? 0 : std::min(batch / 2, 16), s)))
+      return rc;
   Acc acc;
   acc.products_per_iter = method == MAGNUS_M4 ? 4 : 2;
   const double2* in = reinterpret_cast<const double2*>(psi_in);
@@ -2525,10 +2712,10 @@ static int step_common(int method, magnus_ctx* ctx, const magnus_hamiltonian* h,
   for (int32_t c = 0; c < batch;) {
     const int g = (!S.commutator && multi_ok(h, 0.0)) ? group_for(ctx, h, batch - c) : 1;
     if (g > 1) {
-      HIP_TRY(magnus::launch_pack(in + c * dim, ctx->vec(kY), (int)dim, g, s));
+      if ((rc = pack_group(ctx, h, in + c * dim, ctx->vec(kY), g, s))) return rc;
       rc = multi_cf_steps(ctx, h, S, g, tau, 0, 1, [&](int, int64_t, int j) { return fv[j]; }, tol_e, opts, &acc, s);
       if (rc) return rc;
-      HIP_TRY(magnus::launch_unpack(ctx->vec(kY), out + c * dim, (int)dim, g, s));
+      rc = unpack_group(ctx, h, ctx->vec(kY), out + c * dim, g, s);
     } else {
       rc = S.commutator ? m4_state(ctx, h, tau, f1, f2, in + c * dim, out + c * dim, tol_e, opts, &acc, s)
                         : cf_state(ctx, h, S, tau, fv, in + c * dim, out + c * dim, tol_e, opts, &acc, s);
@@ -2611,8 +2798,10 @@ int propagate(magnus_ctx* ctx, const magnus_hamiltonian* h, int32_t method, doub
     const int64_t k = ((n / every_k) + 1) * every_k;
     return std::min(k, nsteps);
   };
-  if (!small && !S.sixth && tau != 0.0 && single_left(ctx, h, batch, grouped || batch == 1))
-    if ((rc = begin_coded(ctx, h, S.commutator && csr_comm_ready(ctx, h), exps * (S.commutator ? batch : 1), s))) return rc;
+  if (!small && !S.sixth && tau != 0.0)
+    if ((rc = begin_coded(ctx, h, S.commutator && csr_comm_ready(ctx, h), exps * (S.commutator ? batch : 1),
+                          grouped ? std::min(batch / 2, 16) : 0, s)))
+      return rc;
   // one state on the grid path with every stop test fused: one step captured,
   // replayed once per step
   GraphPlan G;
@@ -2633,11 +2822,11 @@ int propagate(magnus_ctx* ctx, const magnus_hamiltonian* h, int32_t method, doub
     for (int32_t c = small ? batch : 0; c < batch;) {
       const int g = grouped ? group_for(ctx, h, batch - c) : 1;
       if (g > 1) {
-        HIP_TRY(magnus::launch_pack(st + c * dim, ctx->vec(kY), (int)dim, g, s));
+        if ((rc = pack_group(ctx, h, st + c * dim, ctx->vec(kY), g, s))) return rc;
         rc = multi_cf_steps(ctx, h, S, g, tau, n, stop,
                             [&](int cc, int64_t k, int j) { return fval(c + cc, k, j); }, tol_e, opts, &acc, s);
         if (rc) return rc;
-        HIP_TRY(magnus::launch_unpack(ctx->vec(kY), st + c * dim, (int)dim, g, s));
+        if ((rc = unpack_group(ctx, h, ctx->vec(kY), st + c * dim, g, s))) return rc;
       } else if (use_graph) {
         if ((rc = graph_replay(ctx, G, tau, n, stop, tol_e, opts, &acc, s))) return rc;
       } else {
@@ -2764,14 +2953,21 @@ int magnus_propagate_ragged(magnus_ctx* ctx, const magnus_problem* probs, int32_
             vtot <= (size_t)ctx->max_dim * (size_t)ctx->max_batch && ptot <= ctx->npartials &&
             sst.size() + groups * (size_t)JB <= (size_t)ctx->nslots;
   }
-  if (joint && nsteps > 0) {
+  // on coded terms the problems run as pairs of states, whole batches at once
+  std::vector<RagProblem> coded;
+  if (ctx->ragged_joint && !S.commutator && !big.empty() && nsteps > 0 && tau != 0.0)
+    if ((rc = code_ragged(ctx, probs, big, S, nsteps, (int)sst.size(), &coded, s))) return rc;
+  if (!coded.empty()) {
+    if ((rc = ragged_joint_steps(ctx, coded, S, probs[big[0]].batch, tau, nsteps, tol_e, opts, &acc, s))) return rc;
+    big.clear();
+  } else if (joint && nsteps > 0) {
     std::vector<RagProblem> R;
     size_t voff = 0, poff = 0;
     int slot0 = (int)sst.size();
     for (int i : big) {
       const magnus_problem& P = probs[i];
       for (int c0 = 0; c0 < P.batch; c0 += JB) {
-        R.push_back(RagProblem{&P, c0, voff, slot0, poff});
+        R.push_back(RagProblem{&P, {}, c0, voff, slot0, poff});
         voff += (size_t)P.h.H1.dim * JB;
         poff += (size_t)magnus::ragged_grid((int)P.h.H1.dim, JB) * JB * 2;
         slot0 += JB;
@@ -2854,7 +3050,9 @@ int magnus_propagate_adjoint(magnus_ctx* ctx, const magnus_hamiltonian* h, doubl
   if ((rc = ensure_valid(ctx, h, s))) return rc;
 
   if (tau != 0.0)
-    if ((rc = begin_coded(ctx, h, false, 6 * nsteps, s))) return rc;
+    if ((rc = begin_coded(ctx, h, false, 6 * nsteps, 0, s))) return rc;
+  if (ctx->coded_h == h && (!ctx->fuse || !pair_partials_fit(ctx, 2LL * magnus::code_grid((int)h->H1.dim, ctx->coded.rows))))
+    ctx->coded_h = nullptr;
   const int64_t dim = h->H1.dim;
   const int64_t k = std::min<int64_t>(every_k, nsteps);
   const int64_t nck = (nsteps + k - 1) / k + 1;
@@ -2874,66 +3072,90 @@ int magnus_propagate_adjoint(magnus_ctx* ctx, const magnus_hamiltonian* h, doubl
   auto gamma_of = [&](int64_t n) { return magnus::kAlpha1 * f_nodes[2 * n] + magnus::kAlpha2 * f_nodes[2 * n + 1]; };
   const double2* tgt = reinterpret_cast<const double2*>(psi_target);
 
-  // forward sweep with checkpoints (state kept in mu)
+  // psi_{n+1} = E_b E_a psi_n through the half-step state phi_n
+  auto step_to = [&](int64_t n, const double2* p0, double2* ph, double2* p1) {
+    const int rc1 = run_exponential(ctx, ExpOp{h, 0.5, beta_of(n), 0.0}, tau, p0, ph, tol_e, opts, &acc, s);
+    return rc1 ? rc1 : run_exponential(ctx, ExpOp{h, 0.5, gamma_of(n), 0.0}, tau, ph, p1, tol_e, opts, &acc, s);
+  };
+  // forward sweep with checkpoints (state kept in mu); the last segment's states
+  // go where the backward sweep, which starts with it, looks for them
+  const int64_t tail = (nseg - 1) * k;
   HIP_TRY(hipMemcpyAsync(ck, psi0, sizeof(double2) * dim, hipMemcpyDeviceToDevice, s));
-  HIP_TRY(hipMemcpyAsync(mu, psi0, sizeof(double2) * dim, hipMemcpyDeviceToDevice, s));
-  magnus::Scheme cf4;
-  magnus::method_scheme(MAGNUS_CF4, &cf4);
+  HIP_TRY(hipMemcpyAsync(nseg > 1 ? mu : seg_psi, psi0, sizeof(double2) * dim, hipMemcpyDeviceToDevice, s));
   for (int64_t n = 0; n < nsteps; ++n) {
-    rc = cf_state(ctx, h, cf4, tau, f_nodes + 2 * n, mu, mu, tol_e, opts, &acc, s);
-    if (rc) return rc;
-    if ((n + 1) % k == 0 || n + 1 == nsteps) {
-      const int64_t slot = (n + 1) % k == 0 ? (n + 1) / k : nck - 1;
-      HIP_TRY(hipMemcpyAsync(ck + slot * dim, mu, sizeof(double2) * dim, hipMemcpyDeviceToDevice, s));
+    if (n >= tail) {
+      double2* p0 = seg_psi + (n - tail) * dim;
+      if ((rc = step_to(n, p0, seg_phi + (n - tail) * dim, p0 + dim))) return rc;
+      continue;
+    }
+    if ((rc = step_to(n, mu, ctx->vec(kS2), mu))) return rc;
+    if ((n + 1) % k == 0) {
+      HIP_TRY(hipMemcpyAsync(ck + (n + 1) / k * dim, mu, sizeof(double2) * dim, hipMemcpyDeviceToDevice, s));
+      if (n + 1 == tail) HIP_TRY(hipMemcpyAsync(seg_psi, mu, sizeof(double2) * dim, hipMemcpyDeviceToDevice, s));
     }
   }
-  if ((rc = flush_fused_check(ctx, s))) return rc;
-  HIP_TRY(magnus::launch_cdot(tgt, 1, mu, 1, dim, ctx->partials, g + 2 * nsteps, s));
+  HIP_TRY(magnus::launch_cdot(tgt, 1, seg_psi + (nsteps - tail) * dim, 1, dim, ctx->dots, g + 2 * nsteps, s));
   HIP_TRY(hipMemcpyAsync(lam, tgt, sizeof(double2) * dim, hipMemcpyDeviceToDevice, s));
 
-  const double half[2] = {0.5, 0.5};
+  // The block (Frechet) exponentials of a step, of phi_n with gamma_n and of
+  // psi_n with beta_n, do not depend on lambda: on coded terms they run together,
+  // as two pairs (each work buffer two vectors of the context, back to back).
+  const bool pairs = ctx->coded_h == h;
+  const double half[4] = {0.5, 0.5, 0.5, 0.5};
   for (int64_t seg = nseg - 1; seg >= 0; --seg) {
     const int64_t n0 = seg * k, n1 = std::min(n0 + k, nsteps);
-    // recompute psi_n and the half-step states phi_n of the segment
-    HIP_TRY(hipMemcpyAsync(seg_psi, ck + seg * dim, sizeof(double2) * dim, hipMemcpyDeviceToDevice, s));
-    for (int64_t n = n0; n < n1; ++n) {
-      double2* p0 = seg_psi + (n - n0) * dim;
-      double2* ph = seg_phi + (n - n0) * dim;
-      rc = run_exponential(ctx, ExpOp{h, 0.5, beta_of(n), 0.0}, tau, p0, ph, tol_e, opts, &acc, s);
-      if (rc) return rc;
-      rc = run_exponential(ctx, ExpOp{h, 0.5, gamma_of(n), 0.0}, tau, ph, p0 + dim, tol_e, opts, &acc, s);
-      if (rc) return rc;
+    if (seg < nseg - 1) {  // recompute psi_n and the half-step states phi_n of the segment
+      HIP_TRY(hipMemcpyAsync(seg_psi, ck + seg * dim, sizeof(double2) * dim, hipMemcpyDeviceToDevice, s));
+      for (int64_t n = n0; n < n1; ++n) {
+        double2* p0 = seg_psi + (n - n0) * dim;
+        if ((rc = step_to(n, p0, seg_phi + (n - n0) * dim, p0 + dim))) return rc;
+      }
     }
-    // block (Frechet) exponentials of the segment, planned and uploaded together
+    // the segment's block exponentials, planned and uploaded together
     std::vector<ColParam> table;
     std::vector<MultiExp> ea(n1 - n0), eb(n1 - n0);
     for (int64_t n = n0; n < n1; ++n) {
-      const double ga2[2] = {gamma_of(n), gamma_of(n)}, be2[2] = {beta_of(n), beta_of(n)};
-      rc = plan_multi(h, half, ga2, 2, tau, tol_e, opts, 1, &table, &ea[n - n0], &acc);
+      const double ga = gamma_of(n), be = beta_of(n), both[4] = {ga, ga, be, be};
+      rc = plan_multi(h, half, both, pairs ? 4 : 2, tau, tol_e, opts, 1, &table, &ea[n - n0], &acc);
       if (rc) return rc;
-      rc = plan_multi(h, half, be2, 2, tau, tol_e, opts, 1, &table, &eb[n - n0], &acc);
+      if (pairs) continue;
+      rc = plan_multi(h, half, both + 2, 2, tau, tol_e, opts, 1, &table, &eb[n - n0], &acc);
       if (rc) return rc;
     }
     if ((rc = upload_table(ctx, table, s))) return rc;
     for (int64_t n = n1 - 1; n >= n0; --n) {
-      MultiExp A = ea[n - n0], Bx = eb[n - n0];
-      A.src = X2;
-      A.dst = Y2;
-      Bx.src = X2;
-      Bx.dst = Y2;
+      const double2 *psi = seg_psi + (n - n0) * dim, *phi = seg_phi + (n - n0) * dim;
+      const double2 *la = Y2, *lb = Y2;  // L_a phi_n, L_b psi_n (every second element)
+      if (pairs) {
+        la = ctx->vec(kS2);
+        lb = la + 2 * dim;
+        MultiExp E = ea[n - n0];
+        E.src = X2;
+        E.dst = ctx->vec(kS2);
+        const PairWork W{h, ctx->coded, 2, ctx->vec(kA), ctx->vec(kS0), ctx->vec(kV), X2, 0, 0};
+        HIP_TRY(magnus::launch_frechet_pairs_init(phi, psi, X2, (int)dim, s));
+        if ((rc = launch_pairs_exp(ctx, {W}, {E}, tol_e, opts->early_termination, true, s))) return rc;
+      } else {
+        MultiExp A = ea[n - n0];
+        A.src = X2;
+        A.dst = Y2;
+        HIP_TRY(magnus::launch_frechet_init(phi, X2, (int)dim, s));
+        if ((rc = launch_multi(ctx, h, A, tol_e, opts->early_termination, s))) return rc;
+      }
       // g_a(n) = lambda_{n+1}^H L_a phi_n
-      HIP_TRY(magnus::launch_frechet_init(seg_phi + (n - n0) * dim, X2, (int)dim, s));
-      if ((rc = launch_multi(ctx, h, A, tol_e, opts->early_termination, s))) return rc;
-      if ((rc = flush_fused_check(ctx, s))) return rc;
-      HIP_TRY(magnus::launch_cdot(lam, 1, Y2, 2, dim, ctx->partials, g + 2 * n, s));
+      HIP_TRY(magnus::launch_cdot(lam, 1, la, 2, dim, ctx->dots, g + 2 * n, s));
       // mu_n = E_a^H lambda_{n+1}
       rc = run_exponential(ctx, ExpOp{h, 0.5, gamma_of(n), 0.0}, -tau, lam, mu, tol_e, opts, &acc, s);
       if (rc) return rc;
+      if (!pairs) {
+        MultiExp Bx = eb[n - n0];
+        Bx.src = X2;
+        Bx.dst = Y2;
+        HIP_TRY(magnus::launch_frechet_init(psi, X2, (int)dim, s));
+        if ((rc = launch_multi(ctx, h, Bx, tol_e, opts->early_termination, s))) return rc;
+      }
       // g_b(n) = mu_n^H L_b psi_n
-      HIP_TRY(magnus::launch_frechet_init(seg_psi + (n - n0) * dim, X2, (int)dim, s));
-      if ((rc = launch_multi(ctx, h, Bx, tol_e, opts->early_termination, s))) return rc;
-      if ((rc = flush_fused_check(ctx, s))) return rc;
-      HIP_TRY(magnus::launch_cdot(mu, 1, Y2, 2, dim, ctx->partials, g + 2 * n + 1, s));
+      HIP_TRY(magnus::launch_cdot(mu, 1, lb, 2, dim, ctx->dots, g + 2 * n + 1, s));
       // lambda_n = E_b^H mu_n
       rc = run_exponential(ctx, ExpOp{h, 0.5, beta_of(n), 0.0}, -tau, mu, lam, tol_e, opts, &acc, s);
       if (rc) return rc;
@@ -2942,6 +3164,8 @@ int magnus_propagate_adjoint(magnus_ctx* ctx, const magnus_hamiltonian* h, doubl
   std::vector<double2> hg(2 * nsteps + 1);
   HIP_TRY(hipMemcpyAsync(hg.data(), g, sizeof(double2) * hg.size(), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
+  for (const double2& v : hg)
+    if (!is_fin(v.x) || !is_fin(v.y)) ctx->sticky_status |= 1;
   const std::complex<double> z(hg[2 * nsteps].x, hg[2 * nsteps].y);
   *loss = 1.0 - std::norm(z);
   for (int32_t p = 0; p < nparams; ++p) {

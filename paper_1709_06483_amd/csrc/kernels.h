@@ -176,10 +176,10 @@ struct CodedDev {
   int rows;          // rows per block (a multiple of 64)
 };
 int code_rows(int dim);
-int code_grid(int dim);
+int code_grid(int dim, int rows);
 // Code T's terms into C; *bad_blocks (if not null) grows by the blocks that could not be.
 hipError_t launch_code_build(const CodeTerms& T, int dim, const CodedDev& C, int* bad_blocks, hipStream_t s);
-// One Leja iteration on a1 T0 x1 + a2 T1 x2 (+ a3 T2 x1), or mode kSplitComm, on code_grid(dim) workgroups.
+// One Leja iteration on a1 T0 x1 + a2 T1 x2 (+ a3 T2 x1), or mode kSplitComm, on code_grid(dim, C.rows) workgroups.
 hipError_t launch_coded_iter(int mode, const CodeTerms& T, int dim, const CodedDev& C, const IterArgs& a, double a3,
                              hipStream_t s);
 
@@ -296,6 +296,42 @@ struct RaggedArgs {
 };
 int ragged_grid(int dim, int B);
 hipError_t launch_csr2_ragged(RaggedArgs r, int B, hipStream_t s);
+// ---- pairs of states on coded CSR terms (kernels_coded_pairs.hip) ----
+constexpr int kMaxPairProblems = 8;
+struct PairProblem {
+  CsrDev t1, t2;
+  CodedDev C;
+  int dim;
+  int npairs;
+  int blocks;            // blocks of C.rows rows (filled by launch_coded_pairs, with block0)
+  int block0;            // first workgroup of the problem
+  const double2* x;      // w_{i-1} (v on the first iteration); pair p, interleaved, at 2 dim p
+  double2* wout;         // w_i
+  double2* pacc;         // p
+  Slot* slots;           // pair p's two columns at 2 p
+  double* partials;      // pair p at 4 blocks p: per block |w|^2 of column 0, of column 1, |v|^2 likewise
+  const double* prev_partials;  // the previous iteration's
+  const ColParam* prm;   // pair p's two columns at 2 p, of this iteration
+  const ColParam* prev;  // of the previous iteration
+  int first, early, iter;
+  double tol;
+};
+struct PairArgs {
+  PairProblem p[kMaxPairProblems];
+  int np;
+};
+// Rows per block for npairs pairs (a multiple of 64, at least min_rows).
+int code_pair_rows(int dim, int npairs, int min_rows);
+// One Leja iteration of every pair (`frechet`: pairs are block vectors of
+// [[H, H2], [0, H]], one stop test each); makes the previous iteration's stop test.
+hipError_t launch_coded_pairs(bool frechet, PairArgs& A, hipStream_t s);
+hipError_t launch_coded_pairs_check(const PairArgs& A, hipStream_t s);
+// States 2 p, 2 p + 1 (dim entries each, back to back) to and from interleaved pairs.
+hipError_t launch_pack_pairs(const double2* src, double2* dst, int dim, int npairs, hipStream_t s);
+hipError_t launch_unpack_pairs(const double2* src, double2* dst, int dim, int npairs, hipStream_t s);
+// dst = the pairs [0; u], [0; v].
+hipError_t launch_frechet_pairs_init(const double2* u, const double2* v, double2* dst, int dim, hipStream_t s);
+
 // Interleave / de-interleave B states of dim entries (optionally scaling by a
 // per-state phase is not needed: plain copies).
 hipError_t launch_pack(const double2* src, double2* dst, int dim, int B, hipStream_t s);

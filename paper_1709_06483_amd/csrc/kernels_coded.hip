@@ -23,7 +23,7 @@
 // cold by every launch: the three-term iteration at n = 14 20 us, 6.4 now).
 #include <type_traits>
 
-#include "device_common.h"
+#include "coded_device.h"
 
 namespace magnus {
 namespace {
@@ -297,151 +297,6 @@ __global__ __launch_bounds__(kThreads, 4) void code_build_kernel(CodeTerms T, in
   }
 }
 
-// A row of a block that is not coded, from the CSR arrays (its quarter q of the entries).
-__device__ __forceinline__ d2 plain_row(const CsrDev& M, int row, int dim, int q, const d2* x) {
-  d2 acc = {0.0, 0.0};
-  if (row < dim) {
-    const d2* v = reinterpret_cast<const d2*>(M.val);
-    const int e1 = M.rp[row + 1];
-    for (int e = M.rp[row] + q; e < e1; e += 4) acc += cmul(v[e], x[M.ci[e]]);
-  }
-  return acc;
-}
-
-// The dictionary as an iteration uses it, values times their term's coefficient.
-struct RealEntry {
-  double val;
-  int offset, pad;
-};
-struct FullEntry {
-  double2 val;
-  int offset, pad[3];
-};
-union DictLds {
-  FullEntry full[kCodeMax + 1];
-  RealEntry real[kCodeMax + 1];
-};
-
-__device__ __forceinline__ d2 code_mul(double2 h, d2 x) { return cmul(tod2(h), x); }
-__device__ __forceinline__ d2 code_mul(double h, d2 x) { return rmul(h, x); }
-
-// A state as a buffer of num_records bytes: a load outside it returns zeros
-// without an access, which is what a lane without an entry (offset kNoEntry) does.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t state_buffer(const d2* x, int dim) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<d2*>(x), 0, dim * 16, 0x00020000);
-}
-__device__ __forceinline__ d2 buffer_at(__amdgpu_buffer_rsrc_t x, unsigned offset) {
-  typedef unsigned u4 __attribute__((ext_vector_type(4)));
-  const u4 v = __builtin_amdgcn_raw_buffer_load_b128(x, (int)offset, 0, 0);
-  return __builtin_bit_cast(d2, v);
-}
-
-// The next K rounds, a code to a byte of `words`: all gathers issued before the first product.
-template <int K, class Entry>
-__device__ __forceinline__ void code_rounds(const Entry* dict, const unsigned (&words)[2], unsigned row16,
-                                            __amdgpu_buffer_rsrc_t x, d2& sum) {
-  d2 g[K];
-#pragma unroll
-  for (int k = 0; k < K; ++k)
-    g[k] = buffer_at(x, row16 + (unsigned)dict[(words[k / 4] >> (8 * (k & 3))) & 255u].offset);
-  asm volatile("" ::: "memory");  // the values are read once the gathers are out: held with them they cost waves
-#pragma unroll
-  for (int k = 0; k < K; ++k) sum += code_mul(dict[(words[k / 4] >> (8 * (k & 3))) & 255u].val, g[k]);
-}
-
-// A slice's codes: the words loaded ahead, and where to find all of them.
-struct CodeWords {
-  unsigned ahead[kCodeAhead];
-  const unsigned* first;  // word k < kCodeAhead at first[k]
-  const unsigned* more;   // word k at more[(k - kCodeAhead) * 64] after them
-  int rounds;             // of the slice
-};
-
-// The codes of the eight rounds from rd on (uniform; bytes past the slice's rounds are not used).
-__device__ __forceinline__ void code_window(const CodeWords& w, int rd, unsigned (&out)[2]) {
-  const int i = rd >> 2;
-  unsigned a[3];
-  static_assert(kCodeAhead == 3, "three words ahead");
-  if (w.rounds <= 4 * kCodeAhead) {
-    a[0] = i == 0 ? w.ahead[0] : i == 1 ? w.ahead[1] : w.ahead[2];
-    a[1] = i == 0 ? w.ahead[1] : w.ahead[2];
-    a[2] = w.ahead[2];
-  } else {
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const int g = min(i + k, (w.rounds - 1) >> 2);
-      a[k] = g < kCodeAhead ? w.first[g] : w.more[(g - kCodeAhead) * 64];
-    }
-  }
-  out[0] = __builtin_amdgcn_alignbyte(a[1], a[0], rd & 3);
-  out[1] = __builtin_amdgcn_alignbyte(a[2], a[1], rd & 3);
-}
-
-// The lane's products over rounds [rd, end) of a slice, in pieces of eight
-// rounds (four where values are complex, whose registers would leave fewer
-// waves), then of 4, 2 or 1.
-template <class Entry>
-__device__ __forceinline__ d2 code_stream(const Entry* dict, const CodeWords& w, int rd, int end, unsigned row16,
-                                          __amdgpu_buffer_rsrc_t x) {
-  constexpr bool kWide = sizeof(Entry) == sizeof(RealEntry);
-  d2 sum = {0.0, 0.0};
-#pragma unroll 1
-  while (rd < end) {
-    const int left = end - rd;
-    unsigned words[2];
-    code_window(w, rd, words);
-    if (kWide && left > 4) {
-      if (left < 8) words[1] &= (1u << (8 * (left - 4))) - 1u;
-      code_rounds<8>(dict, words, row16, x, sum);
-      rd += 8;
-    } else if (left > 2) {
-      if (left < 4) words[0] &= 0xFFFFFFu;
-      code_rounds<4>(dict, words, row16, x, sum);
-      rd += 4;
-    } else if (left == 2) {
-      code_rounds<2>(dict, words, row16, x, sum);
-      rd += 2;
-    } else {
-      code_rounds<1>(dict, words, row16, x, sum);
-      rd += 1;
-    }
-  }
-  return sum;
-}
-
-__device__ __forceinline__ void swap32(double& a, double& b) {
-  typedef unsigned u2 __attribute__((ext_vector_type(2)));
-  union { double d; unsigned u[2]; } x{a}, y{b};
-  for (int k = 0; k < 2; ++k) {
-    const u2 r = __builtin_amdgcn_permlane32_swap(x.u[k], y.u[k], false, false);
-    x.u[k] = r.x;
-    y.u[k] = r.y;
-  }
-  a = x.d;
-  b = y.d;
-}
-__device__ __forceinline__ void swap16(double& a, double& b) {
-  typedef unsigned u2 __attribute__((ext_vector_type(2)));
-  union { double d; unsigned u[2]; } x{a}, y{b};
-  for (int k = 0; k < 2; ++k) {
-    const u2 r = __builtin_amdgcn_permlane16_swap(x.u[k], y.u[k], false, false);
-    x.u[k] = r.x;
-    y.u[k] = r.y;
-  }
-  a = x.d;
-  b = y.d;
-}
-
-// Lane 16 j + r gets the sum of y_j over the lanes 16 q + r: a transposing
-// reduction, two exchanges instead of eight shuffles and adds.
-__device__ __forceinline__ double quarter_sums(double y0, double y1, double y2, double y3) {
-  swap32(y0, y2);  // y0: rows 0, 1 of y0, then of y2; y2: rows 2, 3 likewise
-  swap32(y1, y3);
-  double a = y0 + y2, b = y1 + y3;
-  swap16(a, b);  // a: rows 0 of y0, y1, y2, y3; b: rows 1
-  return a + b;
-}
-
 // MODE kLeja: y = a1 H1 x1 + a2 H2 x2 (+ a3 K x1 with NT = 3), then the Leja
 // update; kSplitComm as in the streamed kernel.  A wave takes STEPS slices of
 // 16 rows at a time, four lanes to a row (lane = 16 q + r; lane q takes the
@@ -528,7 +383,7 @@ __global__ __launch_bounds__(THREADS, 4) void coded_iter_kernel(CodeTerms T, int
     const bool mine = own < dim && q < STEPS;
     // kLeja: the terms' sum with their coefficients; kSplitComm: both products
     constexpr int NR = MODE == kSplitComm ? 2 : 1;
-    d2 part[STEPS][NR];
+    SliceSums<STEPS> sums[NR];
 #pragma unroll 1
     for (int j = 0; j < STEPS; ++j) {
       const int row = row0 + 16 * j + r;
@@ -577,30 +432,11 @@ __global__ __launch_bounds__(THREADS, 4) void coded_iter_kernel(CodeTerms T, int
         }
       }
 #pragma unroll
-      for (int k = 0; k < STEPS; ++k)
-        if (k == j)  // uniform
-#pragma unroll
-          for (int i = 0; i < NR; ++i) part[k][i] = sum[i];
+      for (int i = 0; i < NR; ++i) sums[i].put(j, sum[i]);
     }
     d2 res[NR];
 #pragma unroll
-    for (int i = 0; i < NR; ++i) {
-      if constexpr (STEPS == 4) {
-        res[i].x = quarter_sums(part[0][i].x, part[1][i].x, part[2][i].x, part[3][i].x);
-        res[i].y = quarter_sums(part[0][i].y, part[1][i].y, part[2][i].y, part[3][i].y);
-      } else {
-#pragma unroll
-        for (int j = 0; j < STEPS; ++j) {
-          d2 v = part[j][i];
-#pragma unroll
-          for (int off = 32; off >= 16; off >>= 1) {
-            v.x += __shfl_xor(v.x, off, 64);
-            v.y += __shfl_xor(v.y, off, 64);
-          }
-          if (STEPS == 1 || q == j) res[i] = v;
-        }
-      }
-    }
+    for (int i = 0; i < NR; ++i) res[i] = sums[i].total(q);
     if (mine) {
       auto diag_part = [&](int t) {
         d2 x = w_old;
@@ -660,13 +496,10 @@ int code_rows(int dim) {
   return r;
 }
 
-int code_grid(int dim) {
-  const int r = code_rows(dim);
-  return (dim + r - 1) / r;
-}
+int code_grid(int dim, int rows) { return (dim + rows - 1) / rows; }
 
 hipError_t launch_code_build(const CodeTerms& T, int dim, const CodedDev& C, int* bad_blocks, hipStream_t s) {
-  const int g = code_grid(dim);
+  const int g = code_grid(dim, C.rows);
   if (T.n == 2) code_build_kernel<2><<<g, kThreads, 0, s>>>(T, dim, C, bad_blocks);
   else if (T.n == 3) code_build_kernel<3><<<g, kThreads, 0, s>>>(T, dim, C, bad_blocks);
   else return hipErrorInvalidValue;
@@ -675,7 +508,7 @@ hipError_t launch_code_build(const CodeTerms& T, int dim, const CodedDev& C, int
 
 hipError_t launch_coded_iter(int mode, const CodeTerms& T, int dim, const CodedDev& C, const IterArgs& a, double a3,
                              hipStream_t s) {
-  const int g = code_grid(dim);
+  const int g = code_grid(dim, C.rows);
 #define MAGNUS_CODED(M, N)                                                                  \
   do {                                                                                      \
     if (C.rows == 64) coded_iter_kernel<M, N, 1, 256><<<g, 256, 0, s>>>(T, dim, C, a, a3);  \

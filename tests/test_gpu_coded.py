@@ -185,3 +185,85 @@ def test_coded_m4_run_matches_oracle(comm, monkeypatch):
     ref = mg.propagate("M4", mg.two_term(H1.to_scipy(), H2.to_scipy(), f), tau, steps, psi0, expm="taylor")
     assert rel(psi.cpu().numpy(), ref) <= 20 * 1e-12 * steps
     ctx.close()
+
+
+def batch_run(monkeypatch, coded, H1, H2, psi0, f, tol=1e-12, widen=1.0):
+    monkeypatch.setenv("MAGNUS_CODED", coded)
+    monkeypatch.setenv("MAGNUS_PERSIST", "0")
+    ctx = B.Context(max_dim=H1.dim, max_batch=psi0.shape[0])
+    ham = B.magnus_spectral_bounds(ctx, B.DeviceHamiltonian.from_csr(H1, H2))
+    for T in (ham.struct.H1, ham.struct.H2):
+        c, r = 0.5 * (T.lam_min + T.lam_max), 0.5 * (T.lam_max - T.lam_min)
+        T.lam_min, T.lam_max = c - widen * r, c + widen * r
+    psi = torch.from_numpy(psi0).cuda()
+    _, st = B.propagate(ctx, ham, B.CF4, 0.05, f, psi, opts=B.leja_opts(tol), stats=True)
+    ctx.close()
+    return psi.cpu().numpy(), st
+
+
+# pairs, pairs and a single state, eight pairs (an XCD per pair) and more; each state with its own field, so
+# with its own degree and stop; enclosures widened so that early termination cuts the a priori degree
+@pytest.mark.parametrize("batch", [2, 3, 5, 16, 21])
+@pytest.mark.parametrize("kind,N", [("real", 1000), ("imaginary", 65), ("complex", 1000), ("wide", 300), ("too many", 4133),
+                                    ("empty", 17)])
+def test_coded_batches_match_oracle(kind, N, batch, monkeypatch):
+    A1, A2 = terms(kind, N)
+    psi0 = inputs.random_states(N, seed=N + batch, batch=batch)
+    f = np.stack([np.array([[0.2, 0.4], [0.5, 0.1]]) * (0.2 + b) for b in range(batch)])
+    got, st = batch_run(monkeypatch, "2", csr(A1), csr(A2), psi0, f, widen=2.0)
+    want, sw = batch_run(monkeypatch, "0", csr(A1), csr(A2), psi0, f, widen=2.0)
+    if batch != 21:  # (20 + 1 states on coded terms, 16 + 4 + 1 else: a group shares the largest substep count)
+        assert st["iters"] == sw["iters"] and st["planned_iters"] == sw["planned_iters"]
+        assert rel(got, want) <= 1e-13
+    for b in (0, batch - 1):
+        ref = psi0[b]
+        for n in range(2):
+            for w in ((mg.CF4_ALPHA2, mg.CF4_ALPHA1), (mg.CF4_ALPHA1, mg.CF4_ALPHA2)):
+                ref = oracle(A1, A2, 0.5, w[0] * f[b, n, 0] + w[1] * f[b, n, 1], 0.0, 0.05, ref)
+        assert rel(got[b], ref) <= 20 * 1e-12 * 4
+
+
+# one block of rows (several passes of a wave), blocks of 64 to 1024 rows
+@pytest.mark.parametrize("N,batch", [(65536, 2), (70001, 4), (262145, 2), (262145, 16)])
+def test_coded_batches_match_csr_kernels(N, batch, monkeypatch):
+    A1, A2 = terms("real", N)
+    psi0 = inputs.random_states(N, seed=1, batch=batch)
+    f = np.array([[0.3, 0.5]])
+    got, st = batch_run(monkeypatch, "1", csr(A1), csr(A2), psi0, f)
+    want, sw = batch_run(monkeypatch, "0", csr(A1), csr(A2), psi0, f)
+    assert st["iters"] == sw["iters"]
+    assert rel(got, want) <= 1e-13
+
+
+def test_coded_ragged_batch_matches_csr_kernels(monkeypatch):
+    monkeypatch.setenv("MAGNUS_PERSIST", "0")
+    sizes, batch = [("real", 300), ("complex", 5000), ("too many", 20011)], 6
+    out = []
+    for coded in ("2", "0"):
+        monkeypatch.setenv("MAGNUS_CODED", coded)
+        ctx = B.Context(max_dim=sum(N for _, N in sizes), max_batch=batch)
+        probs = []
+        for kind, N in sizes:
+            ham = B.magnus_spectral_bounds(ctx, B.DeviceHamiltonian.from_csr(*map(csr, terms(kind, N))))
+            f = np.stack([np.array([[0.2, 0.4], [0.5, 0.1], [0.3, 0.3]]) * (0.5 + b) for b in range(batch)])
+            probs.append((ham, torch.from_numpy(inputs.random_states(N, seed=N, batch=batch)).cuda(), f))
+        B.magnus_propagate_ragged(ctx, probs, B.CF4, 0.05, opts=B.leja_opts(1e-12))
+        out.append([p.cpu().numpy() for _, p, _ in probs])
+        ctx.close()
+    # groups of 6 states against groups of 2, so other substep counts: each side within its six exponentials' bound
+    for a, b in zip(*out):
+        assert rel(a, b) <= 2 * 6 * 20 * 1e-12
+
+
+def test_coded_batch_reports_a_non_finite_state(monkeypatch):
+    monkeypatch.setenv("MAGNUS_CODED", "2")
+    monkeypatch.setenv("MAGNUS_PERSIST", "0")
+    N = 2000
+    ctx = B.Context(max_dim=N, max_batch=4)
+    ham = B.magnus_spectral_bounds(ctx, B.DeviceHamiltonian.from_csr(*map(csr, terms("real", N))))
+    x = inputs.random_states(N, seed=2, batch=4)
+    x[2, 1999] = np.nan
+    with pytest.raises(B.MagnusError) as e:  # a plan of one iteration: only the check at the end sees it
+        B.expmv_leja(ctx, ham, 1.0, 0.5, 0.0, 1e-7, torch.from_numpy(x).cuda(), opts=B.leja_opts(1e-6), stats=True)
+    assert e.value.code == B.ENAN
+    ctx.close()
