@@ -644,7 +644,7 @@ int launch_iteration(magnus_ctx* ctx, const ExpOp& op, const ExpPlan& P, int i, 
     a.x1 = win;
     a.x2 = win;
     const int rpw = dense_rpw(ctx, h);
-    const int grid = magnus::dense2_grid(dim, op.assembled ? 1 : 2, rpw);
+    const int grid = magnus::dense2_grid(dim);
     if (int rc = setup_stop_test(ctx, P, i, grid, &a, s)) return rc;
     const bool fused = a.fused;
     HIP_TRY(timed(ctx, MAGNUS_KERNEL_DENSE_LEJA, s, [&] {
@@ -1967,7 +1967,8 @@ int magnus_create(magnus_ctx** out, int64_t max_dim, int32_t max_batch, int32_t 
   c->max_dim = max_dim;
   c->max_batch = max_batch;
   if (const char* v = getenv("MAGNUS_CSR_VARIANT")) c->csr_variant = atoi(v);
-  c->max_grid = max_dim / 8 + 2;  // the smallest row block of any iteration kernel is 8 rows
+  // the smallest row block of any CSR iteration kernel is 8 rows; the dense ones have their own grid
+  c->max_grid = std::max<int64_t>(max_dim / 8 + 2, magnus::dense2_grid((int)max_dim));
   c->scan_len = 2 * (max_dim / 4 + 2) + 3 * (max_dim / 256 + 2);
   c->nslots = std::max<int>(256, max_batch);
   if (const char* v = getenv("MAGNUS_PERSIST")) c->persist = atoi(v);

@@ -14,6 +14,13 @@ constexpr int kThreads = 256;
 
 __device__ __forceinline__ d2 cmul(d2 a, d2 b) { return d2{a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; }
 __device__ __forceinline__ d2 rmul(double s, d2 a) { return d2{s * a.x, s * a.y}; }
+// Contractions spelled out, for results that two kernels form alike bit for bit.
+__device__ __forceinline__ d2 fma_r(double s, d2 a, d2 c) {
+  return d2{__builtin_fma(s, a.x, c.x), __builtin_fma(s, a.y, c.y)};
+}
+__device__ __forceinline__ d2 fma_c(d2 a, d2 b, d2 c) {
+  return d2{__builtin_fma(-a.y, b.y, __builtin_fma(a.x, b.x, c.x)), __builtin_fma(a.y, b.x, __builtin_fma(a.x, b.y, c.y))};
+}
 __device__ __forceinline__ d2 tod2(double2 v) { return d2{v.x, v.y}; }
 __device__ __forceinline__ double2 fromd2(d2 v) { return make_double2(v.x, v.y); }
 __device__ __forceinline__ double nrm2(d2 v) { return v.x * v.x + v.y * v.y; }

@@ -213,10 +213,10 @@ struct DenseAssembly {
 hipError_t launch_dense_assemble_iter(const DenseAssembly& D, int dim, const IterArgs& a, hipStream_t s, int rpw);
 // Dense Leja iteration (mode kLeja only): two terms, or one (an assembled
 // exponent) when H2 is null.
-// rpw: rows per wave (1, 2 or 4).
+// rpw: rows per wave at a time (1, 2 or 4).
 hipError_t launch_dense2_iter(const double2* H1, const double2* H2, int dim, long long ld,
                               const IterArgs& a, hipStream_t s, int rpw = 2);
-int dense2_grid(int dim, int nterms, int rpw = 2);
+int dense2_grid(int dim);
 
 // Reduce the norm partials of the iteration launched just before (grid
 // workgroups) and write the early-termination verdict into the slot.

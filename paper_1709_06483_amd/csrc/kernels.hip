@@ -566,77 +566,176 @@ __global__ __launch_bounds__(kThreads, MODE == kLejaComm ? 6 : 7) void csr2_wave
 }
 
 // ---------------------------------------------------------------------------
-// Two-term dense iteration (row-major H1, H2).  A wave owns RPW rows; its
-// lanes stride over columns so every matrix load is a coalesced 1 KiB
-// transaction, and each gathered x_j is loaded once per lane for RPW rows and
-// both terms.
+// Dense iterations (row-major matrices), bound by the matrix bytes.  A
+// workgroup owns the rows [dim b / grid, dim (b+1) / grid) and its four waves
+// split the columns: lane l of wave q sums columns j = 64 q + l + 256 m, so
+// every matrix load is a coalesced 1 KiB transaction per wave, and a small
+// matrix still has its rows spread over every CU with few loads in each wave's
+// chain (rows split over waves instead: N = 1001 one term 10.0 us, now 6.2;
+// first M4 iteration with its assembly 26.6, now 14.8).  A wave works on RPW
+// rows at a time and loads x_j once for them (and both terms); a group's loads
+// (UNR column steps) are issued together.  Workgroups go round the XCDs in the
+// order of their rows, so that each reads its share of the rows kept in the
+// MALL and of those that stream (rows in a contiguous range per XCD: N = 8192
+// 160.6 us, now 153 = 7.0 TB/s from HBM and MALL together).
 // ---------------------------------------------------------------------------
+constexpr int kDenseMaxRows = 256;  // rows of a workgroup: one thread each for the update
+
+// Sum over the wave's 64 lanes, in every lane, without LDS traffic: rotations
+// within rows of 16 lanes, then swaps of rows and of halves.
+__device__ __forceinline__ double lanes_sum(double v) {
+  union U {
+    double d;
+    unsigned u[2];
+  };
+  auto rotated = [](double x, auto ctrl) {
+    U a, b;
+    a.d = x;
+    for (int k = 0; k < 2; ++k) b.u[k] = __builtin_amdgcn_mov_dpp(a.u[k], decltype(ctrl)::value, 0xf, 0xf, true);
+    return b.d;
+  };
+  v += rotated(v, std::integral_constant<int, 0x128>{});  // row_ror:8
+  v += rotated(v, std::integral_constant<int, 0x124>{});
+  v += rotated(v, std::integral_constant<int, 0x122>{});
+  v += rotated(v, std::integral_constant<int, 0x121>{});
+  U a, x, y;
+  a.d = v;
+  for (int k = 0; k < 2; ++k) {
+    const auto r = __builtin_amdgcn_permlane16_swap(a.u[k], a.u[k], false, false);
+    x.u[k] = r[0];
+    y.u[k] = r[1];
+  }
+  a.d = x.d + y.d;
+  for (int k = 0; k < 2; ++k) {
+    const auto r = __builtin_amdgcn_permlane32_swap(a.u[k], a.u[k], false, false);
+    x.u[k] = r[0];
+    y.u[k] = r[1];
+  }
+  return x.d + y.d;
+}
+
+// The rows of a workgroup's products: row by row group the loads of F::load
+// and products of F::use over this wave's columns, the lanes' sums to
+// part[row][wave].  The first group's loads are issued before the stop test,
+// whose own loads they do not depend on; false if the substep has stopped.
+template <int RPW, int UNR, class F>
+__device__ __forceinline__ bool dense_rows(const IterArgs& a, int dim, int row0, int rows, F& f, d2 (*part)[kThreads / 64],
+                                           double* fz) {
+  constexpr int kStep = kThreads * UNR;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  StopLoads stop;
+  stop_loads(a, stop);
+  f.load(row0, tid);
+  __builtin_amdgcn_sched_barrier(0);
+  if (stop_verdict(a, stop, fz)) return false;
+  int r = 0, j = tid;  // the group in flight
+  for (;;) {
+    f.use(row0 + r, j);
+    j += kStep;
+    if (j - tid >= dim) {
+      f.sums(part, r, lane, wv);
+      r += RPW;
+      j = tid;
+      if (r >= rows) break;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    f.load(row0 + r, j);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  __syncthreads();
+  return true;
+}
+
+__device__ __forceinline__ void dense_update(const IterArgs& a, int row0, int rows, d2 (*part)[kThreads / 64]) {
+  const int tid = threadIdx.x;
+  double pw = 0.0, pv = 0.0;
+  if (tid < rows) {
+    d2 y = part[tid][0];
+#pragma unroll
+    for (int k = 1; k < kThreads / 64; ++k) y += part[tid][k];
+    leja_row(a, row0 + tid, y, pw, pv);
+  }
+  block_partials(a, pw, pv);
+}
+
+__device__ __forceinline__ int dense_row0(int b, int dim) { return (int)((long long)dim * b / gridDim.x); }
+
 // Rows below keep_rows are read with normal loads so that they stay in the
 // memory-side cache (MALL) from one iteration to the next (the matrix is read
 // again by every iteration); the rest stream through non-temporally.
-template <int RPW, int NT>
-__global__ __launch_bounds__(kThreads) void dense2_iter_kernel(const double2* H1, const double2* H2,
-                                                              int dim, long long ld, IterArgs a, int keep_rows) {
-  __shared__ double fz[kFuseLds];
-  if (iteration_stopped(a, fz)) return;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int L = xcd_remap(blockIdx.x, gridDim.x);
-  const int rbase = (L * (kThreads / 64) + wv) * RPW;
-  const d2* x = reinterpret_cast<const d2*>(a.x1);
-  const d2* A1 = reinterpret_cast<const d2*>(H1);
-  const d2* A2 = reinterpret_cast<const d2*>(H2);
-  d2 acc1[RPW], acc2[RPW];
+template <int RPW, int UNR, int NT, bool STREAM>
+struct DenseProduct {
+  const d2 *x, *A1, *A2;
+  int dim, last;  // last: the workgroup's last row
+  long long ld_row;
+  double a1, a2;
+  d2 xj[UNR], h1[UNR][RPW], h2[UNR][NT == 2 ? RPW : 1], acc1[RPW], acc2[RPW];
+  __device__ __forceinline__ void clear() {
 #pragma unroll
-  for (int r = 0; r < RPW; ++r) { acc1[r] = d2{0.0, 0.0}; acc2[r] = d2{0.0, 0.0}; }
-  int nr = min(RPW, dim - rbase);
-  if (nr < 0) nr = 0;
-  // columns in groups of UNR per lane: the same matrix bytes in flight per wave for one term or two
-  constexpr int UNR = NT == 2 ? 2 : 4;
-  auto run = [&](auto streaming) {
-    for (int j0 = lane; j0 < dim; j0 += 64 * UNR) {
+    for (int r = 0; r < RPW; ++r) acc1[r] = acc2[r] = d2{0.0, 0.0};
+  }
+  // columns past the end read the last one and are not used
+  __device__ __forceinline__ void load(int row, int j0) {
+    auto ld = [](const d2* p) {
+      if constexpr (STREAM) return __builtin_nontemporal_load(p);
+      else return *p;
+    };
 #pragma unroll
-      for (int u = 0; u < UNR; ++u) {
-        const int j = j0 + 64 * u;
-        if (j < dim) {
-          const d2 xj = x[j];
+    for (int u = 0; u < UNR; ++u) {
+      const int j = min(j0 + kThreads * u, dim - 1);
+      xj[u] = x[j];
 #pragma unroll
-          for (int r = 0; r < RPW; ++r) {
-            if (r < nr) {
-              const long long off = (long long)(rbase + r) * ld + j;
-              if constexpr (decltype(streaming)::value) {
-                acc1[r] += cmul(__builtin_nontemporal_load(A1 + off), xj);
-                if constexpr (NT == 2) acc2[r] += cmul(__builtin_nontemporal_load(A2 + off), xj);
-              } else {
-                acc1[r] += cmul(A1[off], xj);
-                if constexpr (NT == 2) acc2[r] += cmul(A2[off], xj);
-              }
-            }
-          }
-        }
+      for (int r = 0; r < RPW; ++r) {
+        if (r > 0 && row + r > last) break;
+        const long long off = (row + r) * ld_row;
+        h1[u][r] = ld(A1 + off + j);
+        if constexpr (NT == 2) h2[u][r] = ld(A2 + off + j);
       }
-    }
-  };
-  if (rbase < keep_rows) run(std::false_type{});
-  else run(std::true_type{});
-  double pw = 0.0, pv = 0.0;
-#pragma unroll
-  for (int r = 0; r < RPW; ++r) {
-    d2 s1 = acc1[r], s2 = acc2[r];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      s1.x += __shfl_xor(s1.x, off, 64);
-      s1.y += __shfl_xor(s1.y, off, 64);
-      if constexpr (NT == 2) {
-        s2.x += __shfl_xor(s2.x, off, 64);
-        s2.y += __shfl_xor(s2.y, off, 64);
-      }
-    }
-    if (lane == r && r < nr) {
-      const d2 y = NT == 2 ? rmul(a.a1, s1) + rmul(a.a2, s2) : rmul(a.a1, s1);
-      leja_row(a, rbase + r, y, pw, pv);
     }
   }
-  block_partials(a, pw, pv);
+  __device__ __forceinline__ void use(int, int j0) {
+#pragma unroll
+    for (int u = 0; u < UNR; ++u)
+      if (j0 + kThreads * u < dim)
+#pragma unroll
+        for (int r = 0; r < RPW; ++r) {
+          acc1[r] = fma_c(h1[u][r], xj[u], acc1[r]);
+          if constexpr (NT == 2) acc2[r] = fma_c(h2[u][r], xj[u], acc2[r]);
+        }
+  }
+  __device__ __forceinline__ void sums(d2 (*part)[kThreads / 64], int r0, int lane, int wv) {
+#pragma unroll
+    for (int r = 0; r < RPW; ++r) {
+      d2 y = rmul(a1, acc1[r]);
+      if constexpr (NT == 2) y += rmul(a2, acc2[r]);
+      y = d2{lanes_sum(y.x), lanes_sum(y.y)};
+      if (lane == 0 && r0 + r < kDenseMaxRows) part[r0 + r][wv] = y;
+    }
+    clear();
+  }
+};
+
+template <int RPW, int UNR, int NT>
+__global__ __launch_bounds__(kThreads) void dense2_iter_kernel(const double2* H1, const double2* H2, int dim,
+                                                              long long ld, IterArgs a, int keep_rows) {
+  __shared__ double fz[kFuseLds];
+  __shared__ d2 part[kDenseMaxRows][kThreads / 64];
+  const int row0 = dense_row0(blockIdx.x, dim), rows = dense_row0(blockIdx.x + 1, dim) - row0;
+  auto products = [&](auto streaming) {
+    DenseProduct<RPW, UNR, NT, decltype(streaming)::value> f;
+    f.x = reinterpret_cast<const d2*>(a.x1);
+    f.A1 = reinterpret_cast<const d2*>(H1);
+    f.A2 = reinterpret_cast<const d2*>(H2);
+    f.dim = dim;
+    f.last = row0 + rows - 1;
+    f.ld_row = ld;
+    f.a1 = a.a1;
+    f.a2 = a.a2;
+    f.clear();
+    return dense_rows<RPW, UNR>(a, dim, row0, rows, f, part, fz);
+  };
+  if (!(row0 < keep_rows ? products(std::false_type{}) : products(std::true_type{}))) return;
+  dense_update(a, row0, rows, part);
 }
 
 // The first iteration of an exponential on dense terms fused with the
@@ -650,55 +749,58 @@ __global__ __launch_bounds__(kThreads) void dense2_iter_kernel(const double2* H1
 // result is bitwise that of assembling first and iterating on the assembled
 // matrix; the separate assembly pass and one full read of the assembled
 // matrix disappear.
-template <int RPW, bool WITH_K>
-__global__ __launch_bounds__(kThreads) void dense_assemble_iter_kernel(DenseAssembly D, int dim, IterArgs a) {
-  __shared__ double fz[kFuseLds];
-  if (iteration_stopped(a, fz)) return;  // a first iteration always runs
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int L = xcd_remap(blockIdx.x, gridDim.x);
-  const int rbase = (L * (kThreads / 64) + wv) * RPW;
-  const d2* x = reinterpret_cast<const d2*>(a.x1);
-  const d2* A1 = reinterpret_cast<const d2*>(D.H1);
-  const d2* A2 = reinterpret_cast<const d2*>(D.H2);
-  const d2* Kp = reinterpret_cast<const d2*>(D.K);
-  d2 acc[RPW];
-#pragma unroll
-  for (int r = 0; r < RPW; ++r) acc[r] = d2{0.0, 0.0};
-  int nr = min(RPW, dim - rbase);
-  if (nr < 0) nr = 0;
-  constexpr int UNR = 2;
-  for (int j0 = lane; j0 < dim; j0 += 64 * UNR) {
+template <int RPW, int UNR, bool WITH_K>
+struct DenseAssembleProduct : DenseProduct<RPW, UNR, 1, true> {
+  using Base = DenseProduct<RPW, UNR, 1, true>;
+  DenseAssembly D;
+  d2 b[UNR][RPW], k[UNR][WITH_K ? RPW : 1];
+  __device__ __forceinline__ void load(int row, int j0) {
 #pragma unroll
     for (int u = 0; u < UNR; ++u) {
-      const int j = j0 + 64 * u;
-      if (j < dim) {
-        const d2 xj = x[j];
+      const int j = min(j0 + kThreads * u, this->dim - 1);
+      this->xj[u] = this->x[j];
 #pragma unroll
-        for (int r = 0; r < RPW; ++r) {
-          if (r < nr) {
-            const long long row = rbase + r;
-            d2 h = rmul(D.ca, __builtin_nontemporal_load(A1 + row * D.ld + j)) +
-                   rmul(D.cb, __builtin_nontemporal_load(A2 + row * D.ld + j));
-            if constexpr (WITH_K) h += rmul(D.ck, __builtin_nontemporal_load(Kp + row * dim + j));
-            __builtin_nontemporal_store(h, reinterpret_cast<d2*>(D.out) + row * dim + j);
-            acc[r] += cmul(h, xj);
-          }
-        }
+      for (int r = 0; r < RPW; ++r) {
+        const long long row_r = min(row + r, this->last);
+        this->h1[u][r] = __builtin_nontemporal_load(reinterpret_cast<const d2*>(D.H1) + row_r * D.ld + j);
+        b[u][r] = __builtin_nontemporal_load(reinterpret_cast<const d2*>(D.H2) + row_r * D.ld + j);
+        if constexpr (WITH_K)
+          k[u][r] = __builtin_nontemporal_load(reinterpret_cast<const d2*>(D.K) + row_r * this->dim + j);
       }
     }
   }
-  double pw = 0.0, pv = 0.0;
+  __device__ __forceinline__ void use(int row, int j0) {
 #pragma unroll
-  for (int r = 0; r < RPW; ++r) {
-    d2 s1 = acc[r];
+    for (int u = 0; u < UNR; ++u) {
+      const int j = j0 + kThreads * u;
+      if (j < this->dim)
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      s1.x += __shfl_xor(s1.x, off, 64);
-      s1.y += __shfl_xor(s1.y, off, 64);
+        for (int r = 0; r < RPW; ++r) {
+          d2 h = fma_r(D.ca, this->h1[u][r], rmul(D.cb, b[u][r]));
+          if constexpr (WITH_K) h = fma_r(D.ck, k[u][r], h);
+          this->h1[u][r] = h;
+          if (row + r <= this->last)
+            __builtin_nontemporal_store(h, reinterpret_cast<d2*>(D.out) + (long long)(row + r) * this->dim + j);
+        }
     }
-    if (lane == r && r < nr) leja_row(a, rbase + r, rmul(a.a1, s1), pw, pv);
+    Base::use(row, j0);
   }
-  block_partials(a, pw, pv);
+};
+
+template <int RPW, int UNR, bool WITH_K>
+__global__ __launch_bounds__(kThreads) void dense_assemble_iter_kernel(DenseAssembly D, int dim, IterArgs a) {
+  __shared__ double fz[kFuseLds];
+  __shared__ d2 part[kDenseMaxRows][kThreads / 64];
+  const int row0 = dense_row0(blockIdx.x, dim), rows = dense_row0(blockIdx.x + 1, dim) - row0;
+  DenseAssembleProduct<RPW, UNR, WITH_K> f;
+  f.x = reinterpret_cast<const d2*>(a.x1);
+  f.dim = dim;
+  f.last = row0 + rows - 1;
+  f.a1 = a.a1;
+  f.D = D;
+  f.clear();
+  if (!dense_rows<RPW, UNR>(a, dim, row0, rows, f, part, fz)) return;
+  dense_update(a, row0, rows, part);
 }
 
 // ---------------------------------------------------------------------------
@@ -966,25 +1068,29 @@ hipError_t launch_dense_gershgorin(const double2* H, int dim, long long ld, doub
   return hipGetLastError();
 }
 
-// Rows per wave: 1, 2 or 4 (magnus_autotune times them on the caller's
-// terms; 2 by default: with 8192 rows that is 16 waves per CU, and more rows
-// per wave leave too few waves to cover the memory latency).
-int dense2_grid(int dim, int nterms, int rpw) {
-  (void)nterms;
-  const int rows_per_block = rpw * (kThreads / 64);
-  return (dim + rows_per_block - 1) / rows_per_block;
-}
+// Two workgroups on every CU, each with an equal share of the rows (one-term
+// iteration, us, against a workgroup per 8 rows, whose number is rarely a
+// multiple of the CUs': N = 4772 58.5 / 61.8, 5100 64.5 / 82.2, 8192
+// 153 / 161; 640 and 1024 workgroups 63.5 and 65.3 at N = 4772); a row each
+// where there are fewer rows.
+constexpr int kDenseGrid = 512;
+int dense2_grid(int dim) { return std::min(dim, std::max(kDenseGrid, (dim + kDenseMaxRows - 1) / kDenseMaxRows)); }
+
+// Rows per wave at a time: one where every workgroup has one row, else 1, 2 or
+// 4 (magnus_autotune times them on the caller's terms; 2 by default).
 
 // MALL budget kept for matrix rows: its 256 MiB less a margin and the vectors
 // an iteration touches (x, w and p read, w and p written).
 constexpr long long kDenseMallKeepBytes = 240LL << 20;
 
 hipError_t launch_dense_assemble_iter(const DenseAssembly& D, int dim, const IterArgs& a, hipStream_t s, int rpw) {
-  const int g = dense2_grid(dim, 1, rpw);
+  const int g = dense2_grid(dim);
+  if (g <= 0) return hipSuccess;
+  if (g == dim) rpw = 1;
 #define MAGNUS_DENSE_ASM_CASE(R)                                                        \
   case R:                                                                               \
-    if (D.K) dense_assemble_iter_kernel<R, true><<<g, kThreads, 0, s>>>(D, dim, a);      \
-    else dense_assemble_iter_kernel<R, false><<<g, kThreads, 0, s>>>(D, dim, a);         \
+    if (D.K) dense_assemble_iter_kernel<R, 4 / R, true><<<g, kThreads, 0, s>>>(D, dim, a);      \
+    else dense_assemble_iter_kernel<R, 4 / R, false><<<g, kThreads, 0, s>>>(D, dim, a);         \
     break;
   switch (rpw) {
     MAGNUS_DENSE_ASM_CASE(1)
@@ -1001,11 +1107,13 @@ hipError_t launch_dense2_iter(const double2* H1, const double2* H2, int dim, lon
   const long long row_bytes = 16LL * ld * (H2 ? 2 : 1);
   const long long keep = std::max(0LL, kDenseMallKeepBytes - 80LL * dim) / std::max(1LL, row_bytes);
   const int keep_rows = (int)std::min<long long>(keep, dim);
-  const int g = dense2_grid(dim, H2 ? 2 : 1, rpw);
+  const int g = dense2_grid(dim);
+  if (g <= 0) return hipSuccess;
+  if (g == dim) rpw = 1;
 #define MAGNUS_DENSE_CASE(R)                                                             \
   case R:                                                                                \
-    if (H2) dense2_iter_kernel<R, 2><<<g, kThreads, 0, s>>>(H1, H2, dim, ld, a, keep_rows); \
-    else dense2_iter_kernel<R, 1><<<g, kThreads, 0, s>>>(H1, H1, dim, ld, a, keep_rows);    \
+    if (H2) dense2_iter_kernel<R, 4 / R, 2><<<g, kThreads, 0, s>>>(H1, H2, dim, ld, a, keep_rows); \
+    else dense2_iter_kernel<R, R == 1 ? 4 : 8 / R, 1><<<g, kThreads, 0, s>>>(H1, H1, dim, ld, a, keep_rows);    \
     break;
   switch (rpw) {
     MAGNUS_DENSE_CASE(1)

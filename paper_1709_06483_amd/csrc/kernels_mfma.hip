@@ -385,8 +385,8 @@ __global__ void dense_assemble_kernel(const double2* __restrict__ H1, const doub
     const d2* h2 = reinterpret_cast<const d2*>(H2) + r * ld;
     double2* o = out + r * dim;
     for (int c = threadIdx.x; c < dim; c += blockDim.x) {
-      d2 h = rmul(ca, __builtin_nontemporal_load(h1 + c)) + rmul(cb, __builtin_nontemporal_load(h2 + c));
-      if constexpr (WITH_K) h += rmul(ck, __builtin_nontemporal_load(reinterpret_cast<const d2*>(K) + r * dim + c));
+      d2 h = fma_r(ca, __builtin_nontemporal_load(h1 + c), rmul(cb, __builtin_nontemporal_load(h2 + c)));
+      if constexpr (WITH_K) h = fma_r(ck, __builtin_nontemporal_load(reinterpret_cast<const d2*>(K) + r * dim + c), h);
       o[c] = fromd2(h);
     }
   }
