@@ -44,6 +44,7 @@ def build(verbose: bool = False) -> str:
         [HIPCC, *HIP_FLAGS, "-c", os.path.join(CSRC, "kernels_comm.hip"), "-o", os.path.join(OBJ, "kernels_comm.o")],
         [HIPCC, *HIP_FLAGS, "-c", os.path.join(CSRC, "kernels_stream.hip"), "-o", os.path.join(OBJ, "kernels_stream.o")],
         [HIPCC, *HIP_FLAGS, "-c", os.path.join(CSRC, "kernels_coded.hip"), "-o", os.path.join(OBJ, "kernels_coded.o")],
+        [HIPCC, *HIP_FLAGS, "-c", os.path.join(CSRC, "kernels_m6.hip"), "-o", os.path.join(OBJ, "kernels_m6.o")],
         [HIPCC, *HIP_FLAGS, "-c", os.path.join(CSRC, "kernels_coded_pairs.hip"),
          "-o", os.path.join(OBJ, "kernels_coded_pairs.o")],
         [HIPCC, *HIP_FLAGS, "-c", os.path.join(CSRC, "abi.hip"), "-o", os.path.join(OBJ, "abi.o")],
@@ -61,7 +62,7 @@ def build(verbose: bool = False) -> str:
            os.path.join(OBJ, "kernels_mfma.o"), os.path.join(OBJ, "kernels_persist.o"),
            os.path.join(OBJ, "kernels_gemm.o"), os.path.join(OBJ, "kernels_comm.o"),
            os.path.join(OBJ, "kernels_stream.o"), os.path.join(OBJ, "kernels_coded.o"),
-           os.path.join(OBJ, "kernels_coded_pairs.o"), os.path.join(OBJ, "abi.o"),
+           os.path.join(OBJ, "kernels_coded_pairs.o"), os.path.join(OBJ, "kernels_m6.o"), os.path.join(OBJ, "abi.o"),
            "-o", tmp]
     _, rc, out = _run(cmd)
     if verbose or rc != 0:

@@ -124,8 +124,8 @@ struct magnus_ctx {
   std::tuple<const void*, const void*, const void*, const void*, int64_t> kc_key{nullptr, nullptr, nullptr, nullptr, 0};
   bool kc_codable = false;  // H1, H2 and K were found to fit the coded form (a guess at what pays, as codable)
   // magnus_csr_m6_prepare: P_a = -i[H_a, K] (a = 1, 2) as CSR for the pair K
-  // belongs to (valid while pm_key equals kc_key), their enclosures, and six
-  // work vectors of pm_ws_dim entries for the M6 iteration (u_1..u_5, y0)
+  // belongs to (valid while pm_key equals kc_key), their enclosures, and
+  // kM6Vecs work vectors of pm_ws_dim entries for the M6 iteration
   int* pm_rp[2] = {nullptr, nullptr};
   int* pm_ci[2] = {nullptr, nullptr};
   double2* pm_val[2] = {nullptr, nullptr};
@@ -508,41 +508,6 @@ int flush_pair_check(magnus_ctx* ctx, hipStream_t s) {
 }
 
 // Launch one Leja iteration (both passes for a commutator exponent).
-// One Leja iteration of Method M6 on CSR terms, the exponent's nested
-// commutators applied to vectors.  With K = i[H1,H2], P_a = -i[H_a,K] assembled
-// and U_ab = i[H_a,P_b], R_a = -i[K,P_a], the Hermitian exponent times w is
-//   y = c0 H1w + c1 H2w + c2 Kw + c3 P1w + c4 P2w
-//     + i H1 (c5 P1w + c6 P2w) - i c5 P1 H1w - i c6 P2 H1w      (c5 U11 + c6 U12)
-//     + i c7 H2 P2w - i c7 P2 H2w                                (c7 U22)
-//     - i K (c8 P1w + c9 P2w) + i c8 P1 Kw + i c9 P2 Kw          (c8 R1 + c9 R2)
-// Grouped by matrix, y = y0 + H1 u1 + H2 u2 + K u3 + P1 u4 + P2 u5 with
-// y0 the first line and u1 = i(c5 P1w + c6 P2w), u2 = i c7 P2w,
-// u3 = -i(c8 P1w + c9 P2w), u4 = i(c8 Kw - c5 H1w), u5 = i(c9 Kw - c6 H1w - c7 H2w):
-// one pass over the five matrices forms y0 and the u's row by row, a second
-// applies them and makes the Leja update, then the stop decision (ten matrix
-// reads where the thirteen products one by one would make thirteen).
-int m6_csr_iteration(magnus_ctx* ctx, const ExpOp& op, double scale, const IterArgs& a, hipStream_t s) {
-  if (int rc = flush_fused_check(ctx, s)) return rc;
-  const magnus_hamiltonian* h = op.h;
-  const int dim = (int)h->H1.dim;
-  const double* c = op.m6c;
-  const CsrDev H1{h->H1.row_ptr, h->H1.col_idx, reinterpret_cast<const double2*>(h->H1.val)};
-  const CsrDev H2{h->H2.row_ptr, h->H2.col_idx, reinterpret_cast<const double2*>(h->H2.val)};
-  const CsrDev K{ctx->kc_rp, ctx->kc_ci, ctx->kc_val};
-  const CsrDev P1{ctx->pm_rp[0], ctx->pm_ci[0], ctx->pm_val[0]};
-  const CsrDev P2{ctx->pm_rp[1], ctx->pm_ci[1], ctx->pm_val[1]};
-  magnus::M6Terms T{{H1, H2, K, P1, P2}};
-  magnus::M6Coef C{};
-  for (int k = 0; k < 10; ++k) C.c[k] = c[k];
-  magnus::M6Vecs V{};
-  for (int k = 0; k < magnus::kM6Terms; ++k) V.u[k] = ctx->pm_ws + (size_t)k * (size_t)ctx->pm_ws_dim;
-  V.y0 = ctx->pm_ws + (size_t)magnus::kM6Terms * (size_t)ctx->pm_ws_dim;
-  HIP_TRY(magnus::launch_m6_stage_a(T, a.wcur, C, V, dim, a.slot, a.check_stop, s));
-  HIP_TRY(timed(ctx, MAGNUS_KERNEL_CSR_LEJA, s, [&] { return magnus::launch_m6_stage_b(T, V, scale, dim, a, s); }));
-  HIP_TRY(magnus::launch_leja_decide(a, magnus::m6_grid(dim), s));
-  return MAGNUS_OK;
-}
-
 // Stop test of iteration i: fused into the iteration kernel on grids of at
 // most kFuseMaxGrid workgroups (every workgroup reduces iteration i-1's
 // partials, which alternate between two halves of the partials buffer),
@@ -562,6 +527,32 @@ int setup_stop_test(magnus_ctx* ctx, const ExpPlan& P, int i, int grid, IterArgs
   ctx->fz_last.iter = i + 1;
   ctx->fz_last.prev_partials = a->partials;
   ctx->fz_pending = true;
+  return MAGNUS_OK;
+}
+
+// One Leja iteration of Method M6 on CSR terms, the exponent's nested
+// commutators applied to vectors by products with H1, H2 and K alone.
+int m6_csr_iteration(magnus_ctx* ctx, const ExpOp& op, const ExpPlan& P, int i, IterArgs& a, hipStream_t s) {
+  const magnus_hamiltonian* h = op.h;
+  const int dim = (int)h->H1.dim;
+  const bool coded = ctx->coded_h == h && ctx->coded_terms.n == 3;
+  const magnus::CodeTerms T =
+      coded ? ctx->coded_terms
+            : magnus::CodeTerms{3, {csr_dev(h->H1), csr_dev(h->H2), CsrDev{ctx->kc_rp, ctx->kc_ci, ctx->kc_val}}};
+  magnus::M6Args M{};
+  for (int k = 0; k < 10; ++k) M.c[k] = op.m6c[k];
+  for (int k = 0; k < 4; ++k) M.a[k] = ctx->pm_ws + (size_t)k * (size_t)ctx->pm_ws_dim;
+  for (int k = 0; k < 3; ++k) M.v[k] = ctx->pm_ws + (size_t)(4 + k) * (size_t)ctx->pm_ws_dim;
+  M.scale = P.scale;
+  const int grid = coded ? magnus::code_grid(dim, ctx->coded.rows) : magnus::m6_grid(dim);
+  if (int rc = setup_stop_test(ctx, P, i, grid, &a, s)) return rc;
+  auto pass = [&](int stage) {
+    return coded ? magnus::launch_coded_m6(stage, T, dim, ctx->coded, M, a, s) : magnus::launch_m6(stage, T, dim, M, a, s);
+  };
+  HIP_TRY(pass(0));
+  HIP_TRY(pass(1));
+  HIP_TRY(timed(ctx, MAGNUS_KERNEL_CSR_LEJA, s, [&] { return pass(2); }));
+  if (!a.fused) HIP_TRY(magnus::launch_leja_decide(a, grid, s));
   return MAGNUS_OK;
 }
 
@@ -638,7 +629,7 @@ int launch_iteration(magnus_ctx* ctx, const ExpOp& op, const ExpPlan& P, int i, 
   a.wcur = win;
   a.wout = wout;
   a.pacc = pacc;
-  if (op.m6c) return m6_csr_iteration(ctx, op, P.scale, a, s);
+  if (op.m6c) return m6_csr_iteration(ctx, op, P, i, a, s);
   if (h->H1.format == MAGNUS_DENSE) {
     if (op.kappa != 0.0) return fail(MAGNUS_EINVAL, "dense commutator exponents run assembled");
     a.x1 = win;
@@ -2177,7 +2168,7 @@ int magnus_csr_m6_prepare(magnus_ctx* ctx, magnus_hamiltonian* h, magnus_stream 
     if (ctx->pm_ws) HIP_TRY(hipFree(ctx->pm_ws));
     ctx->pm_ws = nullptr;
     ctx->pm_ws_dim = 0;
-    HIP_TRY(hipMalloc(&ctx->pm_ws, (magnus::kM6Terms + 1) * sizeof(double2) * (size_t)dim));
+    HIP_TRY(hipMalloc(&ctx->pm_ws, magnus::kM6Vecs * sizeof(double2) * (size_t)dim));
     ctx->pm_ws_dim = dim;
   }
   ctx->pm_key = ctx->kc_key;
@@ -2799,8 +2790,9 @@ int propagate(magnus_ctx* ctx, const magnus_hamiltonian* h, int32_t method, doub
     const int64_t k = ((n / every_k) + 1) * every_k;
     return std::min(k, nsteps);
   };
-  if (!small && !S.sixth && tau != 0.0)
-    if ((rc = begin_coded(ctx, h, S.commutator && csr_comm_ready(ctx, h), exps * (S.commutator ? batch : 1),
+  if (!small && tau != 0.0)  // (M6: three passes per iteration)
+    if ((rc = begin_coded(ctx, h, S.commutator && csr_comm_ready(ctx, h),
+                          exps * (S.commutator ? batch : 1) * (S.sixth ? 3 : 1),
                           grouped ? std::min(batch / 2, 16) : 0, s)))
       return rc;
   // one state on the grid path with every stop test fused: one step captured,

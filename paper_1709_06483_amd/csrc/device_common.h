@@ -199,5 +199,45 @@ __device__ __forceinline__ bool iteration_stopped(const IterArgs& a, double* lds
   return stop_verdict(a, s, lds);
 }
 
+// Leja update for one row; y = (scale-folded) H_hat w at that row.
+__device__ __forceinline__ void leja_row(const IterArgs& a, int r, d2 y, double& pw, double& pv) {
+  const d2 w_old = tod2(a.wcur[r]);
+  const d2 wn = y - rmul(a.sigma, w_old);
+  d2 p;
+  if (a.first) {
+    p = cmul(tod2(a.d0), w_old) + cmul(tod2(a.d), wn);
+    pv += nrm2(w_old);
+  } else {
+    p = tod2(a.pacc[r]) + cmul(tod2(a.d), wn);
+  }
+  a.wout[r] = fromd2(wn);
+  a.pacc[r] = fromd2(p);
+  pw += nrm2(wn);
+}
+
+// |w_i|^2 of the workgroup at partials[blockIdx.x]; on a substep's first
+// iteration also |v|^2 at partials[gridDim.x + blockIdx.x].
+__device__ __forceinline__ void store_partials(const IterArgs& a, double bw, double bv) {
+  a.partials[blockIdx.x] = bw;
+  if (a.first) a.partials[gridDim.x + blockIdx.x] = bv;
+}
+
+// Block sums of the norm partials, one pair per workgroup (plain stores: the
+// reduction across workgroups happens in leja_decide_kernel, after this
+// kernel has finished, so no device-scope atomics or fences are needed).
+__device__ __forceinline__ void block_partials(const IterArgs& a, double pw, double pv) {
+  __shared__ double red[2][kThreads / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  pw = wave_sum(pw);
+  pv = wave_sum(pv);
+  if (lane == 0) { red[0][wv] = pw; red[1][wv] = pv; }
+  __syncthreads();
+  if (tid == 0) {
+    double bw = 0.0, bv = 0.0;
+    for (int w = 0; w < kThreads / 64; ++w) { bw += red[0][w]; bv += red[1][w]; }
+    store_partials(a, bw, bv);
+  }
+}
+
 }  // namespace dev
 }  // namespace magnus

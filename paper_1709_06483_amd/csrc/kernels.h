@@ -115,31 +115,6 @@ int csr2_grid(int dim, int rows_per_block);
 // one pass over the matrix to the next; the rest are read non-temporally.
 int csr_keep_entries(int dim);
 
-// Method M6 on CSR terms, one Leja iteration in two passes over the five
-// matrices (H1, H2, K, P1, P2).  Stage A: with s_k = M_k w,
-//   y0 = sum_k c_k s_k, u1 = i(c5 s3 + c6 s4), u2 = i c7 s4,
-//   u3 = -i(c8 s3 + c9 s4), u4 = i(c8 s2 - c5 s0), u5 = i(c9 s2 - c6 s0 - c7 s1);
-// stage B: y = y0 + sum_k M_k u_{k+1}, then the Leja update from y (the
-// Hermitian exponent times w_{i-1}) with its norm partials (grid m6_grid for
-// the decide kernel).  Both return at once when check_stop and the slot's
-// substep has stopped.
-constexpr int kM6Terms = 5;
-struct M6Terms {
-  CsrDev m[kM6Terms];
-};
-struct M6Coef {
-  double c[10];
-};
-struct M6Vecs {
-  double2* u[kM6Terms];  // stage B's input vectors, in the order of M6Terms
-  double2* y0;
-};
-hipError_t launch_m6_stage_a(const M6Terms& T, const double2* w, const M6Coef& C, const M6Vecs& V, int dim,
-                             const Slot* slot, int check_stop, hipStream_t s);
-hipError_t launch_m6_stage_b(const M6Terms& T, const M6Vecs& V, double scale, int dim, const IterArgs& a,
-                             hipStream_t s);
-int m6_grid(int dim);
-
 // ---- coded CSR terms (kernels_coded.hip) ----
 constexpr int kCodeMax = 255;     // (column - row, value) pairs per block of rows
 constexpr int kCodeRounds = 32;   // rounds of four entries per row, over all terms
@@ -182,6 +157,23 @@ hipError_t launch_code_build(const CodeTerms& T, int dim, const CodedDev& C, int
 // One Leja iteration on a1 T0 x1 + a2 T1 x2 (+ a3 T2 x1), or mode kSplitComm, on code_grid(dim, C.rows) workgroups.
 hipError_t launch_coded_iter(int mode, const CodeTerms& T, int dim, const CodedDev& C, const IterArgs& a, double a3,
                              hipStream_t s);
+
+// ---- Method M6 on CSR terms (kernels_m6.hip) ----
+// One Leja iteration in three passes over H1, H2 and K, coded (launch_coded_m6)
+// or from the CSR arrays (launch_m6); `stage` 0, 1, 2.  Pass 0 makes the stop
+// test of iteration i - 1 where the test is fused, pass 2 the Leja update with
+// its norm partials (grid m6_grid, or code_grid).
+struct M6Args {
+  double c[10];     // coefficients of H1, H2, K, P1, P2, U11, U12, U22, R1, R2
+  double2* a[4];    // pass 0: H1 w, H2 w, K w and c6 H1 w + c7 H2 w
+  double2* v[3];    // pass 1: what pass 2 multiplies by H1, H2 and K
+  double scale;
+};
+constexpr int kM6Vecs = 7;
+hipError_t launch_m6(int stage, const CodeTerms& T, int dim, const M6Args& M, const IterArgs& a, hipStream_t s);
+hipError_t launch_coded_m6(int stage, const CodeTerms& T, int dim, const CodedDev& C, const M6Args& M,
+                           const IterArgs& a, hipStream_t s);
+int m6_grid(int dim);
 
 // The streaming kernel (kernels_stream.hip).
 hipError_t launch_csr2_stream(int mode, const CsrDev& t1, const CsrDev& t2, int dim, const IterArgs& a,

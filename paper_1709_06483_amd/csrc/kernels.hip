@@ -19,46 +19,6 @@ namespace {
 
 using namespace dev;
 
-// Leja update for one row; y = (scale-folded) H_hat w at that row.
-__device__ __forceinline__ void leja_row(const IterArgs& a, int r, d2 y, double& pw, double& pv) {
-  const d2 w_old = tod2(a.wcur[r]);
-  const d2 wn = y - rmul(a.sigma, w_old);
-  d2 p;
-  if (a.first) {
-    p = cmul(tod2(a.d0), w_old) + cmul(tod2(a.d), wn);
-    pv += nrm2(w_old);
-  } else {
-    p = tod2(a.pacc[r]) + cmul(tod2(a.d), wn);
-  }
-  a.wout[r] = fromd2(wn);
-  a.pacc[r] = fromd2(p);
-  pw += nrm2(wn);
-}
-
-// |w_i|^2 of the workgroup at partials[blockIdx.x]; on a substep's first
-// iteration also |v|^2 at partials[gridDim.x + blockIdx.x].
-__device__ __forceinline__ void store_partials(const IterArgs& a, double bw, double bv) {
-  a.partials[blockIdx.x] = bw;
-  if (a.first) a.partials[gridDim.x + blockIdx.x] = bv;
-}
-
-// Block sums of the norm partials, one pair per workgroup (plain stores: the
-// reduction across workgroups happens in leja_decide_kernel, after this
-// kernel has finished, so no device-scope atomics or fences are needed).
-__device__ void block_partials(const IterArgs& a, double pw, double pv) {
-  __shared__ double red[2][kThreads / 64];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  pw = wave_sum(pw);
-  pv = wave_sum(pv);
-  if (lane == 0) { red[0][wv] = pw; red[1][wv] = pv; }
-  __syncthreads();
-  if (tid == 0) {
-    double bw = 0.0, bv = 0.0;
-    for (int w = 0; w < kThreads / 64; ++w) { bw += red[0][w]; bv += red[1][w]; }
-    store_partials(a, bw, bv);
-  }
-}
-
 // One workgroup: reduce the partials of the iteration just finished in a
 // fixed order, then the early-termination test of Section 3 (our reading:
 // stop once |d_i w_i| + |d_{i-1} w_{i-1}| <= tol |v|).  Every thread issues
@@ -804,100 +764,6 @@ __global__ __launch_bounds__(kThreads) void dense_assemble_iter_kernel(DenseAsse
 }
 
 // ---------------------------------------------------------------------------
-// The Method M6 iteration on CSR terms (the exponent's nested commutators
-// applied to vectors as commutators of assembled CSR matrices), in two
-// passes over the five matrices M = (H1, H2, K, P1, P2), 8 lanes per row,
-// each term's products summed in a fixed order:
-//   stage A: s_k = (M_k w)[r] for the row, then on the row itself y0 and the
-//            five vectors u_k that stage B multiplies (see M6Vecs);
-//   stage B: y = y0 + sum_k M_k u_k, then the Leja update and norm partials.
-// Grouping the products by matrix reads P1 and P2 twice per iteration where
-// applying each commutator product separately reads them three and four times.
-// A lane loads its row's bounds in all five matrices before the first product,
-// so those loads are in flight together (n = 16: 2,263 against 2,197 steps/s).
-// ---------------------------------------------------------------------------
-constexpr int kM6Lanes = 8;  // lanes per row
-
-__device__ __forceinline__ d2 times_i(d2 v) { return d2{-v.y, v.x}; }
-
-__global__ __launch_bounds__(kThreads) void m6_stage_a_kernel(M6Terms T, const double2* __restrict__ w, M6Coef C,
-                                                             M6Vecs V, int dim, const Slot* slot, int check_stop) {
-  if (check_stop && load_stopped(slot)) return;
-  const long long t = (long long)blockIdx.x * kThreads + threadIdx.x;
-  const int r = (int)(t / kM6Lanes), q = (int)(t % kM6Lanes);
-  const d2* wv = reinterpret_cast<const d2*>(w);
-  d2 sk[kM6Terms];
-  int rs[kM6Terms], re[kM6Terms];
-#pragma unroll
-  for (int k = 0; k < kM6Terms; ++k) {
-    rs[k] = r < dim ? T.m[k].rp[r] : 0;
-    re[k] = r < dim ? T.m[k].rp[r + 1] : 0;
-  }
-#pragma unroll
-  for (int k = 0; k < kM6Terms; ++k) {
-    d2 acc = {0.0, 0.0};
-    {
-      const d2* av = reinterpret_cast<const d2*>(T.m[k].val);
-      for (int e = rs[k] + q; e < re[k]; e += kM6Lanes) acc += cmul(av[e], wv[T.m[k].ci[e]]);
-    }
-#pragma unroll
-    for (int off = kM6Lanes / 2; off > 0; off >>= 1) {
-      acc.x += __shfl_xor(acc.x, off, 64);
-      acc.y += __shfl_xor(acc.y, off, 64);
-    }
-    sk[k] = acc;
-  }
-  if (r >= dim) return;
-  const double* c = C.c;
-  // lane q of the row writes output q (all lanes hold the five sums)
-  d2 out;
-  switch (q) {
-    case 0: out = rmul(c[0], sk[0]) + rmul(c[1], sk[1]) + rmul(c[2], sk[2]) + rmul(c[3], sk[3]) + rmul(c[4], sk[4]); break;
-    case 1: out = times_i(rmul(c[5], sk[3]) + rmul(c[6], sk[4])); break;
-    case 2: out = times_i(rmul(c[7], sk[4])); break;
-    case 3: out = times_i(rmul(-c[8], sk[3]) - rmul(c[9], sk[4])); break;
-    case 4: out = times_i(rmul(c[8], sk[2]) - rmul(c[5], sk[0])); break;
-    case 5: out = times_i(rmul(c[9], sk[2]) - rmul(c[6], sk[0]) - rmul(c[7], sk[1])); break;
-    default: return;
-  }
-  double2* dst = q == 0 ? V.y0 : V.u[q - 1];
-  dst[r] = fromd2(out);
-}
-
-__global__ __launch_bounds__(kThreads) void m6_stage_b_kernel(M6Terms T, M6Vecs V, double scale, int dim, IterArgs a) {
-  if (a.check_stop && load_stopped(a.slot)) return;
-  const long long t = (long long)blockIdx.x * kThreads + threadIdx.x;
-  // rows in reverse order: stage A ends on the last rows, whose matrix entries
-  // are still in the MALL when stage B starts on them (and stage B ends on the
-  // first rows, where the next iteration's stage A starts)
-  const int r0 = (int)(t / kM6Lanes), q = (int)(t % kM6Lanes);
-  const int r = r0 < dim ? dim - 1 - r0 : r0;
-  d2 acc = {0.0, 0.0};
-  if (r < dim) {
-    int rs[kM6Terms], re[kM6Terms];
-#pragma unroll
-    for (int k = 0; k < kM6Terms; ++k) {
-      rs[k] = T.m[k].rp[r];
-      re[k] = T.m[k].rp[r + 1];
-    }
-#pragma unroll
-    for (int k = 0; k < kM6Terms; ++k) {
-      const d2* av = reinterpret_cast<const d2*>(T.m[k].val);
-      const d2* uv = reinterpret_cast<const d2*>(V.u[k]);
-      for (int e = rs[k] + q; e < re[k]; e += kM6Lanes) acc += cmul(av[e], uv[T.m[k].ci[e]]);
-    }
-  }
-#pragma unroll
-  for (int off = kM6Lanes / 2; off > 0; off >>= 1) {
-    acc.x += __shfl_xor(acc.x, off, 64);
-    acc.y += __shfl_xor(acc.y, off, 64);
-  }
-  double pw = 0.0, pv = 0.0;
-  if (r < dim && q == 0) leja_row(a, r, rmul(scale, tod2(V.y0[r]) + acc), pw, pv);
-  block_partials(a, pw, pv);
-}
-
-// ---------------------------------------------------------------------------
 // Gershgorin discs + structure check (CSR), one thread per row.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kThreads) void csr_gershgorin_kernel(CsrDev t, int dim, long long nnz,
@@ -1122,22 +988,6 @@ hipError_t launch_dense2_iter(const double2* H1, const double2* H2, int dim, lon
     default: return hipErrorInvalidValue;
   }
 #undef MAGNUS_DENSE_CASE
-  return hipGetLastError();
-}
-
-int m6_grid(int dim) { return (int)(((long long)dim * kM6Lanes + kThreads - 1) / kThreads); }
-
-hipError_t launch_m6_stage_a(const M6Terms& T, const double2* w, const M6Coef& C, const M6Vecs& V, int dim,
-                             const Slot* slot, int check_stop, hipStream_t s) {
-  if (dim <= 0) return hipSuccess;
-  m6_stage_a_kernel<<<m6_grid(dim), kThreads, 0, s>>>(T, w, C, V, dim, slot, check_stop);
-  return hipGetLastError();
-}
-
-hipError_t launch_m6_stage_b(const M6Terms& T, const M6Vecs& V, double scale, int dim, const IterArgs& a,
-                             hipStream_t s) {
-  if (dim <= 0) return hipSuccess;
-  m6_stage_b_kernel<<<m6_grid(dim), kThreads, 0, s>>>(T, V, scale, dim, a);
   return hipGetLastError();
 }
 
