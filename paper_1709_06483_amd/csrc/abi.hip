@@ -1545,6 +1545,42 @@ bool small_ok(magnus_ctx* ctx, const magnus_hamiltonian* h, int64_t nstates) {
   return small_candidate(h) && h->H1.dim <= small_cap(ctx, nstates);
 }
 
+// exp(-i tau (a H1 + b H2)) for the one-workgroup kernels: its header, and its iterations appended to the table.
+int persist_exponential(const magnus_hamiltonian* h, double ca, double cb, double tau, double tol_e,
+                        const magnus_leja_opts* o, PersistExp* E, std::vector<ColParam>* table, Acc* acc) {
+  const auto& xi = magnus::leja_points();
+  double lo, hi;
+  magnus::weyl_interval(ca, h->H1.lam_min, h->H1.lam_max, cb, h->H2.lam_min, h->H2.lam_max, 0.0, 0.0, 0.0, &lo, &hi);
+  ExpPlan P;
+  if (!magnus::plan_exponential(tau, lo, hi, tol_e, o->max_degree, o->max_substeps, &P))
+    return fail(MAGNUS_ENOCONV, "no degree <= %d with <= %d substeps reaches tol %g", o->max_degree, o->max_substeps,
+                tol_e);
+  E->m = P.lp.m;
+  E->s = P.lp.s;
+  E->table_off = (long long)table->size();
+  E->tol_sub = tol_e / (2.0 * P.lp.s);
+  for (int i = 1; i <= P.lp.m; ++i) {
+    ColParam c{};
+    c.a1 = P.scale * ca;
+    c.a2 = P.scale * cb;
+    c.sigma = P.scale * P.c + xi[i - 1];
+    c.dre = P.d[i].real();
+    c.dim = P.d[i].imag();
+    c.dabs = std::abs(P.d[i]);
+    c.d0re = P.d[0].real();
+    c.d0im = P.d[0].imag();
+    c.d0abs = std::abs(P.d[0]);
+    table->push_back(c);
+  }
+  acc->exponentials += 1;
+  acc->substeps += P.lp.s;
+  acc->planned += (int64_t)P.lp.m * P.lp.s;
+  acc->max_m = std::max(acc->max_m, P.lp.m);
+  acc->max_s = std::max(acc->max_s, P.lp.s);
+  acc->max_bound = std::max(acc->max_bound, P.lp.bound);
+  return MAGNUS_OK;
+}
+
 // Steps n0..n1-1 of every state in one launch.
 int persist_segment(magnus_ctx* ctx, const std::vector<const magnus_hamiltonian*>& hs,
                     const std::vector<SmallState>& st, const magnus::Scheme& S, double tau, int64_t n0, int64_t n1,
@@ -1558,44 +1594,14 @@ int persist_segment(magnus_ctx* ctx, const std::vector<const magnus_hamiltonian*
   if (maxdim > magnus::kPersistMaxDim) return fail(MAGNUS_EINVAL, "dimension %lld too large for the small-state kernel", (long long)maxdim);
   std::vector<ColParam> table;
   std::vector<PersistExp> exps((size_t)nst * nexp);
-  const auto& xi = magnus::leja_points();
   for (int b = 0; b < nst; ++b) {
     const magnus_hamiltonian* h = hs[st[b].prob];
     for (int64_t n = n0; n < n1; ++n) {
       const double* f = st[b].fn + S.q * n;
       for (int half = 0; half < S.nexp; ++half) {
-        const double rho = S.rho[half], coef = scheme_b(S, half, f);
-        double lo, hi;
-        magnus::weyl_interval(rho, h->H1.lam_min, h->H1.lam_max, coef, h->H2.lam_min, h->H2.lam_max, 0.0, 0.0, 0.0,
-                              &lo, &hi);
-        ExpPlan P;
-        if (!magnus::plan_exponential(tau, lo, hi, tol_e, o->max_degree, o->max_substeps, &P))
-          return fail(MAGNUS_ENOCONV, "no degree <= %d with <= %d substeps reaches tol %g", o->max_degree,
-                      o->max_substeps, tol_e);
-        PersistExp& E = exps[(size_t)b * nexp + S.nexp * (n - n0) + half];
-        E.m = P.lp.m;
-        E.s = P.lp.s;
-        E.table_off = (long long)table.size();
-        E.tol_sub = tol_e / (2.0 * P.lp.s);
-        for (int i = 1; i <= P.lp.m; ++i) {
-          ColParam c{};
-          c.a1 = P.scale * rho;
-          c.a2 = P.scale * coef;
-          c.sigma = P.scale * P.c + xi[i - 1];
-          c.dre = P.d[i].real();
-          c.dim = P.d[i].imag();
-          c.dabs = std::abs(P.d[i]);
-          c.d0re = P.d[0].real();
-          c.d0im = P.d[0].imag();
-          c.d0abs = std::abs(P.d[0]);
-          table.push_back(c);
-        }
-        acc->exponentials += 1;
-        acc->substeps += P.lp.s;
-        acc->planned += (int64_t)P.lp.m * P.lp.s;
-        acc->max_m = std::max(acc->max_m, P.lp.m);
-        acc->max_s = std::max(acc->max_s, P.lp.s);
-        acc->max_bound = std::max(acc->max_bound, P.lp.bound);
+        if (int rc = persist_exponential(h, S.rho[half], scheme_b(S, half, f), tau, tol_e, o,
+                                         &exps[(size_t)b * nexp + S.nexp * (n - n0) + half], &table, acc))
+          return rc;
       }
     }
   }
@@ -2675,6 +2681,49 @@ int expmv_leja(magnus_ctx* ctx, const magnus_hamiltonian* h, double a, double b,
   return end_call(ctx, acc, tol_e, stats, s);
 }
 
+// One step of small states in one launch, when that is faster than a launch
+// per iteration: rows that the kernel holds in registers, which terms that fit
+// the coded form with 20 entries a row between them do (chains, us per
+// iteration, a launch each / in one launch: n = 6 4.4 / 0.9, n = 10 4.6 / 2.4;
+// rows that do not fit 5.2 and more), and iterations that fit the launch's
+// arguments.  *done: whether it was launched.
+static int small_step(magnus_ctx* ctx, const magnus_hamiltonian* h, const magnus::Scheme& S, double tau,
+                      const double* f, const double2* in, double2* out, int batch, double tol_e,
+                      const magnus_leja_opts* o, Acc* acc, bool* done, hipStream_t s) {
+  *done = false;
+  const int64_t dim = h->H1.dim;
+  if (dim > magnus::kPersistStepDim || batch > ctx->nslots || !small_ok(ctx, h, batch) || ctx->csr_variant ||
+      S.nexp > magnus::kPersistStepExps || h->H1.nnz + h->H2.nnz > 20 * dim || !ctx->codable.count(pair_key(h)))
+    return MAGNUS_OK;
+  magnus::PersistStep a{};
+  std::vector<ColParam> table;
+  Acc one;
+  for (int k = 0; k < S.nexp; ++k) {
+    if (int rc = persist_exponential(h, S.rho[k], scheme_b(S, k, f), tau, tol_e, o, &a.plan.exps[k], &table, &one))
+      return rc;
+    if (table.size() > (size_t)magnus::kPersistStepRecords) return MAGNUS_OK;
+  }
+  std::copy(table.begin(), table.end(), a.plan.table);
+  a.problem.t1 = csr_dev(h->H1);
+  a.problem.t2 = csr_dev(h->H2);
+  a.problem.dim = (int)dim;
+  a.in = in;
+  a.out = out;
+  a.slots = ctx->slots;
+  a.nexp = S.nexp;
+  a.early = o->early_termination;
+  if (int rc = flush_fused_check(ctx, s)) return rc;
+  HIP_TRY(timed(ctx, MAGNUS_KERNEL_PERSIST, s, [&] { return magnus::launch_persist_step(a, batch, s); }));
+  acc->exponentials += one.exponentials * batch;
+  acc->substeps += one.substeps * batch;
+  acc->planned += one.planned * batch;
+  acc->max_m = std::max(acc->max_m, one.max_m);
+  acc->max_s = std::max(acc->max_s, one.max_s);
+  acc->max_bound = std::max(acc->max_bound, one.max_bound);
+  *done = true;
+  return MAGNUS_OK;
+}
+
 static int step_common(int method, magnus_ctx* ctx, const magnus_hamiltonian* h, double tau, double f1,
                        double f2, const void* psi_in, void* psi_out, int32_t batch,
                        const magnus_leja_opts* opts, magnus_stats* stats, magnus_stream stream) {
@@ -2693,14 +2742,19 @@ static int step_common(int method, magnus_ctx* ctx, const magnus_hamiltonian* h,
   magnus::method_scheme(method, &S);
   const double fv[2] = {f1, f2};
   const double tol_e = per_exp_tol(opts, S.nexp);
-  if (tau != 0.0)
-    if ((rc = begin_coded(ctx, h, S.commutator && csr_comm_ready(ctx, h), S.commutator ? batch : S.nexp,
-                          S.commutator ? 0 : std::min(batch / 2, 16), s)))
-      return rc;
   Acc acc;
   acc.products_per_iter = method == MAGNUS_M4 ? 4 : 2;
   const double2* in = reinterpret_cast<const double2*>(psi_in);
   double2* out = reinterpret_cast<double2*>(psi_out);
+  if (tau != 0.0 && !S.commutator) {
+    bool done = false;
+    if ((rc = small_step(ctx, h, S, tau, fv, in, out, batch, tol_e, opts, &acc, &done, s))) return rc;
+    if (done) return end_call(ctx, acc, tol_e, stats, s);
+  }
+  if (tau != 0.0)
+    if ((rc = begin_coded(ctx, h, S.commutator && csr_comm_ready(ctx, h), S.commutator ? batch : S.nexp,
+                          S.commutator ? 0 : std::min(batch / 2, 16), s)))
+      return rc;
   for (int32_t c = 0; c < batch;) {
     const int g = (!S.commutator && multi_ok(h, 0.0)) ? group_for(ctx, h, batch - c) : 1;
     if (g > 1) {

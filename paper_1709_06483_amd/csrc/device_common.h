@@ -43,6 +43,46 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
+// Rotations of a value by N lanes within each row of 16 lanes.
+template <int N>
+__device__ __forceinline__ double row_rotated(double v) {
+  union U {
+    double d;
+    unsigned u[2];
+  } a{v}, b;
+  for (int k = 0; k < 2; ++k) b.u[k] = __builtin_amdgcn_mov_dpp(a.u[k], 0x120 + N, 0xf, 0xf, true);
+  return b.d;
+}
+
+// Sum over each row of 16 lanes, in all of them, without LDS traffic.
+__device__ __forceinline__ double row16_sum(double v) {
+  v += row_rotated<8>(v);
+  v += row_rotated<4>(v);
+  v += row_rotated<2>(v);
+  return v + row_rotated<1>(v);
+}
+
+// Sum over the wave's 64 lanes, in every lane: rows of 16, then swaps of rows
+// and of halves.
+__device__ __forceinline__ double lanes_sum(double v) {
+  union U {
+    double d;
+    unsigned u[2];
+  } a{row16_sum(v)}, x, y;
+  for (int k = 0; k < 2; ++k) {
+    const auto r = __builtin_amdgcn_permlane16_swap(a.u[k], a.u[k], false, false);
+    x.u[k] = r[0];
+    y.u[k] = r[1];
+  }
+  a.d = x.d + y.d;
+  for (int k = 0; k < 2; ++k) {
+    const auto r = __builtin_amdgcn_permlane32_swap(a.u[k], a.u[k], false, false);
+    x.u[k] = r[0];
+    y.u[k] = r[1];
+  }
+  return x.d + y.d;
+}
+
 // Cross-lane exchange through a wave-private LDS slice: wait for this wave's
 // LDS traffic and keep the compiler from moving memory operations across.
 __device__ __forceinline__ void wave_lds_sync() {

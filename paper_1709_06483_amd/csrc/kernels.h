@@ -427,6 +427,26 @@ constexpr int kPersistMaxDim = 4096;
 constexpr int kPersistCache = 6400;
 hipError_t launch_persist_propagate(const PersistArgs& a, int nstates, int max_dim, hipStream_t s);
 
+// One step of every state with the same parameters, which travel in the
+// launch's arguments.
+constexpr int kPersistStepDim = 1024;   // largest dimension
+constexpr int kPersistStepExps = 3;     // exponentials of a step
+constexpr int kPersistStepRecords = 40; // iterations of all of them
+struct PersistInline {
+  PersistExp exps[kPersistStepExps];
+  ColParam table[kPersistStepRecords];
+};
+struct PersistStep {
+  PersistInline plan;
+  PersistProblem problem;
+  const double2* in;  // nstates vectors of dim entries
+  double2* out;
+  Slot* slots;        // one per state
+  int nexp, early;
+};
+static_assert(sizeof(PersistStep) <= 4096, "kernel arguments");
+hipError_t launch_persist_step(const PersistStep& a, int nstates, hipStream_t s);
+
 // Small helpers.
 hipError_t launch_copy(const double2* src, double2* dst, long long n, hipStream_t s);
 hipError_t launch_slot_reset(Slot* slot, int n, hipStream_t s);

@@ -541,39 +541,6 @@ __global__ __launch_bounds__(kThreads, MODE == kLejaComm ? 6 : 7) void csr2_wave
 // ---------------------------------------------------------------------------
 constexpr int kDenseMaxRows = 256;  // rows of a workgroup: one thread each for the update
 
-// Sum over the wave's 64 lanes, in every lane, without LDS traffic: rotations
-// within rows of 16 lanes, then swaps of rows and of halves.
-__device__ __forceinline__ double lanes_sum(double v) {
-  union U {
-    double d;
-    unsigned u[2];
-  };
-  auto rotated = [](double x, auto ctrl) {
-    U a, b;
-    a.d = x;
-    for (int k = 0; k < 2; ++k) b.u[k] = __builtin_amdgcn_mov_dpp(a.u[k], decltype(ctrl)::value, 0xf, 0xf, true);
-    return b.d;
-  };
-  v += rotated(v, std::integral_constant<int, 0x128>{});  // row_ror:8
-  v += rotated(v, std::integral_constant<int, 0x124>{});
-  v += rotated(v, std::integral_constant<int, 0x122>{});
-  v += rotated(v, std::integral_constant<int, 0x121>{});
-  U a, x, y;
-  a.d = v;
-  for (int k = 0; k < 2; ++k) {
-    const auto r = __builtin_amdgcn_permlane16_swap(a.u[k], a.u[k], false, false);
-    x.u[k] = r[0];
-    y.u[k] = r[1];
-  }
-  a.d = x.d + y.d;
-  for (int k = 0; k < 2; ++k) {
-    const auto r = __builtin_amdgcn_permlane32_swap(a.u[k], a.u[k], false, false);
-    x.u[k] = r[0];
-    y.u[k] = r[1];
-  }
-  return x.d + y.d;
-}
-
 // The rows of a workgroup's products: row by row group the loads of F::load
 // and products of F::use over this wave's columns, the lanes' sums to
 // part[row][wave].  The first group's loads are issued before the stop test,
