@@ -424,8 +424,8 @@ int magnus_propagate_adjoint(magnus_ctx* ctx, const magnus_hamiltonian* h, doubl
 
 /* Autotuner for the H·v stream that Section 3 reduces the method's cost to:
  * times, on the device, each row mapping of the single-state CSR Leja
- * iteration on these terms (variant codes 1 nonzero streaming, 2-4 a row per
- * lane in blocks of 64/32/128 rows, 5-6 wave tiles of 8/16 rows, 7 runs of 8
+ * iteration on these terms (variant codes 1 eight lanes per row, past 2^17
+ * rows nonzero streaming, 2-4 a row per lane in blocks of 64/32/128 rows, 5-6 wave tiles of 8/16 rows, 7 runs of 8
  * wave tiles of 8 rows streamed through LDS one tile ahead;
  * 5 timed launches each) and, when batch > 1, the multi-state iteration with 2, 4, 8,
  * 16 and 32 states per pass (up to batch; cost per state), and keeps the

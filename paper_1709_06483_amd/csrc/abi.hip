@@ -381,12 +381,32 @@ bool pair_partials_fit(const magnus_ctx* ctx, int64_t pair_blocks) {
   return pair_partials_at(ctx) + 8 * (size_t)pair_blocks <= ctx->npartials;
 }
 
+// Exponentials from which coding pays.  It costs what about three iterations
+// gain from 2^16 rows on (chains, us: coding, and an iteration on the CSR
+// arrays / on the coded terms: n = 16 21, 15.1 / 8.6; n = 18 53, 37 / 15; n = 20
+// 200, 151 / 47), 16 at n = 15 (18, 7.6 / 6.5; an exponential takes four
+// iterations or more).  At n = 14 it is 15 against 6.0 / 5.6 with the chain's
+// 21 entries a row, and the ring's 16 gain nothing (5.5 / 5.7); nor do smaller
+// sizes (n = 12 5.1 / 5.8).  Pairs gain a decide kernel in every iteration too.
+// M6's three passes: n = 12 22 / 20, n = 16 60 / 31.  A gradient takes six
+// exponentials a step, two of them pairs.
+enum class CodeUse { kSingle, kM6, kGradient };
+int64_t coding_pays(const magnus_hamiltonian* h, int npairs, CodeUse use) {
+  const int64_t dim = h->H1.dim;
+  if (dim >= 65536) return 1;
+  if (npairs > 0) return 2;
+  if (use == CodeUse::kM6) return dim >= 16384 ? 2 : 6;
+  if (use == CodeUse::kGradient) return dim >= 16384 ? 6 : 16;
+  if (dim >= 28672) return 3;
+  return dim >= 16384 && h->H1.nnz + h->H2.nnz >= 20 * dim ? 8 : INT64_MAX;
+}
+
 // At the start of a call on CSR terms: rewrite the terms in coded form
 // when the call's iterations pay for that.  `with_k`: its iterations apply the
 // assembled commutator too.
 // npairs > 0: the call's states run as that many pairs (and perhaps one more).
 int begin_coded(magnus_ctx* ctx, const magnus_hamiltonian* h, bool with_k, int64_t exponentials, int npairs,
-                hipStream_t s) {
+                hipStream_t s, CodeUse use = CodeUse::kSingle) {
   ctx->coded_h = nullptr;
   ctx->coded_pairs = false;
   if (!coding_possible(ctx, h) || ctx->csr_variant) return MAGNUS_OK;
@@ -396,12 +416,7 @@ int begin_coded(magnus_ctx* ctx, const magnus_hamiltonian* h, bool with_k, int64
     return MAGNUS_OK;
   if (ctx->coding < 2) {
     if (with_k ? !ctx->kc_codable : !ctx->codable.count(pair_key(h))) return MAGNUS_OK;
-    // Coding costs what about three iterations gain from 2^16 rows on (chains, us: coding, and an iteration on
-    // the CSR arrays / on the coded terms: n = 16 21, 15.8 / 8.1; n = 18 53, 35 / 15; n = 20 200, 151 / 47), about
-    // 20 below (n = 14 15, 6.8 / 6.0) and 45 at the smallest sizes (n = 12 13, 6.2 / 5.9); an exponential
-    // takes four iterations or more.  Pairs gain a decide kernel in every iteration too.
-    const int64_t pays = dim >= 65536 ? 1 : npairs > 0 ? 2 : dim >= 16384 ? 6 : 16;
-    if (exponentials < pays) return MAGNUS_OK;
+    if (exponentials < coding_pays(h, npairs, use)) return MAGNUS_OK;
   }
   magnus::CodeTerms T{2, {csr_dev(h->H1), csr_dev(h->H2)}};
   if (with_k) T.m[T.n++] = CsrDev{ctx->kc_rp, ctx->kc_ci, ctx->kc_val};
@@ -415,35 +430,42 @@ int begin_coded(magnus_ctx* ctx, const magnus_hamiltonian* h, bool with_k, int64
 
 // Row mapping of the single-state CSR iteration for a variant code (the
 // MAGNUS_CSR_VARIANT numbering; 0 = the size heuristic).
-int variant_rows(int code, int64_t dim) {
+int variant_rows(int code, int64_t dim, bool two_pass = false) {
   switch (code) {
-    case 1: return dim >= 65536 ? 64 : 16;
+    case 1: return dim > 131072 ? 64 : dim > 65536 ? magnus::kRowsDirect + 64 : magnus::kRowsDirect + 32;
     case 2: return magnus::kRowLane;
     case 3: return -32;
     case 4: return -128;
     case 5: return magnus::kWaveTile + 8;
     case 6: return magnus::kWaveTile + 16;
     case 7: return magnus::kStreamTile;
-    // Measured on spin chains, Cf4 steps/s with each mapping (the stop test is
-    // fused into the iteration on grids of at most kFuseMaxGrid workgroups, else
-    // a decide kernel follows every iteration): the streamed tiles from 2^17
-    // rows on (n = 17: 2,566 against 2,378 with 8-row wave tiles; n = 18, 19,
-    // 20: 42 vs 48 us and 169 vs 183 us per iteration), 16-row wave tiles at
-    // 2^16 (3,796 against 3,730), a row per lane in blocks of 64 rows at 2^15
-    // (8,134 against 4,922 with 16-row nonzero streaming) and of 32 rows
-    // below (n = 14: 9,183 against 7,585; n = 13: 9,983 against 9,657).
+    // Measured, us per iteration with each mapping (the stop test is made by the
+    // iteration on grids of at most csr2_fuse_grid workgroups, else by a decide
+    // kernel after it), random terms with 6 / 24 / 38 entries a row where no
+    // other are named.  Eight lanes per row (direct) against a row per lane:
+    // 20,000 rows 6.1 / 8.0 / 10.2 against 6.9 / 8.2 / 10.5, 50,021 rows
+    // 11.1 / 15.7 / 22.2 against 11.7 / 17.2 / 24.8; chains of 13 and 14 sites
+    // 5.2 / 5.9 against 6.3 / 6.8.  In between the rows fill one round of
+    // workgroups of 64 rows: 33,000 rows 8.6 / 10.6 / 14.6 against
+    // 7.3 / 10.1 / 15.3, n = 15 7.7 against 7.6.  From 2^16 rows on the
+    // wave tiles of 16 rows: 100,003 rows 17.1 / 28.6 / 37.6 (direct) against
+    // 19.4 / 30.3 / 41.3; but two passes per iteration (a commutator applied to
+    // vectors) on spin models of 2^16 rows 23.9 against 22.5.  Streamed tiles
+    // from 2^17 rows on: 160,001 rows 26.2 / 43.9 / 58.9 (direct) against
+    // 23.7 / 38.3 / 59.5.
     default:
-      return dim >= 131072 ? magnus::kStreamTile
-             : dim >= 65536 ? magnus::kWaveTile + 16
-             : dim >= 32768 ? -64
-                            : -32;
+      return dim >= 131072  ? magnus::kStreamTile
+             : dim >= 65536 ? (two_pass ? magnus::kWaveTile + 16 : magnus::kRowsDirect + 64)
+             : dim >= 49152 ? magnus::kRowsDirect + 32
+             : dim >= 28672 ? -64
+                            : magnus::kRowsDirect + 32;
   }
 }
 
-int rows_per_block(magnus_ctx* ctx, const magnus_hamiltonian* h) {
-  if (ctx->csr_variant) return variant_rows(ctx->csr_variant, h->H1.dim);
+int rows_per_block(const magnus_ctx* ctx, const magnus_hamiltonian* h, bool two_pass = false) {
+  if (ctx->csr_variant) return variant_rows(ctx->csr_variant, h->H1.dim, two_pass);
   auto it = ctx->tuned_variant.find({(const void*)h->H1.row_ptr, h->H1.dim});
-  return variant_rows(it == ctx->tuned_variant.end() ? 0 : it->second, h->H1.dim);
+  return variant_rows(it == ctx->tuned_variant.end() ? 0 : it->second, h->H1.dim, two_pass);
 }
 
 // Tuned dense choices (the defaults until magnus_autotune ran on these terms).
@@ -512,10 +534,11 @@ int flush_pair_check(magnus_ctx* ctx, hipStream_t s) {
 // most kFuseMaxGrid workgroups (every workgroup reduces iteration i-1's
 // partials, which alternate between two halves of the partials buffer),
 // else a decide kernel after each iteration.  Sets a->fused.
-int setup_stop_test(magnus_ctx* ctx, const ExpPlan& P, int i, int grid, IterArgs* a, hipStream_t s) {
+int setup_stop_test(magnus_ctx* ctx, const ExpPlan& P, int i, int grid, IterArgs* a, hipStream_t s,
+                    int limit = magnus::kFuseMaxGrid) {
   a->iter = i;
   a->fused = 0;
-  if (!ctx->fuse || grid > magnus::kFuseMaxGrid) return flush_fused_check(ctx, s);
+  if (!ctx->fuse || grid > limit) return flush_fused_check(ctx, s);
   const size_t half = 2 * (size_t)ctx->max_grid;
   a->fused = 1;
   a->partials = ctx->partials + (size_t)(i & 1) * half;
@@ -660,12 +683,12 @@ int launch_iteration(magnus_ctx* ctx, const ExpOp& op, const ExpPlan& P, int i, 
   if (ctx->coded_h == h) return launch_coded(ctx, op, P, i, win, a, s);
   CsrDev t1{h->H1.row_ptr, h->H1.col_idx, reinterpret_cast<const double2*>(h->H1.val)};
   CsrDev t2{h->H2.row_ptr, h->H2.col_idx, reinterpret_cast<const double2*>(h->H2.val)};
-  const int rpb = rows_per_block(ctx, h);
   if (op.kappa == 0.0) {
     a.x1 = win;
     a.x2 = win;
+    const int rpb = rows_per_block(ctx, h);
     const int grid = magnus::csr2_grid(dim, rpb);
-    if (int rc = setup_stop_test(ctx, P, i, grid, &a, s)) return rc;
+    if (int rc = setup_stop_test(ctx, P, i, grid, &a, s, magnus::csr2_fuse_grid(rpb))) return rc;
     const bool fused = a.fused;
     HIP_TRY(timed(ctx, MAGNUS_KERNEL_CSR_LEJA, s,
                   [&] { return magnus::launch_csr2_iter(magnus::kLeja, t1, t2, dim, a, rpb, s); }));
@@ -677,12 +700,12 @@ int launch_iteration(magnus_ctx* ctx, const ExpOp& op, const ExpPlan& P, int i, 
     CsrDev t3{ctx->kc_rp, ctx->kc_ci, ctx->kc_val};
     a.x1 = win;
     a.x2 = win;
-    const bool streamed = rpb == magnus::kStreamTile;  // the three-term kernel follows the two-term choice
-    const int grid = magnus::csr3_grid(dim, streamed);
-    if (int rc = setup_stop_test(ctx, P, i, grid, &a, s)) return rc;
+    const int rpb = magnus::csr3_rows(dim, rows_per_block(ctx, h));
+    const int grid = magnus::csr2_grid(dim, rpb);
+    if (int rc = setup_stop_test(ctx, P, i, grid, &a, s, magnus::csr2_fuse_grid(rpb))) return rc;
     const bool fused = a.fused;
     HIP_TRY(timed(ctx, MAGNUS_KERNEL_CSR_LEJA3, s,
-                  [&] { return magnus::launch_csr3_iter(t1, t2, t3, dim, a, P.scale * op.kappa, streamed, s); }));
+                  [&] { return magnus::launch_csr3_iter(t1, t2, t3, dim, a, P.scale * op.kappa, rpb, s); }));
     if (!fused) HIP_TRY(magnus::launch_leja_decide(a, grid, s));
     return MAGNUS_OK;
   }
@@ -692,8 +715,9 @@ int launch_iteration(magnus_ctx* ctx, const ExpOp& op, const ExpPlan& P, int i, 
   // partials the next iteration's first pass reduces.
   double2* U = ctx->vec(kU);
   double2* V = ctx->vec(kV);
+  const int rpb = rows_per_block(ctx, h, true);
   const int grid = magnus::csr2_grid(dim, rpb);
-  if (int rc = setup_stop_test(ctx, P, i, grid, &a, s)) return rc;
+  if (int rc = setup_stop_test(ctx, P, i, grid, &a, s, magnus::csr2_fuse_grid(rpb))) return rc;
   const bool fused = a.fused;
   IterArgs p1 = a;
   p1.x1 = win;
@@ -1703,11 +1727,10 @@ int64_t graph_table_cap(const magnus_ctx*) {
 bool graph_eligible(magnus_ctx* ctx, const magnus_hamiltonian* h, const magnus::Scheme& S) {
   if (!ctx->graph || !ctx->fuse || ctx->timing || h->H1.format != MAGNUS_CSR || S.sixth) return false;
   const int dim = (int)h->H1.dim;
-  const int rpb = rows_per_block(ctx, h);
   if (ctx->coded_h == h) return magnus::code_grid(dim, ctx->coded.rows) <= magnus::kFuseMaxGrid;
-  int grid = magnus::csr2_grid(dim, rpb);
-  if (S.commutator && csr_comm_ready(ctx, h)) grid = magnus::csr3_grid(dim, rpb == magnus::kStreamTile);
-  return grid <= magnus::kFuseMaxGrid;
+  int rpb = rows_per_block(ctx, h, S.commutator);
+  if (S.commutator && csr_comm_ready(ctx, h)) rpb = magnus::csr3_rows(dim, rows_per_block(ctx, h));
+  return magnus::csr2_grid(dim, rpb) <= magnus::csr2_fuse_grid(rpb);
 }
 
 template <class F>
@@ -2381,7 +2404,7 @@ int magnus_autotune(magnus_ctx* ctx, const magnus_hamiltonian* h, int32_t batch,
     double us = 0.0;
     // an iteration on a grid too large for the fused stop test is followed by
     // the decide kernel, so that is timed with it
-    const bool decide = !ctx->fuse || magnus::csr2_grid(dim, rpb) > magnus::kFuseMaxGrid;
+    const bool decide = !ctx->fuse || magnus::csr2_grid(dim, rpb) > magnus::csr2_fuse_grid(rpb);
     err = time_us(
         [&] {
           hipError_t e = magnus::launch_csr2_iter(magnus::kLeja, t1, t2, dim, a, rpb, s);
@@ -2844,10 +2867,10 @@ int propagate(magnus_ctx* ctx, const magnus_hamiltonian* h, int32_t method, doub
     const int64_t k = ((n / every_k) + 1) * every_k;
     return std::min(k, nsteps);
   };
-  if (!small && tau != 0.0)  // (M6: three passes per iteration)
+  if (!small && tau != 0.0)
     if ((rc = begin_coded(ctx, h, S.commutator && csr_comm_ready(ctx, h),
-                          exps * (S.commutator ? batch : 1) * (S.sixth ? 3 : 1),
-                          grouped ? std::min(batch / 2, 16) : 0, s)))
+                          exps * (S.commutator ? batch : 1), grouped ? std::min(batch / 2, 16) : 0, s,
+                          S.sixth ? CodeUse::kM6 : CodeUse::kSingle)))
       return rc;
   // one state on the grid path with every stop test fused: one step captured,
   // replayed once per step
@@ -3097,7 +3120,7 @@ int magnus_propagate_adjoint(magnus_ctx* ctx, const magnus_hamiltonian* h, doubl
   if ((rc = ensure_valid(ctx, h, s))) return rc;
 
   if (tau != 0.0)
-    if ((rc = begin_coded(ctx, h, false, 6 * nsteps, 0, s))) return rc;
+    if ((rc = begin_coded(ctx, h, false, 6 * nsteps, 0, s, CodeUse::kGradient))) return rc;
   if (ctx->coded_h == h && (!ctx->fuse || !pair_partials_fit(ctx, 2LL * magnus::code_grid((int)h->H1.dim, ctx->coded.rows))))
     ctx->coded_h = nullptr;
   const int64_t dim = h->H1.dim;

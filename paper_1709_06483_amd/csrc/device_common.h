@@ -151,28 +151,31 @@ __device__ __forceinline__ IterArgs resolve_args(const IterArgs& in) {
 // cost two more round trips in every iteration).
 constexpr int kFuseLds = 40;
 constexpr int kStopLoads = 4;  // partial sums per thread: kFuseMaxGrid over at least 256 threads
+template <int N = kStopLoads>
 struct StopLoads {
-  double w[kStopLoads], v[kStopLoads];
+  double w[N], v[N];
   double vnorm, term;
   int stopped;
 };
-__device__ __forceinline__ void stop_loads(const IterArgs& a, StopLoads& s) {
+template <int N>
+__device__ __forceinline__ void stop_loads(const IterArgs& a, StopLoads<N>& s) {
   s.stopped = a.check_stop ? load_stopped(a.slot) : 0;
   if (!a.fused || !a.check_stop) return;
   const int n = a.prev_grid, nt = blockDim.x, tid = threadIdx.x;
 #pragma unroll
-  for (int u = 0; u < kStopLoads; ++u) s.w[u] = a.prev_partials[min(u * nt + tid, n - 1)];
+  for (int u = 0; u < N; ++u) s.w[u] = a.prev_partials[min(u * nt + tid, n - 1)];
   s.vnorm = s.term = 0.0;
   if (a.iter == 2) {  // the previous iteration was the substep's first
 #pragma unroll
-    for (int u = 0; u < kStopLoads; ++u) s.v[u] = a.prev_partials[n + min(u * nt + tid, n - 1)];
+    for (int u = 0; u < N; ++u) s.v[u] = a.prev_partials[n + min(u * nt + tid, n - 1)];
   } else {
     s.vnorm = a.slot->vnorm;
     s.term = a.slot->term[a.iter & 1];  // iteration iter-2's term
   }
 }
 
-__device__ __forceinline__ bool stop_verdict(const IterArgs& a, const StopLoads& s, double* lds) {
+template <int N>
+__device__ __forceinline__ bool stop_verdict(const IterArgs& a, const StopLoads<N>& s, double* lds) {
   if (!a.fused) return a.skip || s.stopped;
   Slot* S = a.slot;
   const int tid = threadIdx.x;
@@ -191,7 +194,7 @@ __device__ __forceinline__ bool stop_verdict(const IterArgs& a, const StopLoads&
   const bool vfirst = a.iter == 2;
   double sw = 0.0, sv = 0.0;
 #pragma unroll
-  for (int u = 0; u < kStopLoads; ++u)
+  for (int u = 0; u < N; ++u)
     if (u * nt + tid < n) {
       sw += s.w[u];
       if (vfirst) sv += s.v[u];
@@ -234,7 +237,7 @@ __device__ __forceinline__ bool stop_verdict(const IterArgs& a, const StopLoads&
 }
 
 __device__ __forceinline__ bool iteration_stopped(const IterArgs& a, double* lds) {
-  StopLoads s;
+  StopLoads<> s;
   stop_loads(a, s);
   return stop_verdict(a, s, lds);
 }

@@ -102,6 +102,9 @@ constexpr int kWaveTile = 1000;
 // wave walks 8 tiles of 8 rows, copying each tile's entries into LDS one tile
 // ahead.
 constexpr int kStreamTile = 2000;
+// kRowsDirect + R selects eight lanes per row without staging, R = 32 (up to
+// 32,768 rows) or 64 (up to 262,144) rows per workgroup (of 8 R threads).
+constexpr int kRowsDirect = 4000;
 
 // Launch one iteration over `dim` rows of the two CSR terms.
 hipError_t launch_csr2_iter(int mode, const CsrDev& t1, const CsrDev& t2, int dim,
@@ -109,6 +112,8 @@ hipError_t launch_csr2_iter(int mode, const CsrDev& t1, const CsrDev& t2, int di
 
 // Grid size (workgroups) of launch_csr2_iter for `dim` rows.
 int csr2_grid(int dim, int rows_per_block);
+// Largest grid of that mapping that makes the stop test itself.
+int csr2_fuse_grid(int rows_per_block);
 
 // CSR entries (both terms, from the start of the matrix) that the iteration
 // kernels read with normal loads so that they stay in the 256 MiB MALL from
@@ -386,11 +391,11 @@ constexpr int kCommCap = 1024;
 hipError_t launch_csr_commutator(bool fill, const CsrDev& A, const CsrDev& Bm, int dim, int* counts,
                                  const int* rp_out, int* ci_out, double2* val_out, int* overflow, hipStream_t s);
 // One Leja iteration on a1 H1 + a2 H2 + a3 K (kLeja semantics, x = a.x1).
-// streamed: the three-term kernel streamed through LDS like kStreamTile (grid
-// csr2_stream_grid), else the 8-row wave tiles.
-int csr3_grid(int dim, bool streamed);
+// rows_per_block: csr3_rows, for the mapping that the two-term iteration takes
+// (grid csr2_grid).
+int csr3_rows(int dim, int rows_per_block);
 hipError_t launch_csr3_iter(const CsrDev& t1, const CsrDev& t2, const CsrDev& t3, int dim, const IterArgs& a,
-                            double a3, bool streamed, hipStream_t s);
+                            double a3, int rows_per_block, hipStream_t s);
 hipError_t launch_csr3_stream(const CsrDev& t1, const CsrDev& t2, const CsrDev& t3, int dim, const IterArgs& a,
                               double a3, hipStream_t s);
 

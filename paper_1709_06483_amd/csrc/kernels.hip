@@ -526,6 +526,160 @@ __global__ __launch_bounds__(kThreads, MODE == kLejaComm ? 6 : 7) void csr2_wave
 }
 
 // ---------------------------------------------------------------------------
+// CSR iteration on two terms, or with NT = 3 also on the assembled commutator
+// (mode kLeja), eight lanes per row without staging.  A lane takes every eighth
+// entry of the row's terms (one list, term 1's first), U of them at a time.
+// Up to about 2^15 rows an iteration is bound by its chain of dependent loads:
+// the stop test's inputs, the row's bounds and its own elements go out first,
+// then the U entries, then (once the verdict is known) the U gathers; beyond
+// that by the gathers that leave the L2.  Against staging a block's entries in
+// LDS with a row to a lane, us per iteration: chains, n = 13 6.3, now 5.2,
+// n = 14 6.8, now 5.9; 50,021 rows of 24 random entries 17.2, now 15.7; with the
+// commutator assembled, n = 12 8.1 (a wave to 8 rows), now 5.3, n = 16 24.6, now
+// 16.7.  U = 4 leaves rows of 24 entries a second chain of loads (16.1), U = 6
+// takes registers (15.7, and 6.7 / 6.5 at 5,000 rows of 38).
+// ---------------------------------------------------------------------------
+constexpr int kRowLanes = 8;
+
+// Sum over the 8 lanes of a row, in all of them: quads, then the quads' mirror images.
+__device__ __forceinline__ double lanes8_sum(double v) {
+  auto moved = [](double x, auto ctrl) {
+    union U {
+      double d;
+      unsigned u[2];
+    } a{x}, b;
+    for (int j = 0; j < 2; ++j) b.u[j] = __builtin_amdgcn_mov_dpp(a.u[j], decltype(ctrl)::value, 0xf, 0xf, true);
+    return b.d;
+  };
+  v += moved(v, std::integral_constant<int, 0xB1>{});   // quad_perm 1, 0, 3, 2
+  v += moved(v, std::integral_constant<int, 0x4E>{});   // quad_perm 2, 3, 0, 1
+  return v + moved(v, std::integral_constant<int, 0x141>{});  // row_half_mirror
+}
+
+// STOP: the previous iteration's partial sums per thread.
+template <int MODE, int NT, int TH, int STOP>
+__global__ __launch_bounds__(TH, 5) void csr_rows_kernel(CsrDev t1, CsrDev t2, CsrDev t3, int dim, IterArgs a_in,
+                                                         double a3_arg) {
+  const IterArgs a = resolve_args(a_in);
+  const double a3 = a_in.coef ? a.kap : a3_arg;
+  constexpr int U = 5;
+  __shared__ double fz[kFuseLds];
+  __shared__ double red[2][TH / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, q = tid % kRowLanes;
+  const int L = xcd_remap(blockIdx.x, gridDim.x);
+  const int r = L * (TH / kRowLanes) + tid / kRowLanes, row = min(r, dim - 1);
+  const d2* x1 = reinterpret_cast<const d2*>(a.x1);
+  const d2* x2 = reinterpret_cast<const d2*>(a.x2);
+  const d2* v1 = reinterpret_cast<const d2*>(t1.val);
+  const d2* v2 = reinterpret_cast<const d2*>(t2.val);
+  const d2* v3 = reinterpret_cast<const d2*>(t3.val);
+  StopLoads<STOP> stop;
+  stop_loads(a, stop);
+  const int s1 = t1.rp[row], s2 = t2.rp[row];
+  const int s3 = NT == 3 ? t3.rp[row] : 0, e3 = NT == 3 ? t3.rp[row + 1] : 0;
+  const int n1 = r < dim ? t1.rp[row + 1] - s1 : 0, n2 = r < dim ? n1 + t2.rp[row + 1] - s2 : 0;
+  const int n = r < dim ? n2 + e3 - s3 : 0;  // (n1, n2, n: where the terms end in the row's list)
+  d2 w_old, p_old = {0.0, 0.0}, u_old = {0.0, 0.0}, v_old = {0.0, 0.0};
+  if (MODE != kSplit) {
+    w_old = tod2(a.wcur[row]);
+    if (!a.first) p_old = tod2(a.pacc[row]);
+    if (MODE == kLejaComm) {
+      u_old = x2[row];
+      v_old = x1[row];
+    }
+  }
+  int col[U];
+  d2 val[U];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = k0 + kRowLanes * u;
+      col[u] = 0;
+      val[u] = d2{0.0, 0.0};
+      if (k < n) {
+        const bool in1 = k < n1, in2 = NT == 2 || k < n2;
+        col[u] = (in1 ? t1.ci + s1 : in2 ? t2.ci + (s2 - n1) : t3.ci + (s3 - n2))[k];
+        val[u] = (in1 ? v1 + s1 : in2 ? v2 + (s2 - n1) : v3 + (s3 - n2))[k];
+      }
+    }
+  };
+  load(q);
+  __builtin_amdgcn_sched_barrier(0);
+  if (stop_verdict(a, stop, fz)) return;
+  d2 acc1 = {0.0, 0.0}, acc2 = {0.0, 0.0};
+  for (int k0 = q;;) {
+    d2 g[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      g[u] = d2{0.0, 0.0};
+      if (k0 + kRowLanes * u < n) g[u] = (k0 + kRowLanes * u < n1 ? x1 : x2)[col[u]];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const d2 y = cmul(val[u], g[u]);
+      const bool in1 = k0 + kRowLanes * u < n1;
+      if constexpr (NT == 3) {
+        acc1 += rmul(in1 ? a.a1 : k0 + kRowLanes * u < n2 ? a.a2 : a3, y);
+      } else {
+        acc1 += in1 ? y : d2{0.0, 0.0};
+        acc2 += in1 ? d2{0.0, 0.0} : y;
+      }
+    }
+    k0 += kRowLanes * U;
+    if (!__any(k0 < n)) break;
+    load(k0);
+  }
+  acc1 = d2{lanes8_sum(acc1.x), lanes8_sum(acc1.y)};
+  if (NT == 2) acc2 = d2{lanes8_sum(acc2.x), lanes8_sum(acc2.y)};
+  const bool owner = q == 0 && r < dim;
+  if constexpr (MODE == kSplit) {
+    if (owner) {
+      a.wout[r] = fromd2(acc1);
+      a.pacc[r] = fromd2(acc2);
+    }
+  } else {
+    double pw = 0.0, pv = 0.0;
+    if (owner) {
+      d2 y;
+      if constexpr (NT == 3) {
+        y = acc1;
+      } else if constexpr (MODE == kLeja) {
+        y = rmul(a.a1, acc1) + rmul(a.a2, acc2);
+      } else {
+        const d2 dl = acc1 - acc2;
+        y = rmul(a.a1, u_old) + rmul(a.a2, v_old) + d2{-a.kap * dl.y, a.kap * dl.x};
+      }
+      const d2 wn = y - rmul(a.sigma, w_old);
+      d2 p;
+      if (a.first) {
+        p = cmul(tod2(a.d0), w_old) + cmul(tod2(a.d), wn);
+        pv = nrm2(w_old);
+      } else {
+        p = p_old + cmul(tod2(a.d), wn);
+      }
+      a.wout[r] = fromd2(wn);
+      a.pacc[r] = fromd2(p);
+      pw = nrm2(wn);
+    }
+    pw = lanes_sum(pw);
+    pv = lanes_sum(pv);
+    if (lane == 0) {
+      red[0][wv] = pw;
+      red[1][wv] = pv;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      double bw = 0.0, bv = 0.0;
+      for (int k = 0; k < TH / 64; ++k) {
+        bw += red[0][k];
+        bv += red[1][k];
+      }
+      store_partials(a, bw, bv);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Dense iterations (row-major matrices), bound by the matrix bytes.  A
 // workgroup owns the rows [dim b / grid, dim (b+1) / grid) and its four waves
 // split the columns: lane l of wave q sums columns j = 64 q + l + 256 m, so
@@ -550,7 +704,7 @@ __device__ __forceinline__ bool dense_rows(const IterArgs& a, int dim, int row0,
                                            double* fz) {
   constexpr int kStep = kThreads * UNR;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  StopLoads stop;
+  StopLoads<> stop;
   stop_loads(a, stop);
   f.load(row0, tid);
   __builtin_amdgcn_sched_barrier(0);
@@ -838,11 +992,45 @@ int csr_keep_entries(int dim) {
   return (int)std::min<long long>(keep, 1LL << 30);
 }
 
+int csr2_fuse_grid(int rows_per_block) { return rows_per_block > kRowsDirect ? 2048 : kFuseMaxGrid; }
+
 int csr2_grid(int dim, int rows_per_block) {
   if (rows_per_block == kStreamTile) return csr2_stream_grid(dim);
   int rows = rows_per_block < 0 ? -rows_per_block : rows_per_block;
-  if (rows_per_block > kWaveTile) rows = (rows_per_block - kWaveTile) * (kThreads / 64);
+  if (rows_per_block > kRowsDirect) rows = rows_per_block - kRowsDirect;
+  else if (rows_per_block > kWaveTile) rows = (rows_per_block - kWaveTile) * (kThreads / 64);
   return (dim + rows - 1) / rows;
+}
+
+namespace {
+template <int MODE, int NT>
+hipError_t launch_rows(const CsrDev& t1, const CsrDev& t2, const CsrDev& t3, int dim, const IterArgs& a, double a3,
+                       int rows_per_block, hipStream_t s) {
+  const int grid = csr2_grid(dim, rows_per_block);
+  if (rows_per_block == kRowsDirect + 32 && grid <= 1024)
+    csr_rows_kernel<MODE, NT, 256, 4><<<grid, 256, 0, s>>>(t1, t2, t3, dim, a, a3);
+  else if (rows_per_block == kRowsDirect + 32 && grid <= 2048)
+    csr_rows_kernel<MODE, NT, 256, 8><<<grid, 256, 0, s>>>(t1, t2, t3, dim, a, a3);
+  else if (rows_per_block == kRowsDirect + 64 && grid <= 2048)
+    csr_rows_kernel<MODE, NT, 512, 4><<<grid, 512, 0, s>>>(t1, t2, t3, dim, a, a3);
+  else
+    return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+}  // namespace
+
+// Streamed tiles where the two terms are streamed (and past the direct kernel's
+// largest grid), else eight lanes per row: chains of 10, 14 and 16 sites 5.3, 6.3
+// and 16.7 us per iteration, against 7.5, 9.5 and 24.6 with a wave to 8 rows.
+int csr3_rows(int dim, int rows_per_block) {
+  if (rows_per_block == kStreamTile || dim > 131072) return kStreamTile;
+  return dim > 65536 ? kRowsDirect + 64 : kRowsDirect + 32;
+}
+
+hipError_t launch_csr3_iter(const CsrDev& t1, const CsrDev& t2, const CsrDev& t3, int dim, const IterArgs& a, double a3,
+                            int rows_per_block, hipStream_t s) {
+  if (rows_per_block == kStreamTile) return launch_csr3_stream(t1, t2, t3, dim, a, a3, s);
+  return launch_rows<kLeja, 3>(t1, t2, t3, dim, a, a3, rows_per_block, s);
 }
 
 hipError_t launch_csr2_iter(int mode, const CsrDev& t1, const CsrDev& t2, int dim, const IterArgs& a,
@@ -855,9 +1043,6 @@ hipError_t launch_csr2_iter(int mode, const CsrDev& t1, const CsrDev& t2, int di
   MAGNUS_CSR_CASE(64, kLeja)
   MAGNUS_CSR_CASE(64, kSplit)
   MAGNUS_CSR_CASE(64, kLejaComm)
-  MAGNUS_CSR_CASE(16, kLeja)
-  MAGNUS_CSR_CASE(16, kSplit)
-  MAGNUS_CSR_CASE(16, kLejaComm)
 #undef MAGNUS_CSR_CASE
 #define MAGNUS_ROWLANE_CASE(R)                                                                     \
   if (rows_per_block == -R) {                                                                      \
@@ -883,6 +1068,11 @@ hipError_t launch_csr2_iter(int mode, const CsrDev& t1, const CsrDev& t2, int di
   MAGNUS_WAVE_CASE(8)
   MAGNUS_WAVE_CASE(16)
 #undef MAGNUS_WAVE_CASE
+  if (rows_per_block > kRowsDirect) {
+    if (mode == kLeja) return launch_rows<kLeja, 2>(t1, t2, t2, dim, a, 0.0, rows_per_block, s);
+    if (mode == kSplit) return launch_rows<kSplit, 2>(t1, t2, t2, dim, a, 0.0, rows_per_block, s);
+    return launch_rows<kLejaComm, 2>(t1, t2, t2, dim, a, 0.0, rows_per_block, s);
+  }
   return hipErrorInvalidValue;
 }
 

@@ -326,7 +326,7 @@ __global__ __launch_bounds__(THREADS, 4) void coded_iter_kernel(CodeTerms T, int
                      reinterpret_cast<const d2*>(a.x1)};
   const int last_slice = (dim - 1) / 16;
 
-  StopLoads stop;
+  StopLoads<> stop;
   stop_loads(a, stop);
   static_assert(THREADS > kCodeMax, "a thread per dictionary entry");
   const d2 ent_val = tod2(C.dict[(size_t)L * (kCodeMax + 1) + (tid & kCodeMax)].val);

@@ -218,7 +218,7 @@ __global__ __launch_bounds__(kThreads, 4) void coded_m6_kernel(CodeTerms T, int 
   const int last_slice = (dim - 1) / 16;
 
   // everything that needs no other load's result, together
-  StopLoads stop;
+  StopLoads<> stop;
   int stopped = 0;
   if (STAGE == 0) stop_loads(a, stop);
   else if (a.check_stop) stopped = load_stopped(a.slot);
