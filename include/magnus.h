@@ -155,9 +155,9 @@ typedef struct {
  * max_dim entries and batches of up to max_batch states (allocated here; later
  * allocations happen only in magnus_reserve_dense, magnus_dense_commutator,
  * magnus_dense_m6_prepare, magnus_csr_commutator and magnus_csr_m6_prepare;
- * about 8 vectors per state, and 184 bytes per row of max_dim for the coded
- * form of CSR terms below).  *out receives the
- * context.  Calls on one context share its workspace: they must not run
+ * about 8 vectors per state, 184 bytes per row of max_dim for the coded form
+ * of CSR terms below, and with max_batch > 1 at most 16 MiB for partial
+ * products of dense groups).  *out receives the context.  Calls on one context share its workspace: they must not run
  * concurrently from several host threads, and work they enqueue on different
  * streams must not overlap on the device (one stream per context, or the
  * caller orders them).  Errors: EINVAL (null out, max_dim < 1, max_batch < 1),

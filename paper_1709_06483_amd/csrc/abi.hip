@@ -86,6 +86,8 @@ struct magnus_ctx {
   bool coded_pairs = false;      // the states of the current call's batch run as interleaved pairs
   magnus::PairArgs pair_last{};  // the last launch of pairs, for the check of its norms
   bool pair_pending = false;
+  double2* split = nullptr;      // shares of a dense group's products (split_entries of them)
+  long long split_entries = 0;
   double* dots = nullptr;        // per-workgroup sums of dot products, and a result (inside partials)
   int coding = 1;   // MAGNUS_CODED: 0 reads the CSR arrays in every iteration, 2 codes the terms of every call
   // term pairs found to fit the coded form when they were scanned: only a
@@ -486,6 +488,13 @@ int mfma_tile(const magnus_ctx* ctx, const magnus_hamiltonian* h, int B) {
   if (it != ctx->tuned_mfma.end()) return it->second;
   const long long blocks = (h->H1.dim + 63) / 64 * ((B + 63) / 64);
   return blocks >= 256 ? 6 : 5;
+}
+
+// Workgroups per block of that tile (1: the tile as it is), whose shares and
+// norm partials (two per state and 16 rows) must fit the workspace.
+int mfma_split(const magnus_ctx* ctx, int dim, int B, int tile) {
+  if ((size_t)magnus::dense_mfma_row_blocks(dim, 2) * (size_t)B * 2 > ctx->npartials) return 1;
+  return magnus::dense_mfma_split(dim, B, tile, ctx->split_entries);
 }
 
 hipEvent_t next_event(magnus_ctx* ctx) {
@@ -1196,7 +1205,9 @@ int launch_multi(magnus_ctx* ctx, const magnus_hamiltonian* h, const MultiExp& E
   CsrDev t1{h->H1.row_ptr, h->H1.col_idx, reinterpret_cast<const double2*>(h->H1.val)};
   CsrDev t2{h->H2.row_ptr, h->H2.col_idx, reinterpret_cast<const double2*>(h->H2.val)};
   const bool dense = h->H1.format == MAGNUS_DENSE;
-  const int grid = dense ? (E.frechet ? magnus::dense_frechet_grid(dim) : magnus::dense_mfma_row_blocks(dim))
+  const int tile = dense && !E.frechet ? mfma_tile(ctx, h, B) : 0;
+  const int split = dense && !E.frechet ? mfma_split(ctx, dim, B, tile) : 1;
+  const int grid = dense ? (E.frechet ? magnus::dense_frechet_grid(dim) : magnus::dense_mfma_row_blocks(dim, split))
                          : magnus::csr2_multi_grid(dim, B);
   const int mode = E.frechet ? magnus::kMultiFrechet : magnus::kMultiLeja;
   if (grid <= 0 || (size_t)grid * (size_t)B * 2 > ctx->npartials)
@@ -1235,7 +1246,7 @@ int launch_multi(magnus_ctx* ctx, const magnus_hamiltonian* h, const MultiExp& E
                       [&] { return magnus::launch_dense_frechet(D1, D2, dim, h->H1.ld, a, s); }));
       else if (dense)
         HIP_TRY(timed(ctx, MAGNUS_KERNEL_DENSE_MFMA, s,
-                      [&] { return magnus::launch_dense_mfma(E.dense_terms, D1, D2, ldd, dim, a, s, mfma_tile(ctx, h, B)); }));
+                      [&] { return magnus::launch_dense_mfma(E.dense_terms, D1, D2, ldd, dim, a, s, tile, split, ctx->split); }));
       else
         HIP_TRY(timed(ctx, MAGNUS_KERNEL_CSR_MULTI, s, [&] { return magnus::launch_csr2_multi(mode, t1, t2, dim, a, s); }));
       HIP_TRY(magnus::launch_multi_decide(a, grid, s));
@@ -2019,6 +2030,11 @@ int magnus_create(magnus_ctx** out, int64_t max_dim, int32_t max_batch, int32_t 
   const size_t with_dots = c->npartials + magnus::kDotPartials + 64;
   if (e == hipSuccess) e = hipMalloc(&c->partials, sizeof(double) * with_dots);
   c->dots = c->partials + c->npartials;
+  if (e == hipSuccess && max_batch > 1) {
+    // groups of dense states: at most a third of the K chunks' number of shares
+    c->split_entries = std::min<long long>(magnus::kSplitEntries, (max_dim / 48 + 1) * max_dim * (long long)max_batch);
+    e = hipMalloc(&c->split, sizeof(double2) * (size_t)c->split_entries);
+  }
   if (e == hipSuccess) e = hipMalloc(&c->scan, sizeof(double) * (size_t)c->scan_len);
   if (e == hipSuccess) e = hipMalloc(&c->gctr, 256);
   if (const char* v = getenv("MAGNUS_CODED")) c->coding = atoi(v);
@@ -2332,7 +2348,8 @@ int autotune_dense(magnus_ctx* ctx, const magnus_hamiltonian* h, int32_t batch, 
       m.B = batch;
       m.first = 1;
       double us = 0.0;
-      err = time_us([&] { return magnus::launch_dense_mfma(one ? 1 : 2, D1, D2, h->H1.ld, dim, m, s, t); }, &us);
+      const int split = mfma_split(ctx, dim, m.B, t);
+      err = time_us([&] { return magnus::launch_dense_mfma(one ? 1 : 2, D1, D2, h->H1.ld, dim, m, s, t, split, ctx->split); }, &us);
       if (group_us) group_us[t] = us;
       if (us < best_t) {
         best_t = us;
@@ -2484,6 +2501,7 @@ int magnus_destroy(magnus_ctx* ctx) {
   if (ctx->pm_ws) (void)hipFree(ctx->pm_ws);
   if (ctx->partials) (void)hipFree(ctx->partials);
   if (ctx->scan) (void)hipFree(ctx->scan);
+  if (ctx->split) (void)hipFree(ctx->split);
   if (ctx->graph_x || ctx->graph_g) {
     if (ctx->graph_done) (void)hipEventSynchronize(ctx->graph_done);
     graph_release(ctx);

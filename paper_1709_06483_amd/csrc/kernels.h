@@ -336,13 +336,19 @@ hipError_t launch_unpack(const double2* src, double2* dst, int dim, int B, hipSt
 
 // Dense group iteration as an FP64 MFMA GEMM fused with the Leja update
 // (nterms = 1: H1 only, y_b = a1_b H1 w_b; nterms = 2: y_b = H1 (a1_b w_b) + H2 (a2_b w_b)).
-// Partials are written per 32-row block: decide with dense_mfma_row_blocks(dim).
+// Partials are written per block of rows: decide with dense_mfma_row_blocks.
 // tile: 0 32 x 64 with K split in two (default), 1 32 x 64, 2 64 x 64,
-// 3 64 x 64 with K split in two, 4 32 x 128 with K split in two (rows x states).
+// 3 64 x 64 with K split in two, 4 32 x 128 with K split in two (rows x
+// states), 5 and 6 the same as 1 and 2 staged by LDS-DMA.
+// split (dense_mfma_split; tile 5): workgroups that share a block's K range,
+// their sums in scratch (split * dim * B entries) until a second kernel adds them.
 constexpr int kMfmaTiles = 7;
+constexpr long long kSplitEntries = 1 << 20;  // scratch that is ever of use
+int dense_mfma_split(int dim, int B, int tile, long long scratch);
 hipError_t launch_dense_mfma(int nterms, const double2* H1, const double2* H2, long long ld, int dim,
-                             const MultiArgs& a, hipStream_t s, int tile = 0);
-int dense_mfma_row_blocks(int dim);
+                             const MultiArgs& a, hipStream_t s, int tile = 0, int split = 1,
+                             double2* scratch = nullptr);
+int dense_mfma_row_blocks(int dim, int split = 1);
 // out = ca H1 + cb H2 (dim x dim, row stride ld in, dim out).
 // out = ca H1 + cb H2 + ck K (H1, H2 with row stride ld; K, if not null, and
 // out with row stride dim).

@@ -12,6 +12,7 @@
 // a wave computes TI x TJ MFMA tiles, four waves per K group a 32 TI x 32 TJ
 // block of rows x states; K is staged through LDS 16 at a time with the next
 // chunk prefetched into registers while the MFMAs run.
+#include <algorithm>
 #include <type_traits>
 
 #include "device_common.h"
@@ -329,6 +330,14 @@ __global__ __launch_bounds__(T::THREADS) void dense_mfma_leja_kernel(const doubl
   group_epilogue<NT, TI, TJ, WM, WN, TM, TN>(a, dim, row0, col0, wr, wc, epi, are, aim, csum);
 }
 
+// Whether all states of the 64-column block at col0 have stopped (uniform): a
+// thread per state (one thread's loop over them took 10 us at 64 states).
+__device__ __forceinline__ bool block_stopped(const MultiArgs& a, int col0) {
+  const int c = col0 + (int)threadIdx.x;
+  const bool mine = (int)threadIdx.x < dma_gemm::kTN && c < a.B;
+  return !__syncthreads_or(mine && (!a.check_stop || !load_stopped(&a.slots[c])));
+}
+
 // ---------------------------------------------------------------------------
 // The same iteration on the LDS-DMA tile product (mfma_dma.h): TM rows (32 or
 // 64) x 64 states per workgroup of TM / 8 waves, each wave 16 rows x 32
@@ -338,10 +347,9 @@ __global__ __launch_bounds__(TM * 8) void dense_mfma_dma_kernel(const double2* H
                                                                 int dim, MultiArgs a) {
   constexpr int TI = 1, TJ = 2, WM = 16, WN = 32, TN = dma_gemm::kTN;
   __shared__ double csum[TM / WM][2][TN];  // [row of waves][w|v][state]
-  __shared__ int sstop_any;
   const int B = a.B;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wr = wv >> 1, wc = wv & 1;  // wave position: TM / 16 rows x 2 columns of waves
 
   // block coordinates: the column blocks of one row block share an XCD
@@ -350,14 +358,7 @@ __global__ __launch_bounds__(TM * 8) void dense_mfma_dma_kernel(const double2* H
   const int rb = L / gx, cb = L % gx;
   const int row0 = rb * TM, col0 = cb * TN;
 
-  if (tid == 0) {
-    int any_running = 0;
-    for (int c = col0; c < min(B, col0 + TN); ++c)
-      any_running |= a.check_stop ? !load_stopped(&a.slots[c]) : 1;
-    sstop_any = any_running;
-  }
-  __syncthreads();
-  if (!sstop_any) return;  // every state of this block has stopped (uniform)
+  if (block_stopped(a, col0)) return;
 
   // per-lane operand scale factors (NT = 2): columns of this lane's B operands
   double sc[NT][TJ];
@@ -372,6 +373,110 @@ __global__ __launch_bounds__(TM * 8) void dense_mfma_dma_kernel(const double2* H
   dma_gemm::tile_product<NT, TM, TAIL>(reinterpret_cast<const d2*>(H1), reinterpret_cast<const d2*>(H2), ld,
                                        reinterpret_cast<const d2*>(a.x), B, B, dim, row0, col0, sc, are[0], aim[0]);
   group_epilogue<NT, TI, TJ, WM, WN, TM, TN>(a, dim, row0, col0, wr, wc, true, are, aim, csum);
+}
+
+// The same product where its 32 x 64 blocks leave most of the chip idle: S
+// workgroups per block sum a share of the K chunks each, into part[ks], and
+// dense_split_update_kernel adds the shares in their order and makes the Leja
+// update.  A block's time is its chain of K chunks, about 1.2 us each, so it
+// falls with the split.  us per iteration (without the decision), unsplit /
+// both kernels: 251 rows x 4 states 25 / 13, 800 x 2 61 / 18, 800 x 150 77 / 33,
+// 2,000 x 30 155 / 48, 5,000 x 64 437 / 303.
+template <int NT, bool TAIL>
+__global__ __launch_bounds__(256) void dense_mfma_split_kernel(const double2* H1, const double2* H2, long long ld,
+                                                               int dim, MultiArgs a, double2* part, int S) {
+  constexpr int TM = 32, WN = 32, TN = dma_gemm::kTN;
+  const int B = a.B;
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wr = wv >> 1, wc = wv & 1;
+  const int gx = (B + TN - 1) / TN;
+  const int L = xcd_remap(blockIdx.x, gridDim.x);
+  const int ks = L % S, rb = L / S / gx, cb = L / S % gx;
+  const int row0 = rb * TM, col0 = cb * TN;
+  if (block_stopped(a, col0)) return;
+  double sc[NT][2];
+#pragma unroll
+  for (int tj = 0; tj < 2; ++tj) {
+    const int c = col0 + wc * WN + tj * 16 + (lane & 15);
+    const ColParam P = a.prm[c < B ? c : 0];
+    sc[0][tj] = NT == 2 ? P.a1 : 1.0;
+    if constexpr (NT == 2) sc[1][tj] = P.a2;
+  }
+  const int nk = (dim + TK - 1) / TK;
+  v4d are[2], aim[2];
+  dma_gemm::tile_product<NT, TM, TAIL>(reinterpret_cast<const d2*>(H1), reinterpret_cast<const d2*>(H2), ld,
+                                       reinterpret_cast<const d2*>(a.x), B, B, dim, row0, col0, sc, are, aim,
+                                       (int)((long long)nk * ks / S), (int)((long long)nk * (ks + 1) / S));
+#pragma unroll
+  for (int tj = 0; tj < 2; ++tj) {
+    const int c = col0 + wc * WN + tj * 16 + (lane & 15);
+    if (c >= B) continue;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int r = row0 + wr * 16 + (lane >> 4) + 4 * j;
+      if (r < dim) part[((long long)ks * dim + r) * B + c] = make_double2(are[tj][j], aim[tj][j]);
+    }
+  }
+}
+
+// A workgroup per kSplitRows rows x 64 states, a thread per element (the
+// block's elements in memory order), partial norms per state and workgroup.
+constexpr int kSplitRows = 16;
+template <int NT>
+__global__ __launch_bounds__(kSplitRows * 64) void dense_split_update_kernel(int dim, MultiArgs a, const double2* part,
+                                                                             int S) {
+  constexpr int TN = dma_gemm::kTN;
+  __shared__ double norms[2][kSplitRows][TN];
+  const int B = a.B, gx = (B + TN - 1) / TN;
+  const int rb = blockIdx.x / gx, col0 = blockIdx.x % gx * TN;
+  const int cols = min(TN, B - col0), rows = min(kSplitRows, dim - rb * kSplitRows);
+  const int tid = threadIdx.x, rl = tid / cols, cl = tid % cols;
+  if (block_stopped(a, col0)) return;
+  if (rl < rows) {
+    const int r = rb * kSplitRows + rl, c = col0 + cl;
+    const long long idx = (long long)r * B + c, stride = (long long)dim * B;
+    const d2* q = reinterpret_cast<const d2*>(part) + idx;
+    const d2 w_old = reinterpret_cast<const d2*>(a.x)[idx];
+    d2 p = {0.0, 0.0};
+    if (!a.first) p = tod2(a.pacc[idx]);
+    const ColParam P = a.prm[c];
+    const bool stopped_c = a.check_stop ? load_stopped(&a.slots[c]) != 0 : false;
+    d2 y = {0.0, 0.0};
+    for (int k = 0; k < S; k += 8) {
+      d2 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = k + u < S ? q[(k + u) * stride] : d2{0.0, 0.0};
+#pragma unroll
+      for (int u = 0; u < 8; ++u) y += v[u];
+    }
+    if (NT == 1) y = rmul(P.a1, y);
+    const d2 wn = y - rmul(P.sigma, w_old);
+    const d2 dd = {P.dre, P.dim};
+    double pv = 0.0;
+    if (a.first) {
+      p = cmul(d2{P.d0re, P.d0im}, w_old) + cmul(dd, wn);
+      pv = nrm2(w_old);
+    } else if (!stopped_c) {
+      p += cmul(dd, wn);
+    }
+    a.wout[idx] = fromd2(wn);
+    a.pacc[idx] = fromd2(p);
+    norms[0][rl][cl] = nrm2(wn);
+    norms[1][rl][cl] = pv;
+  }
+  __syncthreads();
+  if (tid < cols) {
+    double sw = 0.0, sv = 0.0;
+    for (int r = 0; r < rows; ++r) {
+      sw += norms[0][r][tid];
+      sv += norms[1][r][tid];
+    }
+    const int nrb = (dim + kSplitRows - 1) / kSplitRows;
+    const long long o = ((long long)(col0 + tid) * nrb + rb) * 2;
+    a.partials[o] = sw;
+    a.partials[o + 1] = sv;
+  }
 }
 
 // H = a H1 + b H2 (+ k K) (row-major, row stride ld for H1, H2, dim for K and out).
@@ -394,8 +499,19 @@ __global__ void dense_assemble_kernel(const double2* __restrict__ H1, const doub
 
 }  // namespace
 
-// Partial sums are kept per 32-row block whatever the tile's height.
-int dense_mfma_row_blocks(int dim) { return (dim + 31) / 32; }
+// Shares of K for the 32 x 64 LDS-DMA tile: two workgroups for every CU (what
+// its LDS allows) and at least three chunks to a workgroup (its pipeline's
+// depth), as far as the scratch holds the shares.
+int dense_mfma_split(int dim, int B, int tile, long long scratch) {
+  if (tile != 5 || dim < 64) return 1;
+  const long long tiles = (long long)((dim + 31) / 32) * ((B + 63) / 64);
+  long long S = std::min<long long>(512 / tiles, (dim + TK - 1) / TK / 3);
+  S = std::min<long long>(S, scratch / ((long long)dim * B));
+  return (int)std::max<long long>(S, 1);
+}
+
+// Partial sums are kept per 32-row block whatever the tile's height (per 16 rows with K split).
+int dense_mfma_row_blocks(int dim, int split) { return split > 1 ? (dim + kSplitRows - 1) / kSplitRows : (dim + 31) / 32; }
 
 namespace {
 template <class T>
@@ -422,7 +538,22 @@ hipError_t launch_dma_tile(int nterms, const double2* H1, const double2* H2, lon
 }  // namespace
 
 hipError_t launch_dense_mfma(int nterms, const double2* H1, const double2* H2, long long ld, int dim,
-                             const MultiArgs& a, hipStream_t s, int tile) {
+                             const MultiArgs& a, hipStream_t s, int tile, int split, double2* scratch) {
+  if (split > 1) {
+    const int gx = (a.B + 63) / 64, grid = (dim + 31) / 32 * gx * split;
+    const bool tail = dim % dma_gemm::kTK != 0;
+    if (nterms == 1 && tail) dense_mfma_split_kernel<1, true><<<grid, 256, 0, s>>>(H1, H2, ld, dim, a, scratch, split);
+    else if (nterms == 1) dense_mfma_split_kernel<1, false><<<grid, 256, 0, s>>>(H1, H2, ld, dim, a, scratch, split);
+    else if (tail) dense_mfma_split_kernel<2, true><<<grid, 256, 0, s>>>(H1, H2, ld, dim, a, scratch, split);
+    else dense_mfma_split_kernel<2, false><<<grid, 256, 0, s>>>(H1, H2, ld, dim, a, scratch, split);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const int blocks = dense_mfma_row_blocks(dim, split) * gx;
+    const int threads = (kSplitRows * std::min(a.B, 64) + 63) / 64 * 64;
+    if (nterms == 1) dense_split_update_kernel<1><<<blocks, threads, 0, s>>>(dim, a, scratch, split);
+    else dense_split_update_kernel<2><<<blocks, threads, 0, s>>>(dim, a, scratch, split);
+    return hipGetLastError();
+  }
   switch (tile) {
     case 0: return launch_mfma_tile<MfmaTile<1, 2, 2>>(nterms, H1, H2, ld, dim, a, s);  // 32 x 64, K split in two
     case 1: return launch_mfma_tile<MfmaTile<1, 2, 1>>(nterms, H1, H2, ld, dim, a, s);  // 32 x 64

@@ -78,11 +78,12 @@ struct Buf {
 // 16 x 16 tiles (element j of a lane: row lane / 16 + 4 j, column lane % 16
 // of its tile; wave wv covers rows (wv / 2) * 16.., columns (wv % 2) * 32 +
 // 16 tj..) and no copy is in flight.  sc[t][tj]: scale of this lane's W
-// column in term t.  All waves of the workgroup call it.
+// column in term t.  Sums over the K chunks [c0, c1) alone where given (not
+// empty).  All waves of the workgroup call it.
 template <int NT, int TM, bool TAIL>
 __device__ __forceinline__ void tile_product(const d2* H1, const d2* H2, long long ld, const d2* W, long long ldw,
                                              int ncols, int dim, int row0, int col0, const double (&sc)[NT][2],
-                                             v4d (&are)[2], v4d (&aim)[2]) {
+                                             v4d (&are)[2], v4d (&aim)[2], int c0 = 0, int c1 = -1) {
   constexpr int TK = kTK, TN = kTN, WM = 16, WN = 32;
   constexpr int NW = TM / 8;                  // waves
   constexpr int kHCopies = TM * TK / 64;      // copies of one term's H chunk per workgroup
@@ -105,13 +106,13 @@ __device__ __forceinline__ void tile_product(const d2* H1, const d2* H2, long lo
     hdst[i] = (unsigned)(((u / kHCopies) * TK * TM + (u % kHCopies) * 64) * sizeof(d2));
   }
   const int wcol = min(col0 + lane, ncols - 1);
-  const int nk = (dim + TK - 1) / TK;
-  // copies of K chunk kc into buffer buf, indices clamped into the matrices
+  const int nk = (c1 < 0 ? (dim + TK - 1) / TK : c1) - c0;
+  // copies of K chunk c0 + kc into buffer buf, indices clamped into the matrices
   auto copy_chunk = [&](int kc, auto buf) {
     constexpr int BF = decltype(buf)::value;
     const unsigned hb = lds_offset(&Buf<NT, TM, BF>::h()[0][0][0]);
     const unsigned wb = lds_offset(&Buf<NT, TM, BF>::w()[0][0]);
-    const int k0 = min(kc, nk - 1) * TK;
+    const int k0 = (c0 + min(kc, nk - 1)) * TK;
 #pragma unroll
     for (int i = 0; i < kHOps; ++i) {
       const int u = wv * kHOps + i;
@@ -146,7 +147,7 @@ __device__ __forceinline__ void tile_product(const d2* H1, const d2* H2, long lo
     auto& sh = Buf<NT, TM, BF>::h();
     auto& sw = Buf<NT, TM, BF>::w();
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kOps) : "memory");
-    const int k0 = kc * TK;
+    const int k0 = (c0 + kc) * TK;
 #pragma unroll
     for (int ks = 0; ks < TK / 4; ++ks) {
       const bool k_in = !TAIL || k0 + ks * 4 + kq < dim;
