@@ -1576,8 +1576,22 @@ int64_t small_cap(const magnus_ctx* ctx, int64_t nstates) {
 
 bool small_candidate(const magnus_hamiltonian* h) { return h->H1.format == MAGNUS_CSR && h->H1.dim <= kSmallDim; }
 
+// Whether the one-workgroup kernels are expected to hold these terms' rows in
+// registers: 24 entries a row of real or imaginary values, which terms that fit
+// the coded form with 20 a row between them have (only a guess at what is
+// fastest: the kernel looks at every row).
+bool rows_in_registers(const magnus_ctx* ctx, const magnus_hamiltonian* h) {
+  return h->H1.dim <= magnus::kPersistStepDim && h->H1.nnz + h->H2.nnz <= 20 * h->H1.dim &&
+         ctx->codable.count(pair_key(h));
+}
+
+// One state whose matrix a workgroup would read from memory in every iteration
+// takes the grid path from 12,000 entries on (random terms, us for the same
+// iterations in one workgroup / on the grid: 10,800 entries 330 / 383, 12,000
+// 424 / 423, 13,900 458 / 385).
 bool small_ok(magnus_ctx* ctx, const magnus_hamiltonian* h, int64_t nstates) {
-  return small_candidate(h) && h->H1.dim <= small_cap(ctx, nstates);
+  if (!small_candidate(h) || h->H1.dim > small_cap(ctx, nstates)) return false;
+  return nstates > 1 || ctx->persist >= 2 || rows_in_registers(ctx, h) || h->H1.nnz + h->H2.nnz <= 12000;
 }
 
 // exp(-i tau (a H1 + b H2)) for the one-workgroup kernels: its header, and its iterations appended to the table.
@@ -1681,7 +1695,11 @@ int persist_segment(magnus_ctx* ctx, const std::vector<const magnus_hamiltonian*
   a.early = o->early_termination;
   // term 1 in LDS: one workgroup per CU then, so only while the states fit the chip
   a.cache1 = ctx->persist_cache && maxdim <= 1024 && nst <= 256;
-  for (const magnus_hamiltonian* h : hs) a.cache1 = a.cache1 && h->H1.nnz <= magnus::kPersistCache;
+  a.in_regs = 1;
+  for (const magnus_hamiltonian* h : hs) {
+    a.cache1 = a.cache1 && h->H1.nnz <= magnus::kPersistCache;
+    a.in_regs = a.in_regs && rows_in_registers(ctx, h);
+  }
   HIP_TRY(timed(ctx, MAGNUS_KERNEL_PERSIST, s, [&] { return magnus::launch_persist_propagate(a, nst, (int)maxdim, s); }));
   return MAGNUS_OK;
 }
@@ -2723,18 +2741,17 @@ int expmv_leja(magnus_ctx* ctx, const magnus_hamiltonian* h, double a, double b,
 }
 
 // One step of small states in one launch, when that is faster than a launch
-// per iteration: rows that the kernel holds in registers, which terms that fit
-// the coded form with 20 entries a row between them do (chains, us per
+// per iteration: rows that the kernel holds in registers (chains, us per
 // iteration, a launch each / in one launch: n = 6 4.4 / 0.9, n = 10 4.6 / 2.4;
-// rows that do not fit 5.2 and more), and iterations that fit the launch's
+// rows read from memory 5.2 and more), and iterations that fit the launch's
 // arguments.  *done: whether it was launched.
 static int small_step(magnus_ctx* ctx, const magnus_hamiltonian* h, const magnus::Scheme& S, double tau,
                       const double* f, const double2* in, double2* out, int batch, double tol_e,
                       const magnus_leja_opts* o, Acc* acc, bool* done, hipStream_t s) {
   *done = false;
   const int64_t dim = h->H1.dim;
-  if (dim > magnus::kPersistStepDim || batch > ctx->nslots || !small_ok(ctx, h, batch) || ctx->csr_variant ||
-      S.nexp > magnus::kPersistStepExps || h->H1.nnz + h->H2.nnz > 20 * dim || !ctx->codable.count(pair_key(h)))
+  if (batch > ctx->nslots || !small_ok(ctx, h, batch) || ctx->csr_variant ||
+      S.nexp > magnus::kPersistStepExps || !rows_in_registers(ctx, h))
     return MAGNUS_OK;
   magnus::PersistStep a{};
   std::vector<ColParam> table;

@@ -430,6 +430,7 @@ struct PersistArgs {
   Slot* slots;             // one per state
   int early;
   int cache1;              // every problem's term 1 fits kPersistCache entries (dim <= 1024)
+  int in_regs;             // the rows are expected to fit registers (dim <= 1024)
 };
 
 // Largest dimension of the one-workgroup-per-state kernel (two LDS vectors).

@@ -356,6 +356,16 @@ __device__ __forceinline__ int wave_groups(int len) {
   return __builtin_amdgcn_readfirstlane(g);
 }
 
+__device__ __forceinline__ void persist_record(Slot* S, const PersistControl& c) {
+  S->stopped = c.stopped;
+  S->iters_sub = c.iters_sub;
+  S->status |= c.status;
+  S->iters_total += c.iters;
+  S->vnorm = c.vnorm;
+  S->prev_term = c.prev;
+  S->last_est = c.est;
+}
+
 template <int R>
 __device__ __forceinline__ void persist_finish(double2* state, Slot* S, int dim, const d2 (&cur)[R],
                                                const PersistControl& c) {
@@ -363,15 +373,7 @@ __device__ __forceinline__ void persist_finish(double2* state, Slot* S, int dim,
 #pragma unroll
   for (int k = 0; k < R; ++k)
     if (tid + k * kRowThreads < dim) reinterpret_cast<d2*>(state)[tid + k * kRowThreads] = cur[k];
-  if (tid == 0) {
-    S->stopped = c.stopped;
-    S->iters_sub = c.iters_sub;
-    S->status |= c.status;
-    S->iters_total += c.iters;
-    S->vnorm = c.vnorm;
-    S->prev_term = c.prev;
-    S->last_est = c.est;
-  }
+  if (tid == 0) persist_record(S, c);
 }
 
 // Dimensions up to 1,024: R rows per thread.  Rows whose entries take at most
@@ -379,15 +381,12 @@ __device__ __forceinline__ void persist_finish(double2* state, Slot* S, int dim,
 // off-diagonal ones of a row and term all real or all imaginary, are read into
 // registers once, so that an iteration touches only LDS, where it gathers w; if
 // one row of the state does not fit, all are read from memory in every
-// iteration (CACHE: term 1's entries from a copy in LDS, one workgroup per CU
-// then).
-template <int R, bool CACHE>
+// iteration.
+template <int R>
 __device__ __forceinline__ void persist_state(const PersistProblem& pb, const PersistSchedule& plan, const double2* in,
                                               double2* out, Slot* slot) {
   __shared__ d2 X[2][kPT + 1];
   __shared__ double red[2][2][16];
-  __shared__ d2 cval[CACHE ? kPersistCache : 1];
-  __shared__ int ccol[CACHE ? kPersistCache : 1];
   const int tid = threadIdx.x;
   const int dim = pb.dim;
   d2 cur[R];
@@ -429,35 +428,71 @@ __device__ __forceinline__ void persist_state(const PersistProblem& pb, const Pe
       for (int k = 0; k < R; ++k) y[k] += rmul(a1 * regs[k].diag[0] + a2 * regs[k].diag[1], w[k]);
     });
   } else {
-    if constexpr (CACHE) {  // term 1's entries in LDS (published by the first barrier of persist_rows)
-      const d2* v1 = reinterpret_cast<const d2*>(pb.t1.val);
-      const int nnz1 = min(pb.t1.rp[dim], kPersistCache);  // the host checked that they fit
-      for (int k = tid; k < nnz1; k += (int)blockDim.x) {
-        cval[k] = v1[k];
-        ccol[k] = pb.t1.ci[k];
-      }
-    }
     persist_rows<R>(plan, dim, X[0], X[1], red, cur, c, [&](const d2* x, const d2 (&)[R], double a1, double a2, d2 (&y)[R]) {
 #pragma unroll
       for (int k = 0; k < R; ++k) {
         const int s1 = start[k][0], s2 = start[k][1];
-        d2 y1;
-        if constexpr (CACHE) y1 = row_product(s1, s1 + len[k][0], ccol, cval, x);
-        else y1 = row_product(s1, s1 + len[k][0], pb.t1.ci, reinterpret_cast<const d2*>(pb.t1.val), x);
-        const d2 y2 = row_product(s2, s2 + len[k][1], pb.t2.ci, reinterpret_cast<const d2*>(pb.t2.val), x);
-        y[k] = rmul(a1, y1) + rmul(a2, y2);
+        y[k] = rmul(a1, row_product(s1, s1 + len[k][0], pb.t1.ci, reinterpret_cast<const d2*>(pb.t1.val), x)) +
+               rmul(a2, row_product(s2, s2 + len[k][1], pb.t2.ci, reinterpret_cast<const d2*>(pb.t2.val), x));
       }
     });
   }
   persist_finish<R>(out, slot, dim, cur, c);
 }
 
-template <int R, bool CACHE>
+template <int R>
 __global__ __launch_bounds__(kRowThreads) void persist_rows_kernel(PersistArgs a) {
   const int b = blockIdx.x;
   const PersistProblem pb = persist_problem(a, b);
   const PersistSchedule plan{a.exps + (long long)b * a.nexp, a.table, a.nexp, a.early};
-  persist_state<R, CACHE>(pb, plan, a.state[b], a.state[b], &a.slots[b]);
+  persist_state<R>(pb, plan, a.state[b], a.state[b], &a.slots[b]);
+}
+
+// Rows that are not expected to fit (513 to 1,024 of them; fewer are as fast
+// above): read from memory in every iteration by a thread each (773 rows of 38
+// entries 9.4 us per iteration, 11 with two rows to each of 512 threads), with
+// CACHE term 1 from a copy in LDS, one workgroup per CU then (16 entries a row:
+// 5.2 us, 6.5 without).
+template <bool CACHE>
+__global__ __launch_bounds__(kPT) void persist_csr_kernel(PersistArgs a) {
+  __shared__ d2 X[2][kPT + 1];
+  __shared__ double red[2][2][16];
+  __shared__ d2 cval[CACHE ? kPersistCache : 1];
+  __shared__ int ccol[CACHE ? kPersistCache : 1];
+  const int b = blockIdx.x;
+  const int tid = threadIdx.x;
+  const PersistProblem pb = persist_problem(a, b);
+  const PersistSchedule plan{a.exps + (long long)b * a.nexp, a.table, a.nexp, a.early};
+  const int dim = pb.dim;
+  const d2* v1 = reinterpret_cast<const d2*>(pb.t1.val);
+  const d2* v2 = reinterpret_cast<const d2*>(pb.t2.val);
+  d2 cur[1] = {d2{0.0, 0.0}};
+  int s1 = 0, e1 = 0, s2 = 0, e2 = 0;
+  if (tid < dim) {
+    cur[0] = reinterpret_cast<const d2*>(a.state[b])[tid];
+    s1 = pb.t1.rp[tid];
+    e1 = pb.t1.rp[tid + 1];
+    s2 = pb.t2.rp[tid];
+    e2 = pb.t2.rp[tid + 1];
+  }
+  if (tid < 64) red[tid >> 5][tid >> 4 & 1][tid & 15] = 0.0;
+  if constexpr (CACHE) {  // (the host checked that they fit)
+    const int nnz1 = min(pb.t1.rp[dim], kPersistCache);
+    for (int k = tid; k < nnz1; k += kPT) {
+      cval[k] = v1[k];
+      ccol[k] = pb.t1.ci[k];
+    }
+  }
+  __syncthreads();
+  PersistControl c;
+  persist_rows<1>(plan, dim, X[0], X[1], red, cur, c, [&](const d2* x, const d2 (&)[1], double a1, double a2, d2 (&y)[1]) {
+    d2 y1;
+    if constexpr (CACHE) y1 = row_product(s1, e1, ccol, cval, x);
+    else y1 = row_product(s1, e1, pb.t1.ci, v1, x);
+    y[0] = rmul(a1, y1) + rmul(a2, row_product(s2, e2, pb.t2.ci, v2, x));
+  });
+  if (tid < dim) reinterpret_cast<d2*>(a.state[b])[tid] = cur[0];
+  if (tid == 0) persist_record(&a.slots[b], c);
 }
 
 // One step, the same for every state, its parameters in the launch's own
@@ -473,7 +508,7 @@ __global__ __launch_bounds__(kRowThreads) void persist_step_kernel(PersistStep a
   __syncthreads();
   const PersistSchedule schedule{plan.exps, plan.table, a.nexp, a.early};
   const long long at = (long long)blockIdx.x * a.problem.dim;
-  persist_state<R, false>(a.problem, schedule, a.in + at, a.out + at, &a.slots[blockIdx.x]);
+  persist_state<R>(a.problem, schedule, a.in + at, a.out + at, &a.slots[blockIdx.x]);
 }
 
 // Larger dimensions, up to CAP: thread t owns rows t, t + kPT, ... (at most
@@ -586,10 +621,10 @@ __global__ __launch_bounds__(kPT) void persist_propagate_kernel(PersistArgs a) {
 hipError_t launch_persist_propagate(const PersistArgs& a, int nstates, int max_dim, hipStream_t s) {
   const int threads = (max_dim + 63) / 64 * 64;
   if (max_dim <= 0) return hipSuccess;
-  if (max_dim <= kRowThreads && a.cache1) persist_rows_kernel<1, true><<<nstates, threads, 0, s>>>(a);
-  else if (max_dim <= kRowThreads) persist_rows_kernel<1, false><<<nstates, threads, 0, s>>>(a);
-  else if (max_dim <= kPT && a.cache1) persist_rows_kernel<2, true><<<nstates, kRowThreads, 0, s>>>(a);
-  else if (max_dim <= kPT) persist_rows_kernel<2, false><<<nstates, kRowThreads, 0, s>>>(a);
+  if (max_dim <= kRowThreads) persist_rows_kernel<1><<<nstates, threads, 0, s>>>(a);
+  else if (max_dim <= kPT && a.in_regs) persist_rows_kernel<2><<<nstates, kRowThreads, 0, s>>>(a);
+  else if (max_dim <= kPT && a.cache1) persist_csr_kernel<true><<<nstates, kPT, 0, s>>>(a);
+  else if (max_dim <= kPT) persist_csr_kernel<false><<<nstates, kPT, 0, s>>>(a);
   else if (max_dim <= kPersistMaxDim) persist_propagate_kernel<kPersistMaxDim><<<nstates, kPT, 0, s>>>(a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
