@@ -1046,11 +1046,12 @@ int plan_multi(const magnus_hamiltonian* h, const double* acoef, const double* b
   for (int b = 0; b < B; ++b) {
     magnus::weyl_interval(acoef[b], h->H1.lam_min, h->H1.lam_max, bcoef[b], h->H2.lam_min, h->H2.lam_max, 0.0, 0.0,
                           0.0, &lo[b], &hi[b]);
-    ExpPlan t;
-    if (!magnus::plan_exponential(tau, lo[b], hi[b], tol_e, o->max_degree, o->max_substeps, &t))
+    if (b > 0 && lo[b] == lo[b - 1] && hi[b] == hi[b - 1]) continue;  // planned as the state before
+    magnus::LejaPlan t;
+    if (!magnus::plan_substeps(tau, lo[b], hi[b], tol_e, o->max_degree, o->max_substeps, &t))
       return fail(MAGNUS_ENOCONV, "no degree <= %d with <= %d substeps reaches tol %g", o->max_degree,
                   o->max_substeps, tol_e);
-    s = std::max(s, t.lp.s);
+    s = std::max(s, t.s);
   }
   std::vector<ExpPlan> P(B);
   int m = 1;
@@ -1058,11 +1059,14 @@ int plan_multi(const magnus_hamiltonian* h, const double* acoef, const double* b
   for (int b = 0; b < B; ++b) {
     const double coupling =
         frechet ? std::fmax(std::fabs(h->H2.lam_min), std::fabs(h->H2.lam_max)) : 0.0;
-    if (!magnus::plan_exponential_fixed_s(tau, lo[b], hi[b], tol_e, s, o->max_degree, &P[b], coupling))
+    if (b > 0 && lo[b] == lo[b - 1] && hi[b] == hi[b - 1]) P[b] = P[b - 1];
+    else if (!magnus::plan_exponential_fixed_s(tau, lo[b], hi[b], tol_e, s, o->max_degree, &P[b], coupling))
       return fail(MAGNUS_ENOCONV, "no degree <= %d reaches tol %g with %d substeps", o->max_degree, tol_e, s);
     m = std::max(m, P[b].lp.m);
     worst = std::max(worst, P[b].lp.bound);
   }
+  std::vector<double> d0abs(B);
+  for (int b = 0; b < B; ++b) d0abs[b] = std::abs(P[b].d[0]);
   const auto& xi = magnus::leja_points();
   out->B = B;
   out->s = s;
@@ -1083,7 +1087,7 @@ int plan_multi(const magnus_hamiltonian* h, const double* acoef, const double* b
       c.dabs = std::abs(d);
       c.d0re = p.d[0].real();
       c.d0im = p.d[0].imag();
-      c.d0abs = std::abs(p.d[0]);
+      c.d0abs = d0abs[b];
       c.coup = frechet ? p.scale : 0.0;
       table->push_back(c);
     }
@@ -1608,6 +1612,7 @@ int persist_exponential(const magnus_hamiltonian* h, double ca, double cb, doubl
   E->s = P.lp.s;
   E->table_off = (long long)table->size();
   E->tol_sub = tol_e / (2.0 * P.lp.s);
+  const double d0abs = std::abs(P.d[0]);
   for (int i = 1; i <= P.lp.m; ++i) {
     ColParam c{};
     c.a1 = P.scale * ca;
@@ -1618,7 +1623,7 @@ int persist_exponential(const magnus_hamiltonian* h, double ca, double cb, doubl
     c.dabs = std::abs(P.d[i]);
     c.d0re = P.d[0].real();
     c.d0im = P.d[0].imag();
-    c.d0abs = std::abs(P.d[0]);
+    c.d0abs = d0abs;
     table->push_back(c);
   }
   acc->exponentials += 1;

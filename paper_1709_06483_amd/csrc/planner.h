@@ -80,6 +80,9 @@ struct ExpPlan {
 bool plan_exponential(double tau, double lo, double hi, double tol, int max_degree,
                       int max_substeps, ExpPlan* out);
 
+// Only the degree and substep count that plan_exponential chooses.
+bool plan_substeps(double tau, double lo, double hi, double tol, int max_degree, int max_substeps, LejaPlan* out);
+
 // As plan_exponential with the substep count fixed to s (used when several
 // states share one iteration sequence); false if no degree reaches tol.
 // coupling_norm > 0 plans the block exponential of [[H, E], [0, H]] with
