@@ -84,7 +84,7 @@ struct magnus_ctx {
   magnus::CodeTerms coded_terms{};
   const magnus_hamiltonian* coded_h = nullptr;
   bool coded_pairs = false;      // the states of the current call's batch run as interleaved pairs
-  magnus::PairArgs pair_last{};  // the last launch of pairs, for the check of its norms
+  magnus::PairArgs pair_last{};  // every problem's last launch of pairs, for the check of their norms
   bool pair_pending = false;
   double2* split = nullptr;      // shares of a dense group's products (split_entries of them)
   long long split_entries = 0;
@@ -530,7 +530,7 @@ int flush_fused_check(magnus_ctx* ctx, hipStream_t s) {
   return MAGNUS_OK;
 }
 
-// Likewise for the last launch of pairs (at the end of a group of states, and of the call).
+// Likewise for every problem's last launch of pairs (at the end of a group of states, and of the call).
 int flush_pair_check(magnus_ctx* ctx, hipStream_t s) {
   if (!ctx->pair_pending) return MAGNUS_OK;
   ctx->pair_pending = false;
@@ -1145,8 +1145,10 @@ int launch_pairs_exp(magnus_ctx* ctx, const std::vector<PairWork>& R, const std:
     }
     for (int i = 1; i <= max_m; ++i) {
       magnus::PairArgs A{};
+      size_t who[magnus::kMaxPairProblems];
       for (size_t q = 0; q < np; ++q) {
         if (sub >= E[q].s || i > E[q].m) continue;
+        who[A.np] = q;
         magnus::PairProblem& P = A.p[A.np++];
         P.t1 = csr_dev(R[q].h->H1);
         P.t2 = csr_dev(R[q].h->H2);
@@ -1167,7 +1169,9 @@ int launch_pairs_exp(magnus_ctx* ctx, const std::vector<PairWork>& R, const std:
         P.tol = tol_e / (2.0 * E[q].s);
       }
       HIP_TRY(timed(ctx, MAGNUS_KERNEL_CSR_MULTI, s, [&] { return magnus::launch_coded_pairs(frechet, A, s); }));
-      ctx->pair_last = A;
+      // a problem with fewer iterations is not in the last launch: each keeps its own
+      ctx->pair_last.np = (int)np;
+      for (int k = 0; k < A.np; ++k) ctx->pair_last.p[who[k]] = A.p[k];
       ctx->pair_pending = true;
     }
     for (size_t q = 0; q < np; ++q)

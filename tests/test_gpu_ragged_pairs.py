@@ -1,0 +1,52 @@
+"""Ragged batches whose problems run as pairs of states on coded CSR terms:
+problems of unequal degrees, batches of more than one group of states, and what
+is reported of non-finite states.  MAGNUS_CODED=2 codes every call,
+MAGNUS_PERSIST=0 keeps the small problems out of the one-workgroup kernel."""
+import numpy as np
+import pytest
+
+from paper_1709_06483_amd import inputs
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():  # pragma: no cover - collected only where a GPU exists
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_1709_06483_amd import binding as B  # noqa: E402
+from test_gpu_coded import csr, rel, terms  # noqa: E402
+
+
+@pytest.fixture(autouse=True)
+def coded(monkeypatch):
+    monkeypatch.setenv("MAGNUS_CODED", "2")
+    monkeypatch.setenv("MAGNUS_PERSIST", "0")
+
+
+def problem(ctx, N, batch, scale=1.0, steps=1, seed=0):
+    """Chain-like real terms of N rows times `scale`, with `batch` states and a field per state."""
+    A1, A2 = terms("real", N)
+    ham = B.magnus_spectral_bounds(ctx, B.DeviceHamiltonian.from_csr(csr(scale * A1), csr(scale * A2)))
+    f = np.stack([np.full((steps, 2), 0.3 + 0.4 * b / batch) for b in range(batch)])
+    return ham, torch.from_numpy(inputs.random_states(N, seed=N + seed, batch=batch)).cuda(), f
+
+
+@pytest.mark.parametrize("order", [(0, 1), (1, 0)])
+def test_a_problem_that_ends_before_the_others_is_checked(order):
+    """Two problems, one of a single iteration an exponential and one of more: the last launch holds
+    only the second, and no launch of the first is followed by one that looks at its norms."""
+    batch, opts, tau = 4, B.leja_opts(1e-6), 0.05
+    ctx = B.Context(max_dim=4000, max_batch=batch)
+    both = [problem(ctx, 900, batch, scale=1e-9), problem(ctx, 2000, batch)]
+    degree = []
+    for p in both:
+        st = B.magnus_propagate_ragged(ctx, [p], B.CF4, tau, opts=opts, stats=True)
+        assert st["planned_iters"] % st["exponentials"] == 0 and st["substeps"] == st["exponentials"]
+        degree.append(st["planned_iters"] // st["exponentials"])
+    assert degree[0] == 1 < degree[1]
+    B.magnus_propagate_ragged(ctx, [both[k] for k in order], B.CF4, tau, opts=opts, stats=True)
+    both[0][1][3, 899] = float("nan")
+    with pytest.raises(B.MagnusError) as e:
+        B.magnus_propagate_ragged(ctx, [both[k] for k in order], B.CF4, tau, opts=opts, stats=True)
+    assert e.value.code == B.ENAN
+    ctx.close()
