@@ -1371,13 +1371,13 @@ int multi_cf_steps(magnus_ctx* ctx, const magnus_hamiltonian* h, const magnus::S
 // ---------------------------------------------------------------------------
 // Ragged batches: the large problems of equal group size B advance together,
 // one launch per Leja iteration serving every problem (and one decision
-// launch for all their columns), each problem with its own terms, degrees,
+// launch for all their columns), each group with its own terms, degrees,
 // workspace slice, control slots and partial sums.
 // ---------------------------------------------------------------------------
 struct RagProblem {
   const magnus_problem* P;
   magnus::CodedDev C;  // its coded terms, when the problems run as pairs
-  int c0;         // first of its states in the problem (a group of B states)
+  int c0, B;      // its states in the problem: a group of B from the c0-th on
   size_t voff;    // offset of its slice inside every workspace vector
   int slot0;      // its first control slot
   size_t poff;    // offset of its partial sums
@@ -1442,13 +1442,18 @@ int launch_ragged_exp(magnus_ctx* ctx, const std::vector<RagProblem>& R, const s
 
 // Code the terms of a ragged batch's large problems and lay out their slices of
 // the workspace, when they can run together as pairs: CSR terms found to fit the
-// form, one even batch, everything within the context's buffers.  *out stays
-// empty otherwise.
+// form, one even batch, everything within the context's buffers.  A problem's
+// states go in groups of at most 32, as in propagate: a group shares its largest
+// substep count, and one step's parameters of all groups fit the table (8 groups,
+// 3 exponentials of 32 states and degree 64).  *out stays empty otherwise.
+static_assert((size_t)magnus::kMaxPairProblems * magnus::kMaxCols * 3 * MAGNUS_MAX_DEGREE <= kTableCap,
+              "a step's parameters");
 int code_ragged(magnus_ctx* ctx, const magnus_problem* probs, const std::vector<int>& big, const magnus::Scheme& S,
                 int64_t nsteps, int small_states, std::vector<RagProblem>* out, hipStream_t s) {
   const int batch = probs[big[0]].batch;
+  const int groups = (batch + magnus::kMaxCols - 1) / magnus::kMaxCols;
   if (!ctx->fuse || ctx->csr_variant || batch < 2 || batch % 2 || batch > ctx->max_batch ||
-      big.size() > (size_t)magnus::kMaxPairProblems)
+      big.size() * (size_t)groups > (size_t)magnus::kMaxPairProblems)
     return MAGNUS_OK;
   const int npairs = batch / 2;
   // several rows of slices to a wave where problems of several sizes share a launch
@@ -1470,20 +1475,24 @@ int code_ragged(magnus_ctx* ctx, const magnus_problem* probs, const std::vector<
     C.dict += blocks * (magnus::kCodeMax + 1);
     C.block += blocks;
     C.diag += rows;
-    R.push_back(RagProblem{&P, C, 0, voff, slot0, poff});
     const size_t grid = (size_t)magnus::code_grid(dim, C.rows);
+    for (int c0 = 0; c0 < batch; c0 += magnus::kMaxCols) {
+      const int B = std::min(magnus::kMaxCols, batch - c0);
+      R.push_back(RagProblem{&P, C, c0, B, voff, slot0, poff});
+      voff += (size_t)dim * B;
+      poff += 2 * (size_t)B * grid;
+      slot0 += B;
+    }
     slices += ((size_t)dim + 63) / 64 * 4;
     blocks += grid;
     rows += (size_t)dim;
-    voff += (size_t)dim * batch;
-    poff += 4 * (size_t)npairs * grid;
-    slot0 += batch;
   }
   if (slices > ctx->coded_slices || blocks > ctx->coded_blocks || rows > (size_t)ctx->max_dim ||
       voff > (size_t)ctx->max_dim * (size_t)ctx->max_batch || pair_partials_at(ctx) + 2 * poff > ctx->npartials ||
       slot0 > ctx->nslots)
     return MAGNUS_OK;
-  for (RagProblem& q : R) {
+  for (const RagProblem& q : R) {
+    if (q.c0 > 0) continue;  // a problem's groups share its coded terms
     const magnus::CodeTerms T{2, {csr_dev(q.P->h.H1), csr_dev(q.P->h.H2)}};
     HIP_TRY(magnus::launch_code_build(T, (int)q.P->h.H1.dim, q.C, nullptr, s));
   }
@@ -1491,22 +1500,22 @@ int code_ragged(magnus_ctx* ctx, const magnus_problem* probs, const std::vector<
   return MAGNUS_OK;
 }
 
-// Product-of-exponentials steps of the ragged batch's large problems (all of
-// batch B, B a group size), packed interleaved into their workspace slices.
-int ragged_joint_steps(magnus_ctx* ctx, std::vector<RagProblem>& R, const magnus::Scheme& S, int B, double tau,
+// Product-of-exponentials steps of the ragged batch's large problems, packed
+// into their workspace slices (interleaved groups, all of the same size; or pairs).
+int ragged_joint_steps(magnus_ctx* ctx, std::vector<RagProblem>& R, const magnus::Scheme& S, double tau,
                        int64_t nsteps, double tol_e, const magnus_leja_opts* o, Acc* acc, hipStream_t s) {
   const bool pairs = R[0].C.codes != nullptr;
   std::vector<PairWork> W;
   for (const RagProblem& q : R) {
     const int dim = (int)q.P->h.H1.dim;
     if (pairs) {
-      HIP_TRY(magnus::launch_pack_pairs(q.psi(), q.v(ctx, kY), dim, B / 2, s));
-      W.push_back(PairWork{&q.P->h, q.C, B / 2, q.v(ctx, kA), q.v(ctx, kB), q.v(ctx, kS0), q.v(ctx, kS1), q.slot0, q.poff});
+      HIP_TRY(magnus::launch_pack_pairs(q.psi(), q.v(ctx, kY), dim, q.B / 2, s));
+      W.push_back(PairWork{&q.P->h, q.C, q.B / 2, q.v(ctx, kA), q.v(ctx, kB), q.v(ctx, kS0), q.v(ctx, kS1), q.slot0, q.poff});
     } else {
-      HIP_TRY(magnus::launch_pack(q.psi(), q.v(ctx, kY), dim, B, s));
+      HIP_TRY(magnus::launch_pack(q.psi(), q.v(ctx, kY), dim, q.B, s));
     }
   }
-  std::vector<double> av(B), bv(B), fv(S.q);
+  std::vector<double> av(magnus::kMaxCols), bv(magnus::kMaxCols), fv(S.q);
   int64_t n = 0;
   while (n < nsteps) {
     std::vector<ColParam> table;
@@ -1518,6 +1527,7 @@ int ragged_joint_steps(magnus_ctx* ctx, std::vector<RagProblem>& R, const magnus
       std::vector<std::vector<MultiExp>> st(S.nexp, std::vector<MultiExp>(R.size()));
       for (size_t q = 0; q < R.size(); ++q) {
         const magnus_problem& P = *R[q].P;
+        const int B = R[q].B;
         const double2* src = R[q].v(ctx, kY);
         double2* mids[2] = {R[q].v(ctx, kS2), R[q].v(ctx, kU)};
         for (int e = 0; e < S.nexp; ++e) {
@@ -1547,15 +1557,15 @@ int ragged_joint_steps(magnus_ctx* ctx, std::vector<RagProblem>& R, const magnus
     if (rc) return rc;
     for (const auto& E : steps) {
       rc = pairs ? launch_pairs_exp(ctx, W, E, tol_e, o->early_termination, false, s)
-                 : launch_ragged_exp(ctx, R, E, B, tol_e, o->early_termination, s);
+                 : launch_ragged_exp(ctx, R, E, R[0].B, tol_e, o->early_termination, s);
       if (rc) return rc;
     }
     n = k;
   }
   for (const RagProblem& q : R) {
     const int dim = (int)q.P->h.H1.dim;
-    if (pairs) HIP_TRY(magnus::launch_unpack_pairs(q.v(ctx, kY), q.psi(), dim, B / 2, s));
-    else HIP_TRY(magnus::launch_unpack(q.v(ctx, kY), q.psi(), dim, B, s));
+    if (pairs) HIP_TRY(magnus::launch_unpack_pairs(q.v(ctx, kY), q.psi(), dim, q.B / 2, s));
+    else HIP_TRY(magnus::launch_unpack(q.v(ctx, kY), q.psi(), dim, q.B, s));
   }
   return flush_pair_check(ctx, s);
 }
@@ -3067,12 +3077,12 @@ int magnus_propagate_ragged(magnus_ctx* ctx, const magnus_problem* probs, int32_
             vtot <= (size_t)ctx->max_dim * (size_t)ctx->max_batch && ptot <= ctx->npartials &&
             sst.size() + groups * (size_t)JB <= (size_t)ctx->nslots;
   }
-  // on coded terms the problems run as pairs of states, whole batches at once
+  // on coded terms the problems run as pairs of states
   std::vector<RagProblem> coded;
   if (ctx->ragged_joint && !S.commutator && !big.empty() && nsteps > 0 && tau != 0.0)
     if ((rc = code_ragged(ctx, probs, big, S, nsteps, (int)sst.size(), &coded, s))) return rc;
   if (!coded.empty()) {
-    if ((rc = ragged_joint_steps(ctx, coded, S, probs[big[0]].batch, tau, nsteps, tol_e, opts, &acc, s))) return rc;
+    if ((rc = ragged_joint_steps(ctx, coded, S, tau, nsteps, tol_e, opts, &acc, s))) return rc;
     big.clear();
   } else if (joint && nsteps > 0) {
     std::vector<RagProblem> R;
@@ -3081,13 +3091,13 @@ int magnus_propagate_ragged(magnus_ctx* ctx, const magnus_problem* probs, int32_
     for (int i : big) {
       const magnus_problem& P = probs[i];
       for (int c0 = 0; c0 < P.batch; c0 += JB) {
-        R.push_back(RagProblem{&P, {}, c0, voff, slot0, poff});
+        R.push_back(RagProblem{&P, {}, c0, JB, voff, slot0, poff});
         voff += (size_t)P.h.H1.dim * JB;
         poff += (size_t)magnus::ragged_grid((int)P.h.H1.dim, JB) * JB * 2;
         slot0 += JB;
       }
     }
-    if ((rc = ragged_joint_steps(ctx, R, S, JB, tau, nsteps, tol_e, opts, &acc, s))) return rc;
+    if ((rc = ragged_joint_steps(ctx, R, S, tau, nsteps, tol_e, opts, &acc, s))) return rc;
     big.clear();
   }
   // the large problems first: each is one batched propagation (which resets the control slots)

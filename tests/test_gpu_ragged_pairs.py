@@ -50,3 +50,47 @@ def test_a_problem_that_ends_before_the_others_is_checked(order):
         B.magnus_propagate_ragged(ctx, [both[k] for k in order], B.CF4, tau, opts=opts, stats=True)
     assert e.value.code == B.ENAN
     ctx.close()
+
+
+def both_ways(monkeypatch, run):
+    out = []
+    for mode in ("2", "0"):
+        monkeypatch.setenv("MAGNUS_CODED", mode)
+        out.append(run())
+    return out
+
+
+# one and two problems of one group, of groups of 32 and 8 states, of 32, 32 and 2, and of as many groups as a
+# launch takes; tolerance: each side within the bound of its exponentials (2 steps of 2, 20 times the tolerance each)
+@pytest.mark.parametrize("sizes,batch", [([700], 40), ([700, 2001], 40), ([300, 1001], 66), ([200, 333], 128)])
+def test_batches_of_several_groups_match_csr_kernels(sizes, batch, monkeypatch):
+    tol = 1e-12
+
+    def run():
+        ctx = B.Context(max_dim=sum(sizes), max_batch=batch)
+        probs = [problem(ctx, N, batch, steps=2) for N in sizes]
+        st = B.magnus_propagate_ragged(ctx, probs, B.CF4, 0.3, opts=B.leja_opts(tol), stats=True)
+        ctx.close()
+        return [p[1].cpu().numpy() for p in probs], st
+
+    (a, sa), (b, sb) = both_ways(monkeypatch, run)
+    assert sa["exponentials"] == sb["exponentials"]
+    for x, y in zip(a, b):
+        assert np.linalg.norm(x - y, axis=1).max() <= 2 * 4 * 20 * tol
+
+
+def test_a_batch_whose_parameters_exceed_the_table_runs(monkeypatch):
+    """5500 states, two exponentials of degree 26: more records than the device table holds when they are
+    planned as one group."""
+    N, batch, tol = 48, 5500, 1e-12
+
+    def run():
+        ctx = B.Context(max_dim=N, max_batch=batch)
+        p = problem(ctx, N, batch)
+        st = B.magnus_propagate_ragged(ctx, [p], B.CF4, 8.0, opts=B.leja_opts(tol), stats=True)
+        ctx.close()
+        return p[1].cpu().numpy(), st
+
+    (a, sa), (b, _) = both_ways(monkeypatch, run)
+    assert sa["max_degree_used"] * 2 * batch > 1 << 18
+    assert np.linalg.norm(a - b, axis=1).max() <= 2 * 2 * 20 * tol
