@@ -383,7 +383,8 @@ typedef struct {
  * couplings, all of one even batch of at most max_batch, run as pairs of states
  * on coded terms instead (propagate), one launch per iteration for all of them,
  * when their groups of up to 32 states are at most 8 and fit the context's
- * buffers.  Tolerances as in propagate (tol_mode 1:
+ * buffers; with the host wait and report at its end where the groups above
+ * would not have advanced together.  Tolerances as in propagate (tol_mode 1:
  * budget over the exponentials of each state).  Errors as propagate. */
 int magnus_propagate_ragged(magnus_ctx* ctx, const magnus_problem* probs, int32_t nprob, int32_t method,
                             double tau, int64_t nsteps, const magnus_leja_opts* opts, magnus_stats* stats,

@@ -3083,6 +3083,12 @@ int magnus_propagate_ragged(magnus_ctx* ctx, const magnus_problem* probs, int32_
     if ((rc = code_ragged(ctx, probs, big, S, nsteps, (int)sst.size(), &coded, s))) return rc;
   if (!coded.empty()) {
     if ((rc = ragged_joint_steps(ctx, coded, S, tau, nsteps, tol_e, opts, &acc, s))) return rc;
+    if (!joint) {  // batched propagations otherwise, each with a host wait that reports a non-finite norm
+      long long it = 0;
+      int st = 0;
+      if ((rc = read_slots(ctx, s, &it, &st))) return rc;
+      if (st & 1) return fail(MAGNUS_ENAN, "non-finite vector norm met during the call");
+    }
     big.clear();
   } else if (joint && nsteps > 0) {
     std::vector<RagProblem> R;

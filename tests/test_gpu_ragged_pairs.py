@@ -94,3 +94,21 @@ def test_a_batch_whose_parameters_exceed_the_table_runs(monkeypatch):
     (a, sa), (b, _) = both_ways(monkeypatch, run)
     assert sa["max_degree_used"] * 2 * batch > 1 << 18
     assert np.linalg.norm(a - b, axis=1).max() <= 2 * 2 * 20 * tol
+
+
+# a single problem, and four whose groups of two states were too many for one launch of the CSR kernels: without
+# statistics too the call waits and reports, as batched propagations one after another do
+@pytest.mark.parametrize("sizes,batch", [([900], 4), ([300, 700, 200, 500], 6)])
+def test_problems_that_do_not_run_jointly_report_at_once(sizes, batch, monkeypatch):
+    def run():
+        ctx = B.Context(max_dim=sum(sizes) + 300, max_batch=batch)
+        probs = [problem(ctx, N, batch) for N in sizes]
+        probs[-1][1][1, 7] = float("inf")
+        try:
+            with pytest.raises(B.MagnusError) as e:
+                B.magnus_propagate_ragged(ctx, probs, B.CF4, 0.1)
+            return e.value.code
+        finally:
+            ctx.close()
+
+    assert both_ways(monkeypatch, run) == [B.ENAN, B.ENAN]
