@@ -1207,6 +1207,7 @@ int launch_multi(magnus_ctx* ctx, const magnus_hamiltonian* h, const MultiExp& E
     const PairWork W{h, ctx->coded, E.B / 2, ctx->vec(kA), ctx->vec(kB), ctx->vec(kS0), ctx->vec(kS1), 0, 0};
     return launch_pairs_exp(ctx, {W}, {E}, tol_e, early, false, s);
   }
+  if (int rc = flush_pair_check(ctx, s)) return rc;
   const int dim = (int)h->H1.dim;
   const int B = E.B;
   const size_t n = (size_t)dim * B;
@@ -3230,7 +3231,7 @@ int magnus_propagate_adjoint(magnus_ctx* ctx, const magnus_hamiltonian* h, doubl
   // The block (Frechet) exponentials of a step, of phi_n with gamma_n and of
   // psi_n with beta_n, do not depend on lambda: on coded terms they run together,
   // as two pairs (each work buffer two vectors of the context, back to back).
-  const bool pairs = ctx->coded_h == h;
+  bool pairs = ctx->coded_h == h;
   const double half[4] = {0.5, 0.5, 0.5, 0.5};
   for (int64_t seg = nseg - 1; seg >= 0; --seg) {
     const int64_t n0 = seg * k, n1 = std::min(n0 + k, nsteps);
@@ -3244,14 +3245,25 @@ int magnus_propagate_adjoint(magnus_ctx* ctx, const magnus_hamiltonian* h, doubl
     // the segment's block exponentials, planned and uploaded together
     std::vector<ColParam> table;
     std::vector<MultiExp> ea(n1 - n0), eb(n1 - n0);
-    for (int64_t n = n0; n < n1; ++n) {
-      const double ga = gamma_of(n), be = beta_of(n), both[4] = {ga, ga, be, be};
-      rc = plan_multi(h, half, both, pairs ? 4 : 2, tau, tol_e, opts, 1, &table, &ea[n - n0], &acc);
-      if (rc) return rc;
-      if (pairs) continue;
-      rc = plan_multi(h, half, both + 2, 2, tau, tol_e, opts, 1, &table, &eb[n - n0], &acc);
-      if (rc) return rc;
+    auto plan_segment = [&](Acc* a) {
+      table.clear();
+      for (int64_t n = n0; n < n1; ++n) {
+        const double ga = gamma_of(n), be = beta_of(n), both[4] = {ga, ga, be, be};
+        int rc1 = plan_multi(h, half, both, pairs ? 4 : 2, tau, tol_e, opts, 1, &table, &ea[n - n0], a);
+        if (!rc1 && !pairs) rc1 = plan_multi(h, half, both + 2, 2, tau, tol_e, opts, 1, &table, &eb[n - n0], a);
+        if (rc1) return rc1;
+      }
+      return (int)MAGNUS_OK;
+    };
+    Acc planned = acc;
+    if ((rc = plan_segment(&planned))) return rc;
+    if (pairs && table.size() > kTableCap) {
+      // two pairs share the larger degree: one after the other the segment may still fit
+      pairs = false;
+      planned = acc;
+      if ((rc = plan_segment(&planned))) return rc;
     }
+    acc = planned;
     if ((rc = upload_table(ctx, table, s))) return rc;
     for (int64_t n = n1 - 1; n >= n0; --n) {
       const double2 *psi = seg_psi + (n - n0) * dim, *phi = seg_phi + (n - n0) * dim;
