@@ -1604,13 +1604,20 @@ bool rows_in_registers(const magnus_ctx* ctx, const magnus_hamiltonian* h) {
          ctx->codable.count(pair_key(h));
 }
 
-// One state whose matrix a workgroup would read from memory in every iteration
-// takes the grid path from 12,000 entries on (random terms, us for the same
-// iterations in one workgroup / on the grid: 10,800 entries 330 / 383, 12,000
-// 424 / 423, 13,900 458 / 385).
+// Whether the kernels for states of up to 1,024 rows can keep term 1 in LDS.
+bool term1_in_lds(const magnus_ctx* ctx, const magnus_hamiltonian* h) {
+  return ctx->persist_cache && h->H1.dim <= magnus::kPersistStepDim && h->H1.nnz <= magnus::kPersistCache;
+}
+
+// One state of which a workgroup would read more than 12,000 entries from memory
+// in every iteration takes the grid path (us per iteration in one workgroup / on
+// the grid; rows of equal length, 1,024 of them, term 1 in LDS: 10,240 entries
+// 4.5 / 5.3, 14,336 5.7 / 5.5; 700 rows read whole: 14,000 5.2 / 5.4; random rows,
+// whose longest a workgroup waits for, meet at 8,000 and 10,000 entries).
 bool small_ok(magnus_ctx* ctx, const magnus_hamiltonian* h, int64_t nstates) {
   if (!small_candidate(h) || h->H1.dim > small_cap(ctx, nstates)) return false;
-  return nstates > 1 || ctx->persist >= 2 || rows_in_registers(ctx, h) || h->H1.nnz + h->H2.nnz <= 12000;
+  if (nstates > 1 || ctx->persist >= 2 || rows_in_registers(ctx, h)) return true;
+  return h->H2.nnz + (term1_in_lds(ctx, h) ? 0 : h->H1.nnz) <= 12000;
 }
 
 // exp(-i tau (a H1 + b H2)) for the one-workgroup kernels: its header, and its iterations appended to the table.
@@ -1714,10 +1721,10 @@ int persist_segment(magnus_ctx* ctx, const std::vector<const magnus_hamiltonian*
   a.slots = ctx->slots;
   a.early = o->early_termination;
   // term 1 in LDS: one workgroup per CU then, so only while the states fit the chip
-  a.cache1 = ctx->persist_cache && maxdim <= 1024 && nst <= 256;
+  a.cache1 = nst <= 256;
   a.in_regs = 1;
   for (const magnus_hamiltonian* h : hs) {
-    a.cache1 = a.cache1 && h->H1.nnz <= magnus::kPersistCache;
+    a.cache1 = a.cache1 && term1_in_lds(ctx, h);
     a.in_regs = a.in_regs && rows_in_registers(ctx, h);
   }
   HIP_TRY(timed(ctx, MAGNUS_KERNEL_PERSIST, s, [&] { return magnus::launch_persist_propagate(a, nst, (int)maxdim, s); }));

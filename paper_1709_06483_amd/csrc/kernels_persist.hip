@@ -376,17 +376,30 @@ __device__ __forceinline__ void persist_finish(double2* state, Slot* S, int dim,
   if (tid == 0) persist_record(S, c);
 }
 
+// Term 1 into LDS (the host checked that its entries fit; a barrier follows).
+__device__ __forceinline__ void cache_term1(const PersistProblem& pb, d2* val, int* col) {
+  const int n = min(pb.t1.rp[pb.dim], kPersistCache);
+  for (int k = threadIdx.x; k < n; k += (int)blockDim.x) {
+    val[k] = reinterpret_cast<const d2*>(pb.t1.val)[k];
+    col[k] = pb.t1.ci[k];
+  }
+}
+
 // Dimensions up to 1,024: R rows per thread.  Rows whose entries take at most
 // kRegGroups groups of four (those of one wave's longest rows counted), the
 // off-diagonal ones of a row and term all real or all imaginary, are read into
 // registers once, so that an iteration touches only LDS, where it gathers w; if
 // one row of the state does not fit, all are read from memory in every
-// iteration.
-template <int R>
+// iteration, with CACHE term 1 from a copy in LDS (one workgroup per CU then;
+// complex values, us per iteration with / without: 400 rows of 14 + 8 entries
+// 3.5 / 4.4, 512 rows of 10 + 20 4.5 / 5.7 on the grid).
+template <int R, bool CACHE>
 __device__ __forceinline__ void persist_state(const PersistProblem& pb, const PersistSchedule& plan, const double2* in,
                                               double2* out, Slot* slot) {
   __shared__ d2 X[2][kPT + 1];
   __shared__ double red[2][2][16];
+  __shared__ d2 cval[CACHE ? kPersistCache : 1];
+  __shared__ int ccol[CACHE ? kPersistCache : 1];
   const int tid = threadIdx.x;
   const int dim = pb.dim;
   d2 cur[R];
@@ -428,29 +441,32 @@ __device__ __forceinline__ void persist_state(const PersistProblem& pb, const Pe
       for (int k = 0; k < R; ++k) y[k] += rmul(a1 * regs[k].diag[0] + a2 * regs[k].diag[1], w[k]);
     });
   } else {
+    if constexpr (CACHE) cache_term1(pb, cval, ccol);
     persist_rows<R>(plan, dim, X[0], X[1], red, cur, c, [&](const d2* x, const d2 (&)[R], double a1, double a2, d2 (&y)[R]) {
 #pragma unroll
       for (int k = 0; k < R; ++k) {
         const int s1 = start[k][0], s2 = start[k][1];
-        y[k] = rmul(a1, row_product(s1, s1 + len[k][0], pb.t1.ci, reinterpret_cast<const d2*>(pb.t1.val), x)) +
-               rmul(a2, row_product(s2, s2 + len[k][1], pb.t2.ci, reinterpret_cast<const d2*>(pb.t2.val), x));
+        d2 y1;
+        if constexpr (CACHE) y1 = row_product(s1, s1 + len[k][0], ccol, cval, x);
+        else y1 = row_product(s1, s1 + len[k][0], pb.t1.ci, reinterpret_cast<const d2*>(pb.t1.val), x);
+        y[k] = rmul(a1, y1) + rmul(a2, row_product(s2, s2 + len[k][1], pb.t2.ci, reinterpret_cast<const d2*>(pb.t2.val), x));
       }
     });
   }
   persist_finish<R>(out, slot, dim, cur, c);
 }
 
-template <int R>
+template <int R, bool CACHE>
 __global__ __launch_bounds__(kRowThreads) void persist_rows_kernel(PersistArgs a) {
   const int b = blockIdx.x;
   const PersistProblem pb = persist_problem(a, b);
   const PersistSchedule plan{a.exps + (long long)b * a.nexp, a.table, a.nexp, a.early};
-  persist_state<R>(pb, plan, a.state[b], a.state[b], &a.slots[b]);
+  persist_state<R, CACHE>(pb, plan, a.state[b], a.state[b], &a.slots[b]);
 }
 
-// Rows that are not expected to fit (513 to 1,024 of them; fewer are as fast
-// above): read from memory in every iteration by a thread each (773 rows of 38
-// entries 9.4 us per iteration, 11 with two rows to each of 512 threads), with
+// Rows that are not expected to fit (513 to 1,024 of them): read from memory in
+// every iteration by a thread each (773 rows of 38 entries 9.4 us per iteration,
+// 11 with two rows to each of 512 threads), with
 // CACHE term 1 from a copy in LDS, one workgroup per CU then (16 entries a row:
 // 5.2 us, 6.5 without).
 template <bool CACHE>
@@ -476,13 +492,7 @@ __global__ __launch_bounds__(kPT) void persist_csr_kernel(PersistArgs a) {
     e2 = pb.t2.rp[tid + 1];
   }
   if (tid < 64) red[tid >> 5][tid >> 4 & 1][tid & 15] = 0.0;
-  if constexpr (CACHE) {  // (the host checked that they fit)
-    const int nnz1 = min(pb.t1.rp[dim], kPersistCache);
-    for (int k = tid; k < nnz1; k += kPT) {
-      cval[k] = v1[k];
-      ccol[k] = pb.t1.ci[k];
-    }
-  }
+  if constexpr (CACHE) cache_term1(pb, cval, ccol);
   __syncthreads();
   PersistControl c;
   persist_rows<1>(plan, dim, X[0], X[1], red, cur, c, [&](const d2* x, const d2 (&)[1], double a1, double a2, d2 (&y)[1]) {
@@ -508,7 +518,7 @@ __global__ __launch_bounds__(kRowThreads) void persist_step_kernel(PersistStep a
   __syncthreads();
   const PersistSchedule schedule{plan.exps, plan.table, a.nexp, a.early};
   const long long at = (long long)blockIdx.x * a.problem.dim;
-  persist_state<R>(a.problem, schedule, a.in + at, a.out + at, &a.slots[blockIdx.x]);
+  persist_state<R, false>(a.problem, schedule, a.in + at, a.out + at, &a.slots[blockIdx.x]);
 }
 
 // Larger dimensions, up to CAP: thread t owns rows t, t + kPT, ... (at most
@@ -621,8 +631,9 @@ __global__ __launch_bounds__(kPT) void persist_propagate_kernel(PersistArgs a) {
 hipError_t launch_persist_propagate(const PersistArgs& a, int nstates, int max_dim, hipStream_t s) {
   const int threads = (max_dim + 63) / 64 * 64;
   if (max_dim <= 0) return hipSuccess;
-  if (max_dim <= kRowThreads) persist_rows_kernel<1><<<nstates, threads, 0, s>>>(a);
-  else if (max_dim <= kPT && a.in_regs) persist_rows_kernel<2><<<nstates, kRowThreads, 0, s>>>(a);
+  if (max_dim <= kRowThreads && a.cache1 && !a.in_regs) persist_rows_kernel<1, true><<<nstates, threads, 0, s>>>(a);
+  else if (max_dim <= kRowThreads) persist_rows_kernel<1, false><<<nstates, threads, 0, s>>>(a);
+  else if (max_dim <= kPT && a.in_regs) persist_rows_kernel<2, false><<<nstates, kRowThreads, 0, s>>>(a);
   else if (max_dim <= kPT && a.cache1) persist_csr_kernel<true><<<nstates, kPT, 0, s>>>(a);
   else if (max_dim <= kPT) persist_csr_kernel<false><<<nstates, kPT, 0, s>>>(a);
   else if (max_dim <= kPersistMaxDim) persist_propagate_kernel<kPersistMaxDim><<<nstates, kPT, 0, s>>>(a);
