@@ -441,26 +441,28 @@ int variant_rows(int code, int64_t dim, bool two_pass = false) {
     case 5: return magnus::kWaveTile + 8;
     case 6: return magnus::kWaveTile + 16;
     case 7: return magnus::kStreamTile;
-    // Measured, us per iteration with each mapping (the stop test is made by the
-    // iteration on grids of at most csr2_fuse_grid workgroups, else by a decide
-    // kernel after it), random terms with 6 / 24 / 38 entries a row where no
-    // other are named.  Eight lanes per row (direct) against a row per lane:
-    // 20,000 rows 6.1 / 8.0 / 10.2 against 6.9 / 8.2 / 10.5, 50,021 rows
-    // 11.1 / 15.7 / 22.2 against 11.7 / 17.2 / 24.8; chains of 13 and 14 sites
-    // 5.2 / 5.9 against 6.3 / 6.8.  In between the rows fill one round of
-    // workgroups of 64 rows: 33,000 rows 8.6 / 10.6 / 14.6 against
-    // 7.3 / 10.1 / 15.3, n = 15 7.7 against 7.6.  From 2^16 rows on the
-    // wave tiles of 16 rows: 100,003 rows 17.1 / 28.6 / 37.6 (direct) against
-    // 19.4 / 30.3 / 41.3; but two passes per iteration (a commutator applied to
-    // vectors) on spin models of 2^16 rows 23.9 against 22.5.  Streamed tiles
-    // from 2^17 rows on: 160,001 rows 26.2 / 43.9 / 58.9 (direct) against
-    // 23.7 / 38.3 / 59.5.
+    // Measured, us per iteration with the stop test (made by the iteration on
+    // grids of at most csr2_fuse_grid workgroups, else by a decide kernel after
+    // it), random terms.  Eight lanes per row (direct) against a row per lane in
+    // blocks of 32 or 64 rows, 6 / 24 / 38 entries a row: 20,000 rows
+    // 6.1 / 8.0 / 10.2 against 6.9 / 8.2 / 10.5; chains of 13 and 14 sites
+    // 5.2 / 5.9 against 6.3 / 6.8.  From 28,672 to 49,152 rows the blocks of 64
+    // rows fill the chip in one round, three to a CU: 33,000 rows 8.6 / 10.6 / 14.6
+    // (direct) against 7.3 / 10.1 / 15.3, 49,152 rows 10.4 / 14.5 / 20.9 against
+    // 8.5 / 12.9 / 18.3.  Past them direct again: 50,021 rows 11.1 / 15.7 / 22.2
+    // against 11.7 / 17.2 / 24.8, 65,536 rows 12.0 / 18.0 / 24.9 against
+    // 13.0 / 20.3 / 26.9 with wave tiles of 16 rows, but two passes per iteration
+    // (a commutator applied to vectors) on spin models 23.9 against 22.5.  Past
+    // 65,536 rows the wave tiles: 70,000 rows 14.3 / 21.9 / 30.3 (direct) against
+    // 14.1 / 21.4 / 28.1, 90,000 16.4 / 24.6 / 35.3 against 14.8 / 24.6 / 33.2,
+    // 131,071 22.1 / 34.2 / 49.0 against 19.2 / 34.9 / 46.5.  Streamed tiles from
+    // 2^17 rows on (at 131,071 rows 19.5 / 27.9 / 43.5).
     default:
-      return dim >= 131072  ? magnus::kStreamTile
-             : dim >= 65536 ? (two_pass ? magnus::kWaveTile + 16 : magnus::kRowsDirect + 64)
-             : dim >= 49152 ? magnus::kRowsDirect + 32
-             : dim >= 28672 ? -64
-                            : magnus::kRowsDirect + 32;
+      return dim >= 131072                        ? magnus::kStreamTile
+             : dim >= (two_pass ? 65536 : 65537) ? magnus::kWaveTile + 16
+             : dim > 49152                        ? magnus::kRowsDirect + 32
+             : dim >= 28672                       ? -64
+                                                  : magnus::kRowsDirect + 32;
   }
 }
 

@@ -1,0 +1,94 @@
+"""The library's host code on the CPU, against a stand-in for the HIP runtime
+(hip_stub.cpp: host memory for device memory, kernels logged and not run): which
+kernels a call launches, what it allocates, and what it does when memory is
+short.  Each test runs in a process of its own, so that the stand-in's symbols
+come before the real runtime's."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+PRELUDE = """
+import ctypes as C, sys
+stub = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+stub.stub_live.restype = C.c_size_t
+stub.stub_limit.argtypes = [C.c_size_t]
+stub.stub_log.restype = C.c_char_p
+stub.stub_cost.argtypes = [C.c_char_p, C.c_double]
+stub.stub_watch.argtypes = [C.c_char_p, C.c_int]
+import numpy as np
+from paper_1709_06483_amd import binding as B
+L = B.lib()
+keep = []
+
+def context(max_dim, max_batch=1):
+    h = C.c_void_p()
+    B._check(L.magnus_create(C.byref(h), max_dim, max_batch, 0))
+    return h
+
+def term(N, per=1, radius=1.0):
+    # `per` entries in every row, all of column 0 (the values are zeros)
+    rp = (np.arange(N + 1) * per).astype(np.int32); ci = np.zeros(max(N * per, 1), np.int32); va = np.zeros(2 * max(N * per, 1))
+    keep.extend((rp, ci, va))
+    return B.Term(B.CSR, 0, N, N * per, 0, rp.ctypes.data, ci.ctypes.data, va.ctypes.data, -radius, radius)
+
+def ham(ctx, N, per=1, radius=1.0):
+    h = B.Hamiltonian(term(N, per, radius), term(N, per, radius), -1.0, 1.0)
+    B._check(L.magnus_spectral_bounds(ctx, C.byref(h), None))
+    for t in (h.H1, h.H2):
+        t.lam_min, t.lam_max = -radius, radius
+    h.k_min, h.k_max = -2 * radius**2, 2 * radius**2
+    return h
+
+def vector(n):
+    v = np.zeros(2 * n); keep.append(v)
+    return v.ctypes.data
+
+def opts(tol=1e-10):
+    return C.byref(B.LejaOpts(tol, 64, 1 << 20, 1, 0))
+
+def launched(f):
+    # (names of the kernels that f launches, in order)
+    stub.stub_clear()
+    B._check(f())
+    return stub.stub_log().decode().split()
+
+def propagate(ctx, h, method=B.CF4, steps=2, batch=1, tau=0.1):
+    f = np.linspace(0.2, 0.9, steps * L.magnus_method_nodes(method)); keep.append(f)
+    return L.propagate(ctx, C.byref(h), method, tau, steps, B._dptr(f), 1, vector(h.H1.dim * batch), batch, None, 1,
+                       opts(), None, None)
+"""
+
+
+@pytest.fixture(scope="session")
+def stub(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("stub") / "libhipstub.so")
+    subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-std=c++17", "-o", out, os.path.join(HERE, "hip_stub.cpp")], check=True)
+    return out
+
+
+def run(stub, body, **env):
+    p = subprocess.run([sys.executable, "-c", PRELUDE + textwrap.dedent(body), stub], cwd=os.path.dirname(HERE),
+                       env={**os.environ, **env}, capture_output=True, text=True, timeout=300)
+    assert p.returncode == 0, p.stdout + p.stderr
+
+
+@pytest.mark.parametrize("N,single,two_pass", [
+    (20000, "csr_rows_kernel", "csr_rows_kernel"), (28671, "csr_rows_kernel", "csr_rows_kernel"),
+    (28672, "csr2_rowlane_kernel", "csr2_rowlane_kernel"), (49152, "csr2_rowlane_kernel", "csr2_rowlane_kernel"),
+    (49153, "csr_rows_kernel", "csr_rows_kernel"), (65535, "csr_rows_kernel", "csr_rows_kernel"),
+    (65536, "csr_rows_kernel", "csr2_wave_kernel"), (65537, "csr2_wave_kernel", "csr2_wave_kernel"),
+    (131071, "csr2_wave_kernel", "csr2_wave_kernel"), (131072, "csr2_stream_kernel", "csr2_stream_kernel")])
+def test_row_mapping_by_size(stub, N, single, two_pass):
+    """The iteration of one CSR state on the arrays, and with a commutator applied to vectors."""
+    run(stub, f"""
+    ctx = context({N})
+    h = ham(ctx, {N})
+    for method, name in ((B.CF4, "{single}"), (B.M4, "{two_pass}")):
+        names = [n for n in launched(lambda: propagate(ctx, h, method)) if "csr" in n]
+        assert names and all(name in n for n in names), names
+    """, MAGNUS_CODED="0")
