@@ -383,6 +383,26 @@ bool pair_partials_fit(const magnus_ctx* ctx, int64_t pair_blocks) {
   return pair_partials_at(ctx) + 8 * (size_t)pair_blocks <= ctx->npartials;
 }
 
+// Whether an M6 iteration on the CSR arrays takes two passes over H1, H2, K, P1
+// and P2 rather than three over H1, H2 and K: by the entries of a row in P1 and P2
+// (p) and in the others (h).  Measured, us per iteration, two passes / three:
+// chains (p = 2.0 h to 2.7 h) n = 6 13.6 / 17.6, n = 8 17.2 / 19.3, n = 10
+// 21.1 / 21.6, n = 11 23.3 / 22.4, n = 12 26.2 / 22.5; rings (1.1 h to 1.5 h) n = 8
+// 15.0 / 19.9, n = 12 19.4 / 21.0; long-range couplings n = 8 (2.2 h) 15.2 / 19.5,
+// n = 12 (3.2 h) 23.2 / 21.9.  From 2^14 rows on, where it is the entries read that
+// count: the chain with coupling 1, whose P cancel (1.1 h), n = 15 29.2 / 35.1,
+// n = 16 48.4 / 56.8, n = 17 94.7 / 95.4, n = 18, past what the MALL holds,
+// 219 / 171; rings n = 14 (1.6 h) 29.9 / 24.4, n = 16 (1.7 h) 71.5 / 56.1.  Rows
+// that are one round of loads either way (p = 8): 60,001 random rows 30.6 / 38.0.
+bool m6_two_passes(const magnus_ctx* ctx, const magnus_hamiltonian* h) {
+  const int64_t dim = h->H1.dim;
+  const double rows = (double)dim, all = (double)(h->H1.nnz + h->H2.nnz + ctx->kc_nnz);
+  const double ps = (double)(ctx->pm_nnz[0] + ctx->pm_nnz[1]);
+  if (ps <= 10.0 * rows || (dim <= 512 && ps <= 64.0 * rows)) return true;
+  if (dim < 16384) return ps <= 2.25 * all;
+  return ps <= 1.25 * all && 20.0 * (all + ps) <= 200e6;
+}
+
 // Exponentials from which coding pays.  It costs what about three iterations
 // gain from 2^16 rows on (chains, us: coding, and an iteration on the CSR
 // arrays / on the coded terms: n = 16 21, 15.1 / 8.6; n = 18 53, 37 / 15; n = 20
@@ -390,7 +410,9 @@ bool pair_partials_fit(const magnus_ctx* ctx, int64_t pair_blocks) {
 // iterations or more).  At n = 14 it is 15 against 6.0 / 5.6 with the chain's
 // 21 entries a row, and the ring's 16 gain nothing (5.5 / 5.7); nor do smaller
 // sizes (n = 12 5.1 / 5.8).  Pairs gain a decide kernel in every iteration too.
-// M6's three passes: n = 12 22 / 20, n = 16 60 / 31.  A gradient takes six
+// M6's three passes: n = 12 22 / 20, n = 16 60 / 31 (below 2^14 rows two passes on the
+// arrays come first where they are taken: rings of 10 and 12 sites 17.4 / 18.3 and
+// 19.4 / 18.5 coded).  A gradient takes six
 // exponentials a step, two of them pairs.
 enum class CodeUse { kSingle, kM6, kGradient };
 int64_t coding_pays(const magnus_hamiltonian* h, int npairs, CodeUse use) {
@@ -419,6 +441,7 @@ int begin_coded(magnus_ctx* ctx, const magnus_hamiltonian* h, bool with_k, int64
   if (ctx->coding < 2) {
     if (with_k ? !ctx->kc_codable : !ctx->codable.count(pair_key(h))) return MAGNUS_OK;
     if (exponentials < coding_pays(h, npairs, use)) return MAGNUS_OK;
+    if (use == CodeUse::kM6 && dim < 16384 && m6_two_passes(ctx, h)) return MAGNUS_OK;
   }
   magnus::CodeTerms T{2, {csr_dev(h->H1), csr_dev(h->H2)}};
   if (with_k) T.m[T.n++] = CsrDev{ctx->kc_rp, ctx->kc_ci, ctx->kc_val};
@@ -565,12 +588,13 @@ int setup_stop_test(magnus_ctx* ctx, const ExpPlan& P, int i, int grid, IterArgs
 }
 
 // One Leja iteration of Method M6 on CSR terms, the exponent's nested
-// commutators applied to vectors by products with H1, H2 and K alone.
+// commutators applied to vectors by products with H1, H2 and K alone, or with
+// P1 and P2 too.
 int m6_csr_iteration(magnus_ctx* ctx, const ExpOp& op, const ExpPlan& P, int i, IterArgs& a, hipStream_t s) {
   const magnus_hamiltonian* h = op.h;
   const int dim = (int)h->H1.dim;
   const bool coded = ctx->coded_h == h && ctx->coded_terms.n == 3;
-  const magnus::CodeTerms T =
+  magnus::CodeTerms T =
       coded ? ctx->coded_terms
             : magnus::CodeTerms{3, {csr_dev(h->H1), csr_dev(h->H2), CsrDev{ctx->kc_rp, ctx->kc_ci, ctx->kc_val}}};
   magnus::M6Args M{};
@@ -580,12 +604,17 @@ int m6_csr_iteration(magnus_ctx* ctx, const ExpOp& op, const ExpPlan& P, int i, 
   M.scale = P.scale;
   const int grid = coded ? magnus::code_grid(dim, ctx->coded.rows) : magnus::m6_grid(dim);
   if (int rc = setup_stop_test(ctx, P, i, grid, &a, s)) return rc;
+  const bool two = !coded && m6_two_passes(ctx, h);
+  if (two)
+    for (int k = 0; k < 2; ++k) T.m[T.n++] = CsrDev{ctx->pm_rp[k], ctx->pm_ci[k], ctx->pm_val[k]};
   auto pass = [&](int stage) {
-    return coded ? magnus::launch_coded_m6(stage, T, dim, ctx->coded, M, a, s) : magnus::launch_m6(stage, T, dim, M, a, s);
+    return coded ? magnus::launch_coded_m6(stage, T, dim, ctx->coded, M, a, s)
+           : two ? magnus::launch_m6_two(stage, T, dim, M, a, s)
+                 : magnus::launch_m6(stage, T, dim, M, a, s);
   };
   HIP_TRY(pass(0));
-  HIP_TRY(pass(1));
-  HIP_TRY(timed(ctx, MAGNUS_KERNEL_CSR_LEJA, s, [&] { return pass(2); }));
+  if (!two) HIP_TRY(pass(1));
+  HIP_TRY(timed(ctx, MAGNUS_KERNEL_CSR_LEJA, s, [&] { return pass(two ? 1 : 2); }));
   if (!a.fused) HIP_TRY(magnus::launch_leja_decide(a, grid, s));
   return MAGNUS_OK;
 }

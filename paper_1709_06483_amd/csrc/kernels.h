@@ -176,6 +176,8 @@ struct M6Args {
 };
 constexpr int kM6Vecs = 7;
 hipError_t launch_m6(int stage, const CodeTerms& T, int dim, const M6Args& M, const IterArgs& a, hipStream_t s);
+// In two passes over H1, H2, K, P1 and P2 (stage 0, 1; grid m6_grid); M's first six vectors.
+hipError_t launch_m6_two(int stage, const CodeTerms& T, int dim, const M6Args& M, const IterArgs& a, hipStream_t s);
 hipError_t launch_coded_m6(int stage, const CodeTerms& T, int dim, const CodedDev& C, const M6Args& M,
                            const IterArgs& a, hipStream_t s);
 int m6_grid(int dim);

@@ -1,4 +1,4 @@
-// One Leja iteration of Method M6 on CSR terms.
+// One Leja iteration of Method M6 on CSR terms, in three passes or two.
 //
 // The exponent of a step is a combination of H1, H2, K = i[H1,H2], P_a = -i[H_a,K],
 // U_ab = i[H_a,P_b] and R_a = -i[K,P_a], with coefficients c0..c9 in the order
@@ -11,16 +11,17 @@
 //     v3 = c2 w + i (c3 a1 + c4 a2) - c8 q1 - c9 q2 - c8 H1 a3 + c5 H1 a1 - c9 H2 a3 + H2 z;
 //   pass 2: y = H1 v1 + H2 v2 + K v3, the Leja update and the norm partials.
 // (Every nested commutator expanded into products and collected by the matrix
-// that is applied last.)  Two passes over H1, H2, K, P1 and P2 would read 1.5
-// (chains) to 3 times (long-range couplings) as many entries, and with P1 and
-// P2 a block of rows has more distinct couplings than its codes can name.
+// that is applied last.)  Two passes over H1, H2, K, P1 and P2 read up to three
+// times as many entries, and with P1 and P2 a block of rows has more distinct
+// couplings than its codes can name; they are taken where the rows of P1 and P2
+// are short, above all in small states, whose iteration is a chain of launches.
 //
-// Measured, us per iteration: the two passes over five matrices and the stop
-// decision / three passes on the CSR arrays / on coded terms.  Chains, n = 12
-// 29 / 22 / 20, n = 16 123 / 60 / 31, n = 18 645 / 190 / 104; the ring of 15
-// sites 37 / 34 / 23; long-range couplings, n = 12 26 / 22.  Up to n = 16 a
-// coded pass is bound by its chain of dependent loads (about 7 us of 9), the
-// CSR passes by the matrix entries from the MALL (5 TB/s at n = 16).
+// Measured, us per iteration, two passes / three on the CSR arrays / three on coded
+// terms.  Chains, n = 8 17 / 19 / 19, n = 12 26 / 22 / 20, n = 14 42 / 26 / 21, n = 16
+// 122 / 58 / 30; rings, n = 12 19 / 21 / 19, n = 14 30 / 24 / 19, n = 16 72 / 56 / 29;
+// long-range couplings, n = 12 23 / 22, n = 16 106 / 53.  Up to n = 16 a coded pass
+// is bound by its chain of dependent loads (about 7 us of 9), the CSR passes by the
+// matrix entries from the MALL (5 TB/s at n = 16).
 #include "coded_device.h"
 
 namespace magnus {
@@ -162,6 +163,68 @@ __global__ __launch_bounds__(kThreads) void m6_kernel(CodeTerms T, int dim, M6Ar
     }
   }
   if constexpr (STAGE == 2) block_partials(a, pw, pv);
+}
+
+// ---------------------------------------------------------------------------
+// Two passes over H1, H2, K, P1 and P2 (the assembled P_a).  Pass 0 forms the row's five products s_k = M_k w,
+//   y0 = c0 s0 + c1 s1 + c2 s2 + c3 s3 + c4 s4, u1 = i(c5 s3 + c6 s4), u2 = i c7 s4,
+//   u3 = -i(c8 s3 + c9 s4), u4 = i(c8 s2 - c5 s0), u5 = i(c9 s2 - c6 s0 - c7 s1);
+// pass 1: y = y0 + H1 u1 + H2 u2 + K u3 + P1 u4 + P2 u5, then the Leja update.
+// ---------------------------------------------------------------------------
+template <int STAGE>
+__global__ __launch_bounds__(kThreads, 8) void m6_two_kernel(CodeTerms T, int dim, M6Args M, IterArgs a) {
+  __shared__ double fz[kFuseLds];
+  if (m6_stopped<STAGE>(a, fz)) return;
+  const long long t = (long long)blockIdx.x * kThreads + threadIdx.x;
+  const int r0 = (int)(t / kM6Lanes), q = (int)(t % kM6Lanes);
+  const int r = STAGE == 0 || r0 >= dim ? r0 : dim - 1 - r0;  // (the second pass starts on the rows the first ended on)
+  // M.a[0..3], M.v[0..1]: u1 .. u5 and y0
+  double2* const u[6] = {M.a[0], M.a[1], M.a[2], M.a[3], M.v[0], M.v[1]};
+  int rs[5], re[5];
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    rs[k] = r < dim ? T.m[k].rp[r] : 0;
+    re[k] = r < dim ? T.m[k].rp[r + 1] : 0;
+  }
+  auto row_sum = [](d2 v) {  // over the row's lanes, in all of them
+#pragma unroll
+    for (int off = kM6Lanes / 2; off > 0; off >>= 1) {
+      v.x += __shfl_xor(v.x, off, 64);
+      v.y += __shfl_xor(v.y, off, 64);
+    }
+    return v;
+  };
+  d2 s[5], acc = {0.0, 0.0};
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    const d2* val = reinterpret_cast<const d2*>(T.m[k].val);
+    const d2* x = reinterpret_cast<const d2*>(STAGE == 0 ? a.wcur : u[k]);
+    if (STAGE == 0) acc = d2{0.0, 0.0};
+    for (int e = rs[k] + q; e < re[k]; e += kM6Lanes) acc += cmul(val[e], x[T.m[k].ci[e]]);
+    if (STAGE == 0) s[k] = row_sum(acc);
+  }
+  if constexpr (STAGE == 0) {
+    if (r >= dim || q >= 6) return;
+    const double* c = M.c;  // lane q of the row writes vector q
+    d2 out;
+    switch (q) {
+      case 0: out = times_i(rmul(c[5], s[3]) + rmul(c[6], s[4])); break;
+      case 1: out = times_i(rmul(c[7], s[4])); break;
+      case 2: out = times_i(rmul(-c[8], s[3]) - rmul(c[9], s[4])); break;
+      case 3: out = times_i(rmul(c[8], s[2]) - rmul(c[5], s[0])); break;
+      case 4: out = times_i(rmul(c[9], s[2]) - rmul(c[6], s[0]) - rmul(c[7], s[1])); break;
+      default: out = rmul(c[0], s[0]) + rmul(c[1], s[1]) + rmul(c[2], s[2]) + rmul(c[3], s[3]) + rmul(c[4], s[4]);
+    }
+    double2* dst = u[0];
+#pragma unroll
+    for (int k = 1; k < 6; ++k) dst = q == k ? u[k] : dst;
+    dst[r] = fromd2(out);
+  } else {
+    acc = row_sum(acc);
+    double pw = 0.0, pv = 0.0;
+    if (r < dim && q == 0) leja_row(a, r, rmul(M.scale, tod2(u[5][r]) + acc), pw, pv);
+    block_partials(a, pw, pv);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -397,6 +460,15 @@ hipError_t launch_m6(int stage, const CodeTerms& T, int dim, const M6Args& M, co
   if (stage == 0) m6_kernel<0><<<g, kThreads, 0, s>>>(T, dim, M, a);
   else if (stage == 1) m6_kernel<1><<<g, kThreads, 0, s>>>(T, dim, M, a);
   else m6_kernel<2><<<g, kThreads, 0, s>>>(T, dim, M, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_m6_two(int stage, const CodeTerms& T, int dim, const M6Args& M, const IterArgs& a, hipStream_t s) {
+  if (dim <= 0) return hipSuccess;
+  if (T.n != 5) return hipErrorInvalidValue;
+  const int g = m6_grid(dim);
+  if (stage == 0) m6_two_kernel<0><<<g, kThreads, 0, s>>>(T, dim, M, a);
+  else m6_two_kernel<1><<<g, kThreads, 0, s>>>(T, dim, M, a);
   return hipGetLastError();
 }
 
