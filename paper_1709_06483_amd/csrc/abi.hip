@@ -224,56 +224,88 @@ int check_opts(const magnus_leja_opts* o) {
   return MAGNUS_OK;
 }
 
-// Structural check (and Gershgorin enclosure) of a CSR term, run once per term.
-int csr_scan(magnus_ctx* ctx, const magnus_term& t, hipStream_t s, double* lo, double* hi) {
-  const int dim = (int)t.dim;
+int launch_probe(magnus_ctx* ctx, const magnus_hamiltonian* h, bool with_k, int* bad_dev, const double* flags,
+                 int nflags, hipStream_t s);
+bool coding_possible(const magnus_ctx* ctx, const magnus_hamiltonian* h);
+
+// Structural check (and Gershgorin enclosure) of n <= 2 CSR terms of one
+// dimension, run once per term, with one wait for all of them.  *valid: the terms
+// found sound, in order, before the first that is not (MAGNUS_EINVAL then).  The
+// two terms of `both` are coded as well, to say in *fits whether all blocks of rows
+// fit the form (behind the scans on the stream, by a kernel that looks at their flags
+// before it reads the arrays).
+int csr_scan(magnus_ctx* ctx, const magnus_term* const* t, int n, hipStream_t s, double* lo, double* hi,
+             int* valid = nullptr, const magnus_hamiltonian* both = nullptr, bool* fits = nullptr) {
+  if (valid) *valid = 0;
+  if (fits) *fits = false;
+  const bool probe = both && fits && coding_possible(ctx, both);
+  const int dim = (int)t[0]->dim;
   const int grid = magnus::csr_gershgorin_grid(dim);
-  if (3 * (int64_t)grid > ctx->scan_len) return fail(MAGNUS_ENOMEM, "scan buffer too small");
-  auto key = std::make_tuple((const void*)t.row_ptr, (const void*)t.col_idx, t.val, t.dim, t.nnz);
+  const size_t len = 3 * (size_t)grid * n;
+  if ((int64_t)len + 1 > ctx->scan_len) return fail(MAGNUS_ENOMEM, "scan buffer too small");
+  auto key = [](const magnus_term& x) {
+    return std::make_tuple((const void*)x.row_ptr, (const void*)x.col_idx, x.val, x.dim, x.nnz);
+  };
   {
     // a term scanned again (its arrays may have been rewritten) counts as valid only if this scan passes
     std::lock_guard<std::mutex> g(ctx->mu);
-    ctx->validated.erase(key);
+    for (int k = 0; k < n; ++k) ctx->validated.erase(key(*t[k]));
   }
-  double* dout = ctx->scan;
-  CsrDev d{t.row_ptr, t.col_idx, reinterpret_cast<const double2*>(t.val)};
-  hipError_t e = magnus::launch_csr_gershgorin(d, dim, t.nnz, dout, grid, s);
-  std::vector<double> h(3 * (size_t)grid);
-  if (e == hipSuccess) e = hipMemcpyAsync(h.data(), dout, sizeof(double) * h.size(), hipMemcpyDeviceToHost, s);
+  hipError_t e = hipSuccess;
+  for (int k = 0; k < n && e == hipSuccess; ++k) {
+    const CsrDev d{t[k]->row_ptr, t[k]->col_idx, reinterpret_cast<const double2*>(t[k]->val)};
+    e = magnus::launch_csr_gershgorin(d, dim, t[k]->nnz, ctx->scan + (size_t)k * 3 * grid, grid, s);
+  }
+  int* bad_dev = reinterpret_cast<int*>(ctx->scan + len);
+  if (e == hipSuccess && probe)
+    if (int rc = launch_probe(ctx, both, false, bad_dev, ctx->scan, grid * n, s)) return rc;
+  std::vector<double> h(len + 1);
+  if (e == hipSuccess) e = hipMemcpyAsync(h.data(), ctx->scan, sizeof(double) * h.size(), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return fail(MAGNUS_EHIP, "CSR scan: %s", hipGetErrorString(e));
-  double a = INFINITY, b = -INFINITY;
-  bool bad = false;
-  for (int g = 0; g < grid; ++g) {
-    a = std::fmin(a, h[3 * g]);
-    b = std::fmax(b, h[3 * g + 1]);
-    bad = bad || h[3 * g + 2] != 0.0;
+  for (int k = 0; k < n; ++k) {
+    double a = INFINITY, b = -INFINITY;
+    bool bad = false;
+    for (const double* r = h.data() + (size_t)k * 3 * grid; r < h.data() + (size_t)(k + 1) * 3 * grid; r += 3) {
+      a = std::fmin(a, r[0]);
+      b = std::fmax(b, r[1]);
+      bad = bad || r[2] != 0.0;
+    }
+    if (bad) return fail(MAGNUS_EINVAL, "malformed CSR (row_ptr not monotone / not 0..nnz, or column out of range)");
+    lo[k] = a;
+    hi[k] = b;
+    if (valid) *valid = k + 1;
+    std::lock_guard<std::mutex> g(ctx->mu);
+    ctx->validated.insert(key(*t[k]));
   }
-  if (bad) return fail(MAGNUS_EINVAL, "malformed CSR (row_ptr not monotone / not 0..nnz, or column out of range)");
-  *lo = a;
-  *hi = b;
-  std::lock_guard<std::mutex> g(ctx->mu);
-  ctx->validated.insert(key);
+  if (probe) {
+    int bad = 0;
+    memcpy(&bad, &h[len], sizeof bad);
+    *fits = bad == 0;
+  }
   return MAGNUS_OK;
 }
 
-int note_codable(magnus_ctx* ctx, const magnus_hamiltonian* h, hipStream_t s);
+int probe_coding(magnus_ctx* ctx, const magnus_hamiltonian* h, bool with_k, bool* fits, hipStream_t s);
+void note_codable(magnus_ctx* ctx, const magnus_hamiltonian* h, bool fits);
 
 int ensure_valid(magnus_ctx* ctx, const magnus_hamiltonian* h, hipStream_t s) {
-  bool scanned = false;
+  const magnus_term* unseen[2];
+  int n = 0;
   for (const magnus_term* t : {&h->H1, &h->H2}) {
     if (t->format != MAGNUS_CSR) continue;
     auto key = std::make_tuple((const void*)t->row_ptr, (const void*)t->col_idx, t->val, t->dim, t->nnz);
-    {
-      std::lock_guard<std::mutex> g(ctx->mu);
-      if (ctx->validated.count(key)) continue;
-    }
-    double lo, hi;
-    int rc = csr_scan(ctx, *t, s, &lo, &hi);
-    if (rc) return rc;
-    scanned = true;
+    std::lock_guard<std::mutex> g(ctx->mu);
+    if (!ctx->validated.count(key)) unseen[n++] = t;
   }
-  return scanned ? note_codable(ctx, h, s) : MAGNUS_OK;
+  if (n == 0) return MAGNUS_OK;
+  double lo[2], hi[2];
+  bool fits = false;
+  if (int rc = csr_scan(ctx, unseen, n, s, lo, hi, nullptr, n == 2 ? h : nullptr, &fits)) return rc;
+  if (n == 1)
+    if (int rc = probe_coding(ctx, h, false, &fits, s)) return rc;
+  note_codable(ctx, h, fits);
+  return MAGNUS_OK;
 }
 
 int dense_scan(magnus_ctx* ctx, const magnus_term& t, hipStream_t s, double* lo, double* hi) {
@@ -348,32 +380,38 @@ bool coding_possible(const magnus_ctx* ctx, const magnus_hamiltonian* h) {
   return ctx->coding && ctx->coded.codes && h->H1.format == MAGNUS_CSR && h->H1.dim <= magnus::kCodeMaxDim;
 }
 
-// Code the terms once and say whether every block of rows fits (where they
-// have just been scanned or assembled; synchronous, as those are).
-int probe_coding(magnus_ctx* ctx, const magnus_hamiltonian* h, bool with_k, bool* fits, hipStream_t s) {
-  *fits = false;
+// Code the terms once, counting the blocks of rows that do not fit in *bad_dev
+// (flags: as launch_code_build).
+int launch_probe(magnus_ctx* ctx, const magnus_hamiltonian* h, bool with_k, int* bad_dev, const double* flags,
+                 int nflags, hipStream_t s) {
   ctx->coded_h = nullptr;
-  if (!coding_possible(ctx, h)) return MAGNUS_OK;
   const int dim = (int)h->H1.dim;
   magnus::CodeTerms T{2, {csr_dev(h->H1), csr_dev(h->H2)}};
   if (with_k) T.m[T.n++] = CsrDev{ctx->kc_rp, ctx->kc_ci, ctx->kc_val};
   ctx->coded.rows = magnus::code_rows(dim);
+  HIP_TRY(magnus::launch_step_set(bad_dev, 0, s));
+  HIP_TRY(magnus::launch_code_build(T, dim, ctx->coded, bad_dev, s, flags, nflags));
+  return MAGNUS_OK;
+}
+
+// Whether every block of rows fits the coded form (where the terms have just
+// been scanned or assembled; synchronous, as those are).
+int probe_coding(magnus_ctx* ctx, const magnus_hamiltonian* h, bool with_k, bool* fits, hipStream_t s) {
+  *fits = false;
+  ctx->coded_h = nullptr;
+  if (!coding_possible(ctx, h)) return MAGNUS_OK;
   int bad = 0;
   int* bad_dev = ctx->gctr + 1;
-  HIP_TRY(magnus::launch_step_set(bad_dev, 0, s));
-  HIP_TRY(magnus::launch_code_build(T, dim, ctx->coded, bad_dev, s));
+  if (int rc = launch_probe(ctx, h, with_k, bad_dev, nullptr, 0, s)) return rc;
   HIP_TRY(hipMemcpyAsync(&bad, bad_dev, sizeof(int), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   *fits = bad == 0;
   return MAGNUS_OK;
 }
 
-int note_codable(magnus_ctx* ctx, const magnus_hamiltonian* h, hipStream_t s) {
-  bool fits = false;
-  ctx->codable.erase(pair_key(h));
-  if (int rc = probe_coding(ctx, h, false, &fits, s)) return rc;
+void note_codable(magnus_ctx* ctx, const magnus_hamiltonian* h, bool fits) {
   if (fits) ctx->codable.insert(pair_key(h));
-  return MAGNUS_OK;
+  else ctx->codable.erase(pair_key(h));
 }
 
 // The norm partials of pairs lie behind those of single states (two halves by
@@ -2244,7 +2282,8 @@ int assemble_csr_commutator(magnus_ctx* ctx, const CsrDev& A, const CsrDev& Bm, 
   kt.row_ptr = rp_d;
   kt.col_idx = ci_d;
   kt.val = val_d;
-  return csr_scan(ctx, kt, s, lo, hi);
+  const magnus_term* const one[1] = {&kt};
+  return csr_scan(ctx, one, 1, s, lo, hi);
 }
 
 int magnus_csr_commutator(magnus_ctx* ctx, magnus_hamiltonian* h, magnus_stream stream) {
@@ -2615,24 +2654,41 @@ int magnus_spectral_bounds(magnus_ctx* ctx, magnus_hamiltonian* h, magnus_stream
   HIP_TRY(hipSetDevice(ctx->device));
   const int64_t dim = h->H1.dim;
   if (dim < 1 || dim > ctx->max_dim) return fail(dim < 1 ? MAGNUS_EINVAL : MAGNUS_ENOMEM, "dim %lld", (long long)dim);
-  magnus_term* terms[2] = {&h->H1, &h->H2};
-  for (magnus_term* t : terms) {
-    // the enclosure is not yet known: validate the rest of the term only
-    const double l0 = t->lam_min, u0 = t->lam_max;
-    t->lam_min = 0.0;
-    t->lam_max = 0.0;
-    int rc = check_term(*t, dim, t == &h->H1 ? "H1" : "H2");
-    t->lam_min = l0;
-    t->lam_max = u0;
+  // the enclosures are not yet known: validate the rest of the terms only
+  auto check = [&](magnus_term& t, const char* name) {
+    const double l0 = t.lam_min, u0 = t.lam_max;
+    t.lam_min = 0.0;
+    t.lam_max = 0.0;
+    const int rc = check_term(t, dim, name);
+    t.lam_min = l0;
+    t.lam_max = u0;
+    return rc;
+  };
+  if (int rc = check(h->H1, "H1")) return rc;
+  double lo[2], hi[2];
+  auto set = [&](magnus_term& t, int k) {
+    t.lam_min = lo[k];
+    t.lam_max = hi[k];
+  };
+  if (h->H1.format == MAGNUS_CSR && h->H2.format == MAGNUS_CSR && !check(h->H2, "H2")) {  // both with one wait
+    const magnus_term* const terms[2] = {&h->H1, &h->H2};
+    int valid = 0;
+    bool fits = false;
+    const int rc = csr_scan(ctx, terms, 2, s, lo, hi, &valid, h, &fits);
+    if (valid > 0) set(h->H1, 0);
+    note_codable(ctx, h, fits);
     if (rc) return rc;
-    double lo, hi;
-    rc = (t->format == MAGNUS_CSR) ? csr_scan(ctx, *t, s, &lo, &hi) : dense_scan(ctx, *t, s, &lo, &hi);
-    if (rc) return rc;
-    t->lam_min = lo;
-    t->lam_max = hi;
+    set(h->H2, 1);
+  } else {
+    for (magnus_term* t : {&h->H1, &h->H2}) {
+      int rc = t == &h->H2 ? check(h->H2, "H2") : MAGNUS_OK;
+      if (rc) return rc;
+      const magnus_term* const one[1] = {t};
+      rc = (t->format == MAGNUS_CSR) ? csr_scan(ctx, one, 1, s, lo, hi) : dense_scan(ctx, *t, s, lo, hi);
+      if (rc) return rc;
+      set(*t, 0);
+    }
   }
-  if (h->H1.format == MAGNUS_CSR && h->H2.format == MAGNUS_CSR)
-    if (int rc = note_codable(ctx, h, s)) return rc;
   const double n1 = std::fmax(std::fabs(h->H1.lam_min), std::fabs(h->H1.lam_max));
   const double n2 = std::fmax(std::fabs(h->H2.lam_min), std::fabs(h->H2.lam_max));
   h->k_min = -2.0 * n1 * n2;

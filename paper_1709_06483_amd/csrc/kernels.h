@@ -158,7 +158,10 @@ struct CodedDev {
 int code_rows(int dim);
 int code_grid(int dim, int rows);
 // Code T's terms into C; *bad_blocks (if not null) grows by the blocks that could not be.
-hipError_t launch_code_build(const CodeTerms& T, int dim, const CodedDev& C, int* bad_blocks, hipStream_t s);
+// flags: per workgroup outputs of launch_csr_gershgorin for terms scanned just before (nflags
+// workgroups): no array is read, and no block coded, where one of them says malformed.
+hipError_t launch_code_build(const CodeTerms& T, int dim, const CodedDev& C, int* bad_blocks, hipStream_t s,
+                             const double* flags = nullptr, int nflags = 0);
 // One Leja iteration on a1 T0 x1 + a2 T1 x2 (+ a3 T2 x1), or mode kSplitComm, on code_grid(dim, C.rows) workgroups.
 hipError_t launch_coded_iter(int mode, const CodeTerms& T, int dim, const CodedDev& C, const IterArgs& a, double a3,
                              hipStream_t s);

@@ -113,9 +113,21 @@ __device__ __forceinline__ int code_get(BuildLds& S, bool want, int where, long 
 // 4 U entries of each row; the next batch (of the same term or the next) is
 // loaded while one is coded.
 template <int NT>
-__global__ __launch_bounds__(kThreads, 4) void code_build_kernel(CodeTerms T, int dim, CodedDev C, int* bad_blocks) {
+__global__ __launch_bounds__(kThreads, 4) void code_build_kernel(CodeTerms T, int dim, CodedDev C, int* bad_blocks,
+                                                                  const double* flags, int nflags) {
   __shared__ BuildLds S;
   const int tid = threadIdx.x, lane = tid & 63;
+  if (nflags > 0) {  // (uniform)
+    int malformed = 0;
+    for (int k = tid; k < nflags; k += kThreads) malformed |= flags[3 * k + 2] != 0.0;
+    if (__syncthreads_or(malformed)) {
+      if (tid == 0) {
+        C.block[xcd_remap(blockIdx.x, gridDim.x)] = -1;
+        if (bad_blocks) atomicAdd(bad_blocks, 1);
+      }
+      return;
+    }
+  }
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int L = xcd_remap(blockIdx.x, gridDim.x);
   CodeEntry* dict = C.dict + (size_t)L * (kCodeMax + 1);
@@ -498,10 +510,11 @@ int code_rows(int dim) {
 
 int code_grid(int dim, int rows) { return (dim + rows - 1) / rows; }
 
-hipError_t launch_code_build(const CodeTerms& T, int dim, const CodedDev& C, int* bad_blocks, hipStream_t s) {
+hipError_t launch_code_build(const CodeTerms& T, int dim, const CodedDev& C, int* bad_blocks, hipStream_t s,
+                             const double* flags, int nflags) {
   const int g = code_grid(dim, C.rows);
-  if (T.n == 2) code_build_kernel<2><<<g, kThreads, 0, s>>>(T, dim, C, bad_blocks);
-  else if (T.n == 3) code_build_kernel<3><<<g, kThreads, 0, s>>>(T, dim, C, bad_blocks);
+  if (T.n == 2) code_build_kernel<2><<<g, kThreads, 0, s>>>(T, dim, C, bad_blocks, flags, nflags);
+  else if (T.n == 3) code_build_kernel<3><<<g, kThreads, 0, s>>>(T, dim, C, bad_blocks, flags, nflags);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

@@ -17,7 +17,7 @@ struct Dim3 {
 std::map<const void*, std::string> kernels;
 std::map<void*, size_t> blocks;
 size_t live = 0, limit = ~size_t(0);
-int last_error = 0, failures = 0;
+int last_error = 0, failures = 0, waits = 0;
 std::string log_text;
 std::vector<std::pair<std::string, double>> costs;
 double clock_us = 0.0;
@@ -39,6 +39,7 @@ extern "C" {
 // ---- control ----
 size_t stub_live() { return live; }
 int stub_failures() { return failures; }
+int stub_waits() { return waits; }  // waits of the host for the device
 void stub_limit(size_t bytes) { limit = bytes; }
 const char* stub_log() { return log_text.c_str(); }
 void stub_clear() { log_text.clear(); }
@@ -124,8 +125,8 @@ int hipGetDeviceCount(int* n) {
   return 0;
 }
 int hipSetDevice(int) { return 0; }
-int hipDeviceSynchronize() { return 0; }
-int hipStreamSynchronize(void*) { return 0; }
+int hipDeviceSynchronize() { return ++waits, 0; }
+int hipStreamSynchronize(void*) { return ++waits, 0; }
 int hipEventCreate(void** e) {
   *e = new double(0.0);
   return 0;

@@ -92,3 +92,15 @@ def test_row_mapping_by_size(stub, N, single, two_pass):
         names = [n for n in launched(lambda: propagate(ctx, h, method)) if "csr" in n]
         assert names and all(name in n for n in names), names
     """, MAGNUS_CODED="0")
+
+
+def test_spectral_bounds_wait_once(stub):
+    """Both terms' scans and the look whether they fit the coded form, behind one wait of the host."""
+    run(stub, """
+    ctx = context(5000)
+    h = ham(ctx, 5000)
+    before = stub.stub_waits()
+    names = launched(lambda: L.magnus_spectral_bounds(ctx, C.byref(h), None))
+    assert stub.stub_waits() - before == 1
+    assert sum("gershgorin" in n for n in names) == 2 and "code_build" in names[-1], names
+    """)
