@@ -181,7 +181,8 @@ def main():
     code = int(os.environ.get("MAGNUS_CSR_VARIANT", "0") or 0) or (tune["variant"] if tune else 0)
     # the chain's terms fit the coded form, which the library then iterates on unless told otherwise
     coded = not int(os.environ.get("MAGNUS_CSR_VARIANT", "0") or 0) and os.environ.get("MAGNUS_CODED", "1") != "0"
-    kernel = "coded_iter_kernel<kLeja, 2>" if coded else CSR_KERNEL_NAMES.get(code, "unknown")
+    kernel = ("coded_iter_kernel<kLeja, 2>" if coded else "csr_rows_kernel<kLeja, 2>" if code == 1 and dim < 1 << 16
+              else CSR_KERNEL_NAMES.get(code, "unknown"))
     diags = [int(np.count_nonzero(H.to_scipy().diagonal())) for H in (H1, H2)]
     csr_bytes = csr_iter_bytes(nnz_total, dim)
     it_bytes = coded_iter_bytes(nnz_total - sum(diags), sum(d > 0 for d in diags), dim) if coded else csr_bytes

@@ -426,21 +426,24 @@ int magnus_propagate_adjoint(magnus_ctx* ctx, const magnus_hamiltonian* h, doubl
 
 /* Autotuner for the H·v stream that Section 3 reduces the method's cost to:
  * times, on the device, each row mapping of the single-state CSR Leja
- * iteration on these terms (variant codes 1 eight lanes per row, past 2^17
- * rows nonzero streaming, 2-4 a row per lane in blocks of 64/32/128 rows, 5-6 wave tiles of 8/16 rows, 7 runs of 8
- * wave tiles of 8 rows streamed through LDS one tile ahead;
- * 5 timed launches each) and, when batch > 1, the multi-state iteration with 2, 4, 8,
- * 16 and 32 states per pass (up to batch; cost per state), and keeps the
- * fastest for these terms (recognised by H1's row_ptr and dim) in the
- * context: later calls use them.  Results differ from untuned calls only in
+ * iteration on these terms (variant codes 1 eight lanes per row, from 2^16
+ * rows on nonzero streaming, 2-4 a row per lane in blocks of 64/32/128 rows, 5-6
+ * wave tiles of 8/16 rows, 7 runs of 8 wave tiles of 8 rows streamed through LDS
+ * one tile ahead; 5 timed launches each) and, when batch > 1, the multi-state
+ * iteration with 2, 4, 8, 16 and 32 states per pass (up to batch; cost per
+ * state), and keeps the fastest for these terms (recognised by H1's row_ptr and
+ * dim) in the context.  Where the terms fit the coded form (propagate) the
+ * iterations on it are timed too, one state's and, when batch > 1, pairs'; calls
+ * that would use the coded form do so only if it was the faster, and the others
+ * use the mapping and the group size (Method M6 takes no part in this).
+ * Results differ from untuned calls only in
  * rounding (another summation order); the MAGNUS_CSR_VARIANT environment
  * variable, when set, still wins.  Overwrites the context's work vectors.
  *   variant, group       HOST out (may be NULL): the chosen code and group size
  *   variant_us[7], group_us[7]  HOST out (may be NULL): measured microseconds per
- *                        iteration (a mapping whose grid is too large for the
- *                        stop test fused into the iteration is timed with the
- *                        decide kernel that then follows each iteration; group
- *                        entries NAN where not tried).
+ *                        iteration with its stop test (made by the iteration, or
+ *                        by the decide kernel that follows it on larger grids;
+ *                        group entries NAN where not tried).
  * Dense terms: times the two-term GEMV iteration with 1, 2 and 4 rows per
  * wave and, when batch > 1, the FP64-MFMA group iteration of batch states
  * with each tile shape (0: 32 rows x 64 states with K split between two

@@ -297,7 +297,7 @@ def magnus_dense_commutator(ctx: Context, ham: DeviceHamiltonian) -> DeviceHamil
     return ham
 
 
-CSR_VARIANTS = {1: "nonzero streaming", 2: "row per lane, 64 rows", 3: "row per lane, 32 rows",
+CSR_VARIANTS = {1: "eight lanes per row (from 2^16 rows on nonzero streaming)", 2: "row per lane, 64 rows", 3: "row per lane, 32 rows",
                 4: "row per lane, 128 rows", 5: "wave tiles of 8 rows", 6: "wave tiles of 16 rows",
                 7: "streamed wave tiles"}
 
@@ -311,7 +311,7 @@ MFMA_TILES = {0: "32x64, K split in two", 1: "32x64", 2: "64x64", 3: "64x64, K s
 def magnus_autotune(ctx: Context, ham: DeviceHamiltonian, batch: int = 1) -> dict:
     """Time the kernel variants on these terms and keep the fastest in the context.
     CSR terms: the row mappings of the single-state iteration (and multi-state group
-    sizes when batch > 1).  Dense terms: rows per wave of the GEMV iteration (and the
+    sizes when batch > 1), against the coded form of the terms where they fit it.  Dense terms: rows per wave of the GEMV iteration (and the
     FP64-MFMA tile shapes of group iterations of `batch` states).  Returns the choices
     and the timings."""
     v, g = C.c_int32(), C.c_int32()

@@ -150,13 +150,14 @@ struct magnus_ctx {
   std::set<std::tuple<const void*, const void*, const void*, int64_t, int64_t>> validated;
   std::mutex mu;
   // kernel timing: (kind, start, stop) per recorded launch, events reused from a pool
-  int csr_variant = 0;  // MAGNUS_CSR_VARIANT: 0 auto (row per lane in blocks of 32 rows, of 64 from
-                        // 32768 rows, wave tiles of 16 rows from 65536, streamed wave tiles from 131072),
-                        // 1 nonzero-streaming, 2-4 row-per-lane (64/32/128 rows), 5-6 wave tiles
+  int csr_variant = 0;  // MAGNUS_CSR_VARIANT: 0 by size (variant_rows), 1 eight lanes per row (nonzero
+                        // streaming from 2^16 rows on), 2-4 row-per-lane (64/32/128 rows), 5-6 wave tiles
                         // (8/16 rows), 7 streamed wave tiles
   // magnus_autotune results, per CSR term pair (H1 row_ptr, dim): the variant code
   // of the single-state iteration and the states per multi-state pass
   std::map<std::pair<const void*, int64_t>, int> tuned_variant, tuned_group;
+  // and where these were faster than iterations on the coded terms (single states; batches)
+  std::set<std::pair<const void*, int64_t>> uncoded_single, uncoded_batch;
   // magnus_autotune results for dense terms, per (H1 values, dim): rows per
   // wave of the GEMV iteration and the FP64-MFMA tile of group iterations
   std::map<std::pair<const void*, int64_t>, int> tuned_dense_rpw, tuned_mfma;
@@ -463,6 +464,12 @@ int64_t coding_pays(const magnus_hamiltonian* h, int npairs, CodeUse use) {
   return dim >= 16384 && h->H1.nnz + h->H2.nnz >= 20 * dim ? 8 : INT64_MAX;
 }
 
+// Whether magnus_autotune found a mapping of the CSR arrays (for batches a group
+// size) faster than the iterations on the coded terms.
+bool tuned_uncoded(const magnus_ctx* ctx, const magnus_hamiltonian* h, bool batch) {
+  return (batch ? ctx->uncoded_batch : ctx->uncoded_single).count({(const void*)h->H1.row_ptr, h->H1.dim}) > 0;
+}
+
 // At the start of a call on CSR terms: rewrite the terms in coded form
 // when the call's iterations pay for that.  `with_k`: its iterations apply the
 // assembled commutator too.
@@ -480,6 +487,8 @@ int begin_coded(magnus_ctx* ctx, const magnus_hamiltonian* h, bool with_k, int64
     if (with_k ? !ctx->kc_codable : !ctx->codable.count(pair_key(h))) return MAGNUS_OK;
     if (exponentials < coding_pays(h, npairs, use)) return MAGNUS_OK;
     if (use == CodeUse::kM6 && dim < 16384 && m6_two_passes(ctx, h)) return MAGNUS_OK;
+    // (the tuner times none of M6's iterations)
+    if (use != CodeUse::kM6 && tuned_uncoded(ctx, h, npairs > 0)) return MAGNUS_OK;
   }
   magnus::CodeTerms T{2, {csr_dev(h->H1), csr_dev(h->H2)}};
   if (with_k) T.m[T.n++] = CsrDev{ctx->kc_rp, ctx->kc_ci, ctx->kc_val};
@@ -495,7 +504,9 @@ int begin_coded(magnus_ctx* ctx, const magnus_hamiltonian* h, bool with_k, int64
 // MAGNUS_CSR_VARIANT numbering; 0 = the size heuristic).
 int variant_rows(int code, int64_t dim, bool two_pass = false) {
   switch (code) {
-    case 1: return dim > 131072 ? 64 : dim > 65536 ? magnus::kRowsDirect + 64 : magnus::kRowsDirect + 32;
+    // (nonzero streaming, us per iteration: 65,536 rows of 6 entries 9.6, direct 12.0,
+    // wave tiles 13.0; 131,071 rows 18.1, 22.1, 19.2)
+    case 1: return dim >= 65536 ? 64 : magnus::kRowsDirect + 32;
     case 2: return magnus::kRowLane;
     case 3: return -32;
     case 4: return -128;
@@ -1535,7 +1546,9 @@ int code_ragged(magnus_ctx* ctx, const magnus_problem* probs, const std::vector<
     const magnus_problem& P = probs[i];
     const magnus_hamiltonian* h = &P.h;
     if (P.batch != batch || !coding_possible(ctx, h)) return MAGNUS_OK;
-    if (ctx->coding < 2 && (!ctx->codable.count(pair_key(h)) || (h->H1.dim < 65536 && S.nexp * nsteps < 2))) return MAGNUS_OK;
+    if (ctx->coding < 2 && (!ctx->codable.count(pair_key(h)) || (h->H1.dim < 65536 && S.nexp * nsteps < 2) ||
+                            tuned_uncoded(ctx, h, true)))
+      return MAGNUS_OK;
     const int dim = (int)h->H1.dim;
     magnus::CodedDev C = ctx->coded;
     C.rows = magnus::code_pair_rows(dim, npairs, min_rows);
@@ -2520,37 +2533,67 @@ int magnus_autotune(magnus_ctx* ctx, const magnus_hamiltonian* h, int32_t batch,
     return e;
   };
   hipError_t err = hipSuccess;
-  // the single-state iteration: each row mapping on this matrix
+  // the single-state iteration: each row mapping on this matrix, with its stop
+  // test (made by the iteration from the partial sums of the one before, or on
+  // larger grids by the decide kernel after it), then the coded terms
+  HIP_TRY(hipMemsetAsync(ctx->partials, 0, sizeof(double) * ctx->npartials, s));
   IterArgs a{};
   a.x1 = a.x2 = a.wcur = ctx->vec(kA);
   a.wout = ctx->vec(kB);
   a.pacc = ctx->vec(kS0);
   a.slot = ctx->slots;
-  a.partials = ctx->partials;
   a.a1 = a.a2 = 1.0;
-  a.first = 1;
+  a.check_stop = 1;
+  a.iter = 3;
+  auto stop_test = [&](int grid, int limit) {
+    a.fused = ctx->fuse && grid <= limit;
+    a.partials = ctx->partials;
+    a.prev_partials = ctx->partials + 2 * (size_t)ctx->max_grid;
+    a.prev_grid = grid;
+  };
   double best = INFINITY;
   int best_code = 0;
-  for (int code = 1; code <= kTuneVariants && err == hipSuccess; ++code) {
-    const int rpb = variant_rows(code, dim);
+  for (int code = 0; code <= kTuneVariants && err == hipSuccess; ++code) {  // (0: the first one again, to warm up)
+    const int rpb = variant_rows(std::max(code, 1), dim);
+    const int grid = magnus::csr2_grid(dim, rpb);
     double us = 0.0;
-    // an iteration on a grid too large for the fused stop test is followed by
-    // the decide kernel, so that is timed with it
-    const bool decide = !ctx->fuse || magnus::csr2_grid(dim, rpb) > magnus::csr2_fuse_grid(rpb);
+    stop_test(grid, magnus::csr2_fuse_grid(rpb));
     err = time_us(
         [&] {
           hipError_t e = magnus::launch_csr2_iter(magnus::kLeja, t1, t2, dim, a, rpb, s);
-          if (e == hipSuccess && decide) e = magnus::launch_leja_decide(a, magnus::csr2_grid(dim, rpb), s);
+          if (e == hipSuccess && !a.fused) e = magnus::launch_leja_decide(a, grid, s);
           return e;
         },
         &us);
+    if (code == 0) continue;
     if (variant_us) variant_us[code - 1] = us;
     if (us < best) {
       best = us;
       best_code = code;
     }
   }
-  // the multi-state iteration: cost per state of each group size up to the batch
+  const auto key = std::make_pair((const void*)h->H1.row_ptr, h->H1.dim);
+  const bool coded = coding_possible(ctx, h) && ctx->codable.count(pair_key(h));
+  const magnus::CodeTerms T{2, {t1, t2}};
+  ctx->uncoded_single.erase(key);
+  if (err == hipSuccess && coded) {
+    ctx->coded.rows = magnus::code_rows(dim);
+    const int grid = magnus::code_grid(dim, ctx->coded.rows);
+    stop_test(grid, magnus::kFuseMaxGrid);
+    err = magnus::launch_code_build(T, dim, ctx->coded, nullptr, s);
+    double us = 0.0;
+    if (err == hipSuccess)
+      err = time_us(
+          [&] {
+            hipError_t e = magnus::launch_coded_iter(magnus::kLeja, T, dim, ctx->coded, a, 0.0, s);
+            if (e == hipSuccess && !a.fused) e = magnus::launch_leja_decide(a, grid, s);
+            return e;
+          },
+          &us);
+    if (err == hipSuccess && best < us) ctx->uncoded_single.insert(key);
+  }
+  // the multi-state iteration with its decisions: cost per state of each group
+  // size up to the batch, then of pairs on the coded terms
   int best_group = 32;
   double best_per_state = INFINITY;
   std::vector<ColParam> table(32);
@@ -2565,7 +2608,8 @@ int magnus_autotune(magnus_ctx* ctx, const magnus_hamiltonian* h, int32_t batch,
   int gi = 0;
   for (int g : {2, 4, 8, 16, 32}) {
     double us = NAN;
-    if (err == hipSuccess && g <= batch && (size_t)magnus::csr2_multi_grid(dim, g) * g * 2 <= ctx->npartials) {
+    const int grid = magnus::csr2_multi_grid(dim, g);
+    if (err == hipSuccess && g <= batch && (size_t)grid * g * 2 <= ctx->npartials) {
       MultiArgs m{};
       m.x = ctx->vec(kY);
       m.wout = ctx->vec(kA);
@@ -2574,8 +2618,13 @@ int magnus_autotune(magnus_ctx* ctx, const magnus_hamiltonian* h, int32_t batch,
       m.partials = ctx->partials;
       m.prm = ctx->table;
       m.B = g;
-      m.first = 1;
-      err = time_us([&] { return magnus::launch_csr2_multi(magnus::kMultiLeja, t1, t2, dim, m, s); }, &us);
+      m.check_stop = 1;
+      err = time_us(
+          [&] {
+            hipError_t e = magnus::launch_csr2_multi(magnus::kMultiLeja, t1, t2, dim, m, s);
+            return e == hipSuccess ? magnus::launch_multi_decide(m, grid, s) : e;
+          },
+          &us);
       if (err == hipSuccess && us / g < best_per_state) {
         best_per_state = us / g;
         best_group = g;
@@ -2584,10 +2633,38 @@ int magnus_autotune(magnus_ctx* ctx, const magnus_hamiltonian* h, int32_t batch,
     if (group_us) group_us[gi] = us;
     ++gi;
   }
+  const int npairs = std::min(batch / 2, 16);
+  if (batch > 1) ctx->uncoded_batch.erase(key);
+  if (err == hipSuccess && coded && npairs > 0 && ctx->fuse) {
+    ctx->coded.rows = magnus::code_pair_rows(dim, npairs, 64);
+    const int64_t blocks = (int64_t)magnus::code_grid(dim, ctx->coded.rows) * npairs;
+    if (pair_partials_fit(ctx, blocks)) {
+      magnus::PairArgs A{};
+      A.np = 1;
+      magnus::PairProblem& P = A.p[0];
+      P.t1 = t1;
+      P.t2 = t2;
+      P.C = ctx->coded;
+      P.dim = dim;
+      P.npairs = npairs;
+      P.x = ctx->vec(kY);
+      P.wout = ctx->vec(kA);
+      P.pacc = ctx->vec(kB);
+      P.slots = ctx->slots;
+      P.partials = ctx->partials + pair_partials_at(ctx);
+      P.prev_partials = P.partials + 4 * (size_t)blocks;
+      P.prm = P.prev = ctx->table;
+      P.iter = 3;
+      err = hipMemsetAsync(P.partials, 0, sizeof(double) * 8 * (size_t)blocks, s);
+      if (err == hipSuccess) err = magnus::launch_code_build(T, dim, ctx->coded, nullptr, s);
+      double us = 0.0;
+      if (err == hipSuccess) err = time_us([&] { return magnus::launch_coded_pairs(false, A, s); }, &us);
+      if (err == hipSuccess && best_per_state < us / (2 * npairs)) ctx->uncoded_batch.insert(key);
+    }
+  }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (err != hipSuccess) return fail(MAGNUS_EHIP, "autotune: %s", hipGetErrorString(err));
-  const auto key = std::make_pair((const void*)h->H1.row_ptr, h->H1.dim);
   ctx->tuned_variant[key] = best_code;
   if (batch > 1) ctx->tuned_group[key] = best_group;
   if (variant) *variant = best_code;

@@ -103,7 +103,7 @@ constexpr int kWaveTile = 1000;
 // ahead.
 constexpr int kStreamTile = 2000;
 // kRowsDirect + R selects eight lanes per row without staging, R = 32 (up to
-// 65,536 rows) or 64 (up to 131,072) rows per workgroup (of 8 R threads).
+// 65,536 rows) or, for three terms, 64 (up to 131,072) rows per workgroup (of 8 R threads).
 constexpr int kRowsDirect = 4000;
 
 // Launch one iteration over `dim` rows of the two CSR terms.

@@ -1007,12 +1007,15 @@ template <int MODE, int NT>
 hipError_t launch_rows(const CsrDev& t1, const CsrDev& t2, const CsrDev& t3, int dim, const IterArgs& a, double a3,
                        int rows_per_block, hipStream_t s) {
   const int grid = csr2_grid(dim, rows_per_block);
+  if constexpr (NT == 3)
+    if (rows_per_block == kRowsDirect + 64 && grid <= 2048) {
+      csr_rows_kernel<MODE, NT, 512, 4><<<grid, 512, 0, s>>>(t1, t2, t3, dim, a, a3);
+      return hipGetLastError();
+    }
   if (rows_per_block == kRowsDirect + 32 && grid <= 1024)
     csr_rows_kernel<MODE, NT, 256, 4><<<grid, 256, 0, s>>>(t1, t2, t3, dim, a, a3);
   else if (rows_per_block == kRowsDirect + 32 && grid <= 2048)
     csr_rows_kernel<MODE, NT, 256, 8><<<grid, 256, 0, s>>>(t1, t2, t3, dim, a, a3);
-  else if (rows_per_block == kRowsDirect + 64 && grid <= 2048)
-    csr_rows_kernel<MODE, NT, 512, 4><<<grid, 512, 0, s>>>(t1, t2, t3, dim, a, a3);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

@@ -104,3 +104,46 @@ def test_spectral_bounds_wait_once(stub):
     assert stub.stub_waits() - before == 1
     assert sum("gershgorin" in n for n in names) == 2 and "code_build" in names[-1], names
     """)
+
+
+@pytest.mark.parametrize("slow", ["coded", "arrays"])
+def test_autotune_decides_between_the_coded_form_and_the_arrays(stub, slow):
+    """Later calls use what was faster when the tuner timed it: one state, the commutator in two passes, a
+    gradient, a batch (pairs against groups), a ragged batch."""
+    run(stub, f"""
+    N = 70000
+    for name in (b"coded_iter", b"coded_pair"):
+        stub.stub_cost(name, {50.0 if slow == "coded" else 0.01})
+    ctx = context(2 * N, 8)
+    h = ham(ctx, N)
+    fast = {slow == "arrays"}
+    us = np.zeros(7)
+    v, g = C.c_int32(), C.c_int32()
+    def gradient():
+        n = L.magnus_adjoint_workspace_bytes(N, 2, 2)
+        f, df, loss, grad = np.full(4, 0.3), np.ones(4), C.c_double(), np.zeros(1)
+        return L.magnus_propagate_adjoint(ctx, C.byref(h), 0.1, 2, B._dptr(f), B._dptr(df), 1, vector(N), vector(N), 2,
+                                          vector(n // 16 + 1), n, C.byref(loss), B._dptr(grad), opts(), None, None)
+    def ragged():
+        f = np.full(4, 0.3); keep.append(f)
+        P = (B.Problem * 2)(*[B.Problem(h, vector(4 * N), 4, 1, B._dptr(f)) for _ in range(2)])
+        return L.magnus_propagate_ragged(ctx, P, 2, B.CF4, 0.1, 2, opts(), None, None)
+    calls = dict(one=lambda: propagate(ctx, h), two_pass=lambda: propagate(ctx, h, B.M4), gradient=gradient,
+                 batch=lambda: propagate(ctx, h, batch=4), ragged=ragged)
+    def coded(names):
+        return any("coded_iter" in n or "coded_pair_kernel" in n for n in names)
+    assert all(coded(launched(f)) for f in calls.values())      # untuned: terms that fit the form are coded
+    B._check(L.magnus_autotune(ctx, C.byref(h), 4, C.byref(v), C.byref(g), B._dptr(us), None, None))
+    for name, f in calls.items():
+        assert coded(launched(f)) == fast, name
+    """)
+
+
+@pytest.mark.parametrize("N,name", [(65535, "csr_rows_kernel"), (65536, "csr2_iter_kernel"), (131072, "csr2_iter_kernel")])
+def test_variant_one_by_size(stub, N, name):
+    run(stub, f"""
+    ctx = context({N})
+    h = ham(ctx, {N})
+    names = [n for n in launched(lambda: propagate(ctx, h)) if "csr" in n]
+    assert names and all("{name}" in n for n in names), names
+    """, MAGNUS_CSR_VARIANT="1")
