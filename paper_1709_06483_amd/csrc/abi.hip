@@ -2154,6 +2154,7 @@ int magnus_create(magnus_ctx** out, int64_t max_dim, int32_t max_batch, int32_t 
                  (size_t)max_dim * (size_t)std::max(1, max_batch) / 8 + (size_t)max_dim + 64;
   // the dot-product kernel's per-workgroup pairs, whatever the dimension
   c->npartials = std::max(c->npartials, (size_t)magnus::kDotPartials + 64);
+  c->npartials = (c->npartials + 31) / 32 * 32;  // the dot products' complex result behind them is aligned
   const size_t with_dots = c->npartials + magnus::kDotPartials + 64;
   if (e == hipSuccess) e = hipMalloc(&c->partials, sizeof(double) * with_dots);
   c->dots = c->partials + c->npartials;

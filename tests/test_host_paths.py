@@ -147,3 +147,16 @@ def test_variant_one_by_size(stub, N, name):
     names = [n for n in launched(lambda: propagate(ctx, h)) if "csr" in n]
     assert names and all("{name}" in n for n in names), names
     """, MAGNUS_CSR_VARIANT="1")
+
+
+@pytest.mark.parametrize("N,batch", [(50021, 1), (50022, 1), (1, 1), (77, 3), (4133, 7)])
+def test_complex_results_are_aligned(stub, N, batch):
+    """The complex sums of dot products (Lanczos enclosures, gradients) lie at multiples of 16 bytes."""
+    run(stub, f"""
+    stub.stub_watch(b"cdot_final", 2)
+    ctx = context({N}, {batch})
+    h = ham(ctx, {N})
+    names = launched(lambda: L.magnus_spectral_bounds_lanczos(ctx, C.byref(h), 4, 0.01, None))
+    assert any("cdot_final" in n for n in names), names
+    assert stub.stub_watched(0) == 0
+    """)
