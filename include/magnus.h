@@ -152,12 +152,15 @@ typedef struct {
 /* ---- context -------------------------------------------------------------- */
 
 /* Create a context on `device` owning a workspace for states of up to
- * max_dim entries and batches of up to max_batch states (allocated here; later
- * allocations happen only in magnus_reserve_dense, magnus_dense_commutator,
- * magnus_dense_m6_prepare, magnus_csr_commutator and magnus_csr_m6_prepare;
- * about 8 vectors per state, 184 bytes per row of max_dim for the coded form
- * of CSR terms below, and with max_batch > 1 at most 16 MiB for partial
- * products of dense groups).  *out receives the context.  Calls on one context share its workspace: they must not run
+ * max_dim entries and batches of up to max_batch states (allocated here: about
+ * 8 vectors per state, and with max_batch > 1 at most 16 MiB for partial products
+ * of dense groups).  Later allocations happen only in magnus_reserve_dense,
+ * magnus_dense_commutator, magnus_dense_m6_prepare, magnus_csr_commutator and
+ * magnus_csr_m6_prepare, and when CSR terms are first scanned, in
+ * magnus_spectral_bounds or in the first call on them: 153 bytes per row of
+ * max_dim and at most 8 MiB of dictionaries for the coded form below (where
+ * that fails, as with MAGNUS_CODED=0, calls read the CSR arrays).
+ * *out receives the context.  Calls on one context share its workspace: they must not run
  * concurrently from several host threads, and work they enqueue on different
  * streams must not overlap on the device (one stream per context, or the
  * caller orders them).  Errors: EINVAL (null out, max_dim < 1, max_batch < 1),

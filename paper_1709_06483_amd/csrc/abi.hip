@@ -80,7 +80,8 @@ struct magnus_ctx {
   // coded CSR terms (kernels_coded.hip): the form that the current call's terms
   // were rewritten in, for the Hamiltonian at coded_h while the call runs
   magnus::CodedDev coded{};
-  size_t coded_slices = 0, coded_blocks = 0;  // what its buffers hold
+  size_t coded_slices = 0, coded_blocks = 0;  // what its buffers hold (reserve_coded)
+  bool coded_tried = false;                   // whether they have been asked for
   magnus::CodeTerms coded_terms{};
   const magnus_hamiltonian* coded_h = nullptr;
   bool coded_pairs = false;      // the states of the current call's batch run as interleaved pairs
@@ -225,6 +226,36 @@ int check_opts(const magnus_leja_opts* o) {
   return MAGNUS_OK;
 }
 
+void release_coded(magnus_ctx* ctx) {
+  magnus::CodedDev& C = ctx->coded;
+  for (void* p : {(void*)C.codes, (void*)C.more, (void*)C.head, (void*)C.dict, (void*)C.block, (void*)C.diag})
+    if (p) (void)hipFree(p);
+  C = magnus::CodedDev{};
+}
+
+// The buffers of the coded form, when CSR terms are first looked at for it: 153
+// bytes per row of max_dim, and 8 KiB per block of rows (of 64 up to 65,536 rows,
+// then 1,024 blocks).  Without them every call reads the CSR arrays.
+void reserve_coded(magnus_ctx* ctx) {
+  if (ctx->coded_tried || !ctx->coding || ctx->max_dim > magnus::kCodeMaxDim) return;
+  ctx->coded_tried = true;
+  const int64_t n = ctx->max_dim;
+  const size_t slices = ctx->coded_slices = ((size_t)n + 63) / 64 * 4;
+  const size_t blocks = ctx->coded_blocks = (size_t)std::min<int64_t>(magnus::kFuseMaxGrid, (n + 63) / 64);
+  magnus::CodedDev& C = ctx->coded;
+  C.diag_stride = n;
+  hipError_t e = hipMalloc(&C.codes, sizeof(unsigned) * 64 * magnus::kCodeAhead * slices);
+  if (e == hipSuccess) e = hipMalloc(&C.more, sizeof(unsigned) * 64 * magnus::kCodeMore * slices);
+  if (e == hipSuccess) e = hipMalloc(&C.head, sizeof(unsigned) * magnus::kCodeHead * slices);
+  if (e == hipSuccess) e = hipMalloc(&C.dict, sizeof(magnus::CodeEntry) * (magnus::kCodeMax + 1) * blocks);
+  if (e == hipSuccess) e = hipMalloc(&C.block, sizeof(int) * blocks);
+  if (e == hipSuccess) e = hipMalloc(&C.diag, sizeof(double) * magnus::kCodeTerms * (size_t)n);
+  if (e != hipSuccess) {
+    release_coded(ctx);
+    (void)hipGetLastError();  // (the next launch would report it)
+  }
+}
+
 int launch_probe(magnus_ctx* ctx, const magnus_hamiltonian* h, bool with_k, int* bad_dev, const double* flags,
                  int nflags, hipStream_t s);
 bool coding_possible(const magnus_ctx* ctx, const magnus_hamiltonian* h);
@@ -239,6 +270,7 @@ int csr_scan(magnus_ctx* ctx, const magnus_term* const* t, int n, hipStream_t s,
              int* valid = nullptr, const magnus_hamiltonian* both = nullptr, bool* fits = nullptr) {
   if (valid) *valid = 0;
   if (fits) *fits = false;
+  if (both) reserve_coded(ctx);
   const bool probe = both && fits && coding_possible(ctx, both);
   const int dim = (int)t[0]->dim;
   const int grid = magnus::csr_gershgorin_grid(dim);
@@ -400,6 +432,7 @@ int launch_probe(magnus_ctx* ctx, const magnus_hamiltonian* h, bool with_k, int*
 int probe_coding(magnus_ctx* ctx, const magnus_hamiltonian* h, bool with_k, bool* fits, hipStream_t s) {
   *fits = false;
   ctx->coded_h = nullptr;
+  reserve_coded(ctx);
   if (!coding_possible(ctx, h)) return MAGNUS_OK;
   int bad = 0;
   int* bad_dev = ctx->gctr + 1;
@@ -2098,6 +2131,7 @@ int noalloc_context(magnus_ctx** out) {
     c.slots = reinterpret_cast<Slot*>(base + kNaSlotOff);
     c.nslots = 1;
     c.persist = 0;
+    c.coding = 0;  // (its form would be allocated)
     if (const char* v = getenv("MAGNUS_CSR_VARIANT")) c.csr_variant = atoi(v);
     if (const char* v = getenv("MAGNUS_FUSE")) c.fuse = atoi(v);
     c.vecs = reinterpret_cast<double2*>(base);  // last: marks the device's context ready
@@ -2161,23 +2195,15 @@ int magnus_create(magnus_ctx** out, int64_t max_dim, int32_t max_batch, int32_t 
   if (e == hipSuccess && max_batch > 1) {
     // groups of dense states: at most a third of the K chunks' number of shares
     c->split_entries = std::min<long long>(magnus::kSplitEntries, (max_dim / 48 + 1) * max_dim * (long long)max_batch);
-    e = hipMalloc(&c->split, sizeof(double2) * (size_t)c->split_entries);
+    if (hipMalloc(&c->split, sizeof(double2) * (size_t)c->split_entries) != hipSuccess) {  // (groups run unsplit then)
+      c->split = nullptr;
+      c->split_entries = 0;
+      (void)hipGetLastError();
+    }
   }
   if (e == hipSuccess) e = hipMalloc(&c->scan, sizeof(double) * (size_t)c->scan_len);
   if (e == hipSuccess) e = hipMalloc(&c->gctr, 256);
   if (const char* v = getenv("MAGNUS_CODED")) c->coding = atoi(v);
-  if (e == hipSuccess && c->coding && max_dim <= magnus::kCodeMaxDim) {
-    // the coded form of CSR terms: about 176 bytes per row (dimensions up to max_dim need at most these blocks)
-    const size_t slices = c->coded_slices = ((size_t)max_dim + 63) / 64 * 4;
-    const size_t blocks = c->coded_blocks = (size_t)std::min<int64_t>(magnus::kFuseMaxGrid, (max_dim + 63) / 64);
-    c->coded.diag_stride = max_dim;
-    e = hipMalloc(&c->coded.codes, sizeof(unsigned) * 64 * magnus::kCodeAhead * slices);
-    if (e == hipSuccess) e = hipMalloc(&c->coded.more, sizeof(unsigned) * 64 * magnus::kCodeMore * slices);
-    if (e == hipSuccess) e = hipMalloc(&c->coded.head, sizeof(unsigned) * magnus::kCodeHead * slices);
-    if (e == hipSuccess) e = hipMalloc(&c->coded.dict, sizeof(magnus::CodeEntry) * (magnus::kCodeMax + 1) * blocks);
-    if (e == hipSuccess) e = hipMalloc(&c->coded.block, sizeof(int) * blocks);
-    if (e == hipSuccess) e = hipMalloc(&c->coded.diag, sizeof(double) * magnus::kCodeTerms * (size_t)max_dim);
-  }
   if (e == hipSuccess) e = hipMemset(c->slots, 0, sizeof(Slot) * c->nslots);
   if (e == hipSuccess) e = hipMemset(c->vecs, 0, sizeof(double2) * nvec);
   if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -2702,12 +2728,7 @@ int magnus_destroy(magnus_ctx* ctx) {
   if (ctx->graph_done) (void)hipEventDestroy(ctx->graph_done);
   if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
   if (ctx->gctr) (void)hipFree(ctx->gctr);
-  if (ctx->coded.codes) (void)hipFree(ctx->coded.codes);
-  if (ctx->coded.more) (void)hipFree(ctx->coded.more);
-  if (ctx->coded.head) (void)hipFree(ctx->coded.head);
-  if (ctx->coded.dict) (void)hipFree(ctx->coded.dict);
-  if (ctx->coded.block) (void)hipFree(ctx->coded.block);
-  if (ctx->coded.diag) (void)hipFree(ctx->coded.diag);
+  release_coded(ctx);
   for (hipEvent_t e : ctx->pool) (void)hipEventDestroy(e);
   delete ctx;
   return MAGNUS_OK;

@@ -125,8 +125,9 @@ constexpr int kCodeMax = 255;     // (column - row, value) pairs per block of ro
 constexpr int kCodeRounds = 32;   // rounds of four entries per row, over all terms
 constexpr int kCodeAhead = 3;     // words of four rounds' codes that the iteration loads ahead (12 rounds)
 constexpr int kCodeMore = kCodeRounds / 4 - kCodeAhead;
-constexpr int kCodeHead = 8;      // header words per slice of 16 rows (one per term)
-constexpr int kCodeTerms = 5;
+constexpr int kCodeTerms = 3;     // H1, H2 and K
+constexpr int kCodeHead = 4;      // header words per slice of 16 rows (one per term)
+constexpr int kListTerms = 5;     // of a list of terms that are read from the arrays (M6: P1 and P2 too)
 constexpr int kCodeOneReal = 1 << 9;   // block flag: every term's values are all real or all imaginary
 constexpr int kCodeImag = 1 << 16;     // block flag, shifted by t: term t's values are imaginary
 constexpr int kCodeMaxDim = 1 << 26;   // byte offsets of a state's entries stay below 2^30
@@ -134,7 +135,7 @@ constexpr int kNoEntry = 1 << 30;      // an offset past any state
 
 struct CodeTerms {
   int n;
-  CsrDev m[kCodeTerms];
+  CsrDev m[kListTerms];
 };
 // One value of a block's dictionary: an entry at (row, row + offset / 16) of this term.
 struct alignas(32) CodeEntry {

@@ -160,3 +160,50 @@ def test_complex_results_are_aligned(stub, N, batch):
     assert any("cdot_final" in n for n in names), names
     assert stub.stub_watched(0) == 0
     """)
+
+
+def test_the_coded_form_takes_memory_when_csr_terms_come(stub):
+    """Contexts of dense terms pay nothing for it; 153 bytes per row and a dictionary per block otherwise."""
+    run(stub, """
+    N = 70000
+    ctx = context(N)
+    at_create = stub.stub_live()
+    assert at_create < 16 * 8 * N + 8 * 11 * N + (36 << 20)
+    D = np.zeros(2 * 8 * 8); keep.append(D)
+    d = lambda: B.Term(B.DENSE, 0, 8, 0, 8, None, None, D.ctypes.data, -1.0, 1.0)
+    hd = B.Hamiltonian(d(), d(), 0.0, 0.0)
+    B._check(L.magnus_spectral_bounds(ctx, C.byref(hd), None))
+    B._check(propagate(ctx, hd))
+    assert stub.stub_live() == at_create
+    h = ham(ctx, N)
+    rows = -(-N // 64) * 64
+    blocks = min(1024, rows // 64)
+    assert stub.stub_live() - at_create <= 154 * rows + blocks * (8192 + 4)
+    assert any("coded_iter" in n for n in launched(lambda: propagate(ctx, h)))
+    B._check(L.magnus_destroy(ctx))
+    assert stub.stub_live() == 0
+    """)
+
+
+@pytest.mark.parametrize("room", [0, 3, 6, 9])
+def test_without_memory_for_the_coded_form_calls_read_the_arrays(stub, room):
+    """A context and calls that fit the memory without it work without it, whichever of its buffers is refused,
+    and so do batches of dense terms without the scratch of split products."""
+    run(stub, f"""
+    N = 70000
+    ctx = context(N, 2)
+    stub.stub_limit(stub.stub_live() + ({room} << 20))
+    h = ham(ctx, N)
+    assert stub.stub_failures() > 0
+    names = launched(lambda: propagate(ctx, h)) + launched(lambda: propagate(ctx, h, batch=2))
+    assert any("csr" in n for n in names) and not any("coded" in n for n in names), names
+    B._check(L.magnus_destroy(ctx))
+    assert stub.stub_live() == 0
+    stub.stub_limit(1 << 40)
+    ctx = context(800, 150)
+    need = stub.stub_live()
+    B._check(L.magnus_destroy(ctx))
+    stub.stub_limit(need - (8 << 20))
+    ctx = context(800, 150)
+    B._check(L.magnus_destroy(ctx))
+    """)
