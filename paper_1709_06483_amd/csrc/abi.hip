@@ -127,8 +127,8 @@ struct magnus_ctx {
   std::tuple<const void*, const void*, const void*, const void*, int64_t> kc_key{nullptr, nullptr, nullptr, nullptr, 0};
   bool kc_codable = false;  // H1, H2 and K were found to fit the coded form (a guess at what pays, as codable)
   // magnus_csr_m6_prepare: P_a = -i[H_a, K] (a = 1, 2) as CSR for the pair K
-  // belongs to (valid while pm_key equals kc_key), their enclosures, and
-  // kM6Vecs work vectors of pm_ws_dim entries for the M6 iteration
+  // belongs to (valid while pm_key equals kc_key; null where no iteration reads
+  // them), their enclosures, and kM6Vecs work vectors of pm_ws_dim entries for the M6 iteration
   int* pm_rp[2] = {nullptr, nullptr};
   int* pm_ci[2] = {nullptr, nullptr};
   double2* pm_val[2] = {nullptr, nullptr};
@@ -467,6 +467,7 @@ bool pair_partials_fit(const magnus_ctx* ctx, int64_t pair_blocks) {
 // 219 / 171; rings n = 14 (1.6 h) 29.9 / 24.4, n = 16 (1.7 h) 71.5 / 56.1.  Rows
 // that are one round of loads either way (p = 8): 60,001 random rows 30.6 / 38.0.
 bool m6_two_passes(const magnus_ctx* ctx, const magnus_hamiltonian* h) {
+  if (!ctx->pm_rp[0] || !ctx->pm_rp[1]) return false;  // (released by the preparation)
   const int64_t dim = h->H1.dim;
   const double rows = (double)dim, all = (double)(h->H1.nnz + h->H2.nnz + ctx->kc_nnz);
   const double ps = (double)(ctx->pm_nnz[0] + ctx->pm_nnz[1]);
@@ -2363,6 +2364,20 @@ int magnus_csr_m6_prepare(magnus_ctx* ctx, magnus_hamiltonian* h, magnus_stream 
                                       ctx->pm_rows[a], ctx->pm_cap[a], ctx->pm_nnz[a], &ctx->pm_lo[a],
                                       &ctx->pm_hi[a], s)))
       return rc;
+  if (!m6_two_passes(ctx, h))  // P_1 and P_2 were assembled for their enclosures only
+    for (int a = 0; a < 2; ++a) {
+      {
+        std::lock_guard<std::mutex> g(ctx->mu);
+        ctx->validated.erase(std::make_tuple((const void*)ctx->pm_rp[a], (const void*)ctx->pm_ci[a],
+                                             (const void*)ctx->pm_val[a], dim, ctx->pm_nnz[a]));
+      }
+      HIP_TRY(hipFree(ctx->pm_rp[a]));
+      HIP_TRY(hipFree(ctx->pm_ci[a]));
+      HIP_TRY(hipFree(ctx->pm_val[a]));
+      ctx->pm_rp[a] = ctx->pm_ci[a] = nullptr;
+      ctx->pm_val[a] = nullptr;
+      ctx->pm_rows[a] = ctx->pm_cap[a] = 0;
+    }
   if (ctx->pm_ws_dim < dim) {
     HIP_TRY(hipStreamSynchronize(s));
     if (ctx->pm_ws) HIP_TRY(hipFree(ctx->pm_ws));

@@ -27,6 +27,11 @@ struct Watch {
   uintptr_t bits;
 };
 std::vector<Watch> watches;
+struct Fill {
+  std::string name;
+  int arg, value, count;
+};
+std::vector<Fill> fills;
 struct Call {
   Dim3 grid, block;
   size_t lds;
@@ -47,6 +52,9 @@ void stub_cost(const char* name, double us) { costs.insert(costs.begin(), {name,
 // The low four bits that pointer argument `arg` of kernels with this name has had set.
 void stub_watch(const char* name, int arg) { watches.push_back({name, arg, 0}); }
 unsigned stub_watched(int k) { return (unsigned)watches[k].bits; }
+
+// Kernels with this name leave `count` ints of `value` at their pointer argument `arg`.
+void stub_fill(const char* name, int arg, int value, int count) { fills.push_back({name, arg, value, count}); }
 
 // ---- the runtime ----
 void** __hipRegisterFatBinary(const void*) {
@@ -83,6 +91,9 @@ int hipLaunchKernel(const void* host, Dim3, Dim3, void** args, size_t, void*) {
   clock_us += us;
   for (Watch& w : watches)
     if (name.find(w.name) != std::string::npos) w.bits |= *static_cast<uintptr_t*>(args[w.arg]) & 15u;
+  for (const Fill& f : fills)
+    if (name.find(f.name) != std::string::npos)
+      std::fill_n(*static_cast<int**>(args[f.arg]), f.count, f.value);
   return 0;
 }
 int hipMalloc(void** p, size_t n) {

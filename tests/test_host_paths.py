@@ -20,6 +20,7 @@ stub.stub_limit.argtypes = [C.c_size_t]
 stub.stub_log.restype = C.c_char_p
 stub.stub_cost.argtypes = [C.c_char_p, C.c_double]
 stub.stub_watch.argtypes = [C.c_char_p, C.c_int]
+stub.stub_fill.argtypes = [C.c_char_p, C.c_int, C.c_int, C.c_int]
 import numpy as np
 from paper_1709_06483_amd import binding as B
 L = B.lib()
@@ -207,3 +208,30 @@ def test_without_memory_for_the_coded_form_calls_read_the_arrays(stub, room):
     ctx = context(800, 150)
     B._check(L.magnus_destroy(ctx))
     """)
+
+
+@pytest.mark.parametrize("N,two", [(2000, True), (20000, False)])
+def test_m6_keeps_its_commutators_only_where_iterations_read_them(stub, N, two):
+    """Forty entries a row in K, P1 and P2: short against the other terms below 2^14 rows, not from there on.
+    The preparation of another pair, and a second one of the same, run after it."""
+    run(stub, f"""
+    N = {N}
+    stub.stub_fill(b"csr_commutator_kernelILb0", 3, 40, N)   # the rows' lengths
+    ctx = context(N)
+    h = ham(ctx, N)
+    B._check(L.magnus_csr_commutator(ctx, C.byref(h), None))
+    k = stub.stub_live()
+    for _ in range(2):
+        B._check(L.magnus_csr_m6_prepare(ctx, C.byref(h), None))
+        kept = stub.stub_live() - k - 7 * 16 * N
+        p = 2 * (40 * N * 20 + 4 * (N + 1))
+        assert abs(kept - (p if {two} else 0)) < 1024, (kept, p)
+        names = launched(lambda: propagate(ctx, h, B.M6))
+        assert any("m6_two_kernel" in n for n in names) == {two}
+        assert any("m6_kernel" in n for n in names) == (not {two})
+    other = ham(ctx, N)
+    B._check(L.magnus_csr_m6_prepare(ctx, C.byref(other), None))
+    B._check(propagate(ctx, other, B.M6))
+    B._check(L.magnus_destroy(ctx))
+    assert stub.stub_live() == 0
+    """, MAGNUS_CODED="0")
