@@ -51,3 +51,20 @@ def test_a_segment_that_fits_the_table_one_pair_at_a_time(monkeypatch):
     assert s1["planned_iters"] == s0["planned_iters"]  # (one pair at a time on both sides)
     # what two pairs to a launch would take, and what one pair at a time takes
     assert 4 * s0["max_degree_used"] * steps > 1 << 18
+
+
+# one number a value and two, one term imaginary, a diagonal in H2, blocks of rows that are read from the CSR
+# arrays, rows of more rounds than are loaded ahead; partial slices and blocks; one substep and several (whose
+# sums alternate between two buffers); segments recomputed
+@pytest.mark.parametrize("tau", [0.05, 20.0])
+@pytest.mark.parametrize("kind,N", [("real", 17), ("imaginary", 65), ("complex", 1000), ("too many", 300), ("too many", 4133),
+                                    ("wide", 300), ("empty", 1000)])
+def test_block_exponentials_of_all_kinds_of_terms(kind, N, tau, monkeypatch):
+    steps, tol = 5, 1e-10
+    A1, A2 = terms(kind, N)
+    f = 0.3 + 0.1 * np.arange(2 * steps).reshape(steps, 2)
+    df = np.cos(np.arange(4 * steps)).reshape(steps, 2, 2)
+    (l1, g1, s1, radius), (l0, g0, s0, _) = (gradient(monkeypatch, c, A1, A2, tau, f, df, 2, tol) for c in ("2", "0"))
+    lt, gt = allowed(tau, df, radius, tol)
+    assert abs(l1 - l0) <= lt and np.all(np.abs(g1 - g0) <= gt)
+    assert (s1["max_substeps_used"] > 1) == (tau > 1)
