@@ -476,26 +476,45 @@ bool m6_two_passes(const magnus_ctx* ctx, const magnus_hamiltonian* h) {
   return ps <= 1.25 * all && 20.0 * (all + ps) <= 200e6;
 }
 
-// Exponentials from which coding pays.  It costs what about three iterations
-// gain from 2^16 rows on (chains, us: coding, and an iteration on the CSR
-// arrays / on the coded terms: n = 16 21, 15.1 / 8.6; n = 18 53, 37 / 15; n = 20
-// 200, 151 / 47), 16 at n = 15 (18, 7.6 / 6.5; an exponential takes four
-// iterations or more).  At n = 14 it is 15 against 6.0 / 5.6 with the chain's
-// 21 entries a row, and the ring's 16 gain nothing (5.5 / 5.7); nor do smaller
-// sizes (n = 12 5.1 / 5.8).  Pairs gain a decide kernel in every iteration too.
-// M6's three passes: n = 12 22 / 20, n = 16 60 / 31 (below 2^14 rows two passes on the
-// arrays come first where they are taken: rings of 10 and 12 sites 17.4 / 18.3 and
-// 19.4 / 18.5 coded).  A gradient takes six
-// exponentials a step, two of them pairs.
+// Exponentials from which coding pays.  It costs 10 to 20 us up to 2^16 rows (21 at
+// the chain of 16 sites, 53 at 18, 200 at 20), and an exponential takes four
+// iterations or more.  One state, us per step of two exponentials on the CSR
+// arrays / on the coded terms, terms of 7 / 15 / 21 / 31 entries a row:
+//   12,000 rows  55 / 56, 57 / 58, 60 / 59, 62 / 60 (and less gain below)
+//   16,384 rows  55 / 56, 56 / 57, 60 / 59, 63 / 59: pays from 18 and 9 exponentials on
+//   24,000 rows  60 / 60, 62 / 61, 65 / 63, 69 / 64: from 9 and 5
+//   28,672 rows  61 / 61, 65 / 61, 70 / 63, 74 / 64: from 6, 2 and 2
+//   40,009 rows  65 / 66, 71 / 67, 78 / 69, 84 / 70: from 3, 2 and 2
+//   49,153 rows  92 / 68, 99 / 70, 105 / 71, 126 / 72: from the first
+// M6's three passes: chains, n = 12 22 / 20, n = 16 58 / 30 us per iteration (below
+// 2^14 rows two passes on the arrays come first where they are taken: rings of 10
+// and 12 sites 17.4 / 18.3 and 19.4 / 18.5 coded).  A gradient, six exponentials a
+// step, two of them pairs: 1,024 to 49,153 rows of 7 / 21 entries 1.24 to 1.4 /
+// 1.6 to 1.8 times as fast, from the first step on.  Pairs: from the second
+// exponential on where they are the faster (pairs_slower).
 enum class CodeUse { kSingle, kM6, kGradient };
 int64_t coding_pays(const magnus_hamiltonian* h, int npairs, CodeUse use) {
   const int64_t dim = h->H1.dim;
-  if (dim >= 65536) return 1;
+  if (dim > 49152 && npairs == 0) return 1;
+  if (dim >= 65536 || use == CodeUse::kGradient) return 1;
   if (npairs > 0) return 2;
   if (use == CodeUse::kM6) return dim >= 16384 ? 2 : 6;
-  if (use == CodeUse::kGradient) return dim >= 16384 ? 6 : 16;
-  if (dim >= 28672) return 3;
-  return dim >= 16384 && h->H1.nnz + h->H2.nnz >= 20 * dim ? 8 : INT64_MAX;
+  const double per_row = (double)(h->H1.nnz + h->H2.nnz) / (double)dim;
+  if (dim >= 28672) return per_row >= 12 ? 3 : INT64_MAX;
+  return dim < 16384 || per_row < 20 ? INT64_MAX : per_row < 28 ? 12 : 6;
+}
+
+// Whether groups of states on the CSR arrays are faster than pairs on the coded
+// terms: short rows, and groups of a power of two states.  Measured, pairs' time
+// over groups': 3 / 5 / 7 entries a row, batches of 16, 16,384 rows 1.06 / 1.04 /
+// 1.04, 40,009 rows 1.23 / 1.16 / 1.09, 90,001 rows 1.11 / 1.03 / 0.99; batches of
+// 4, 65,535 rows 1.12 / 1.10 / 1.05; of 2, 90,001 rows 1.10 / 1.04 / 1.04; past the
+// upper lines, 200,003 rows, batches of 16 0.90 / 0.83 / 0.79, of 2 1.06 / 0.93 / 0.83;
+// batches of 3, 5, 12 and 24 0.6 to 1.0; 9 entries a row and more 0.5 to 1.02.
+bool pairs_slower(const magnus_hamiltonian* h, int batch) {
+  const int64_t dim = h->H1.dim, nnz = h->H1.nnz + h->H2.nnz, states = dim * std::min(batch, 32);
+  if (nnz >= 8 * dim || (batch < 32 && (batch & (batch - 1)))) return false;
+  return states >= 1 << 17 && states <= (batch == 2 ? 300000 : nnz < 6 * dim ? 3000000 : 1 << 20);
 }
 
 // Whether magnus_autotune found a mapping of the CSR arrays (for batches a group
@@ -504,22 +523,28 @@ bool tuned_uncoded(const magnus_ctx* ctx, const magnus_hamiltonian* h, bool batc
   return (batch ? ctx->uncoded_batch : ctx->uncoded_single).count({(const void*)h->H1.row_ptr, h->H1.dim}) > 0;
 }
 
+// Rows per block of the coded terms for a batch.
+int batch_rows(const magnus_hamiltonian* h, int batch) {
+  return magnus::code_pair_rows((int)h->H1.dim, std::min(batch / 2, 16), 64, h->H1.nnz + h->H2.nnz, batch % 2 != 0);
+}
+
 // At the start of a call on CSR terms: rewrite the terms in coded form
 // when the call's iterations pay for that.  `with_k`: its iterations apply the
 // assembled commutator too.
-// npairs > 0: the call's states run as that many pairs (and perhaps one more).
-int begin_coded(magnus_ctx* ctx, const magnus_hamiltonian* h, bool with_k, int64_t exponentials, int npairs,
+// batch > 1: as many states run in groups, on coded terms as pairs (and perhaps one more).
+int begin_coded(magnus_ctx* ctx, const magnus_hamiltonian* h, bool with_k, int64_t exponentials, int batch,
                 hipStream_t s, CodeUse use = CodeUse::kSingle) {
   ctx->coded_h = nullptr;
   ctx->coded_pairs = false;
+  const int npairs = std::min(batch / 2, 16);
   if (!coding_possible(ctx, h) || ctx->csr_variant) return MAGNUS_OK;
   const int64_t dim = h->H1.dim;
-  const int rows = npairs > 0 ? magnus::code_pair_rows((int)dim, npairs, 64) : magnus::code_rows((int)dim);
+  const int rows = npairs > 0 ? batch_rows(h, batch) : magnus::code_rows((int)dim);
   if (npairs > 0 && (!ctx->fuse || !pair_partials_fit(ctx, (int64_t)magnus::code_grid((int)dim, rows) * npairs)))
     return MAGNUS_OK;
   if (ctx->coding < 2) {
     if (with_k ? !ctx->kc_codable : !ctx->codable.count(pair_key(h))) return MAGNUS_OK;
-    if (exponentials < coding_pays(h, npairs, use)) return MAGNUS_OK;
+    if (exponentials < coding_pays(h, npairs, use) || (npairs > 0 && pairs_slower(h, batch))) return MAGNUS_OK;
     if (use == CodeUse::kM6 && dim < 16384 && m6_two_passes(ctx, h)) return MAGNUS_OK;
     // (the tuner times none of M6's iterations)
     if (use != CodeUse::kM6 && tuned_uncoded(ctx, h, npairs > 0)) return MAGNUS_OK;
@@ -1585,7 +1610,7 @@ int code_ragged(magnus_ctx* ctx, const magnus_problem* probs, const std::vector<
       return MAGNUS_OK;
     const int dim = (int)h->H1.dim;
     magnus::CodedDev C = ctx->coded;
-    C.rows = magnus::code_pair_rows(dim, npairs, min_rows);
+    C.rows = magnus::code_pair_rows(dim, npairs, min_rows, h->H1.nnz + h->H2.nnz, false);
     C.codes += slices * 64 * magnus::kCodeAhead;
     C.more += slices * 64 * magnus::kCodeMore;
     C.head += slices * magnus::kCodeHead;
@@ -2678,7 +2703,7 @@ int magnus_autotune(magnus_ctx* ctx, const magnus_hamiltonian* h, int32_t batch,
   const int npairs = std::min(batch / 2, 16);
   if (batch > 1) ctx->uncoded_batch.erase(key);
   if (err == hipSuccess && coded && npairs > 0 && ctx->fuse) {
-    ctx->coded.rows = magnus::code_pair_rows(dim, npairs, 64);
+    ctx->coded.rows = batch_rows(h, batch);
     const int64_t blocks = (int64_t)magnus::code_grid(dim, ctx->coded.rows) * npairs;
     if (pair_partials_fit(ctx, blocks)) {
       magnus::PairArgs A{};
@@ -2948,7 +2973,7 @@ int expmv_leja(magnus_ctx* ctx, const magnus_hamiltonian* h, double a, double b,
   const double tol_e = per_exp_tol(opts, 1);
   if (tau != 0.0)
     if ((rc = begin_coded(ctx, h, kappa != 0.0 && csr_comm_ready(ctx, h), kappa == 0.0 ? 1 : batch,
-                          kappa == 0.0 ? std::min(batch / 2, 16) : 0, s)))
+                          kappa == 0.0 ? batch : 0, s)))
       return rc;
   Acc acc;
   acc.products_per_iter = kappa != 0.0 ? 4 : 2;
@@ -3039,7 +3064,7 @@ static int step_common(int method, magnus_ctx* ctx, const magnus_hamiltonian* h,
   }
   if (tau != 0.0)
     if ((rc = begin_coded(ctx, h, S.commutator && csr_comm_ready(ctx, h), S.commutator ? batch : S.nexp,
-                          S.commutator ? 0 : std::min(batch / 2, 16), s)))
+                          S.commutator ? 0 : batch, s)))
       return rc;
   for (int32_t c = 0; c < batch;) {
     const int g = (!S.commutator && multi_ok(h, 0.0)) ? group_for(ctx, h, batch - c) : 1;
@@ -3132,7 +3157,7 @@ int propagate(magnus_ctx* ctx, const magnus_hamiltonian* h, int32_t method, doub
   };
   if (!small && tau != 0.0)
     if ((rc = begin_coded(ctx, h, S.commutator && csr_comm_ready(ctx, h),
-                          exps * (S.commutator ? batch : 1), grouped ? std::min(batch / 2, 16) : 0, s,
+                          exps * (S.commutator ? batch : 1), grouped ? batch : 0, s,
                           S.sixth ? CodeUse::kM6 : CodeUse::kSingle)))
       return rc;
   // one state on the grid path with every stop test fused: one step captured,

@@ -323,8 +323,9 @@ struct PairArgs {
   PairProblem p[kMaxPairProblems];
   int np;
 };
-// Rows per block for npairs pairs (a multiple of 64, at least min_rows).
-int code_pair_rows(int dim, int npairs, int min_rows);
+// Rows per block for npairs pairs on terms of nnz entries (a multiple of 64, at
+// least min_rows); single_too: and for a single state after them.
+int code_pair_rows(int dim, int npairs, int min_rows, long long nnz, bool single_too);
 // One Leja iteration of every pair (`frechet`: pairs are block vectors of
 // [[H, H2], [0, H]], one stop test each); makes the previous iteration's stop test.
 hipError_t launch_coded_pairs(bool frechet, PairArgs& A, hipStream_t s);

@@ -526,7 +526,6 @@ hipError_t launch_coded_iter(int mode, const CodeTerms& T, int dim, const CodedD
   do {                                                                                      \
     if (C.rows == 64) coded_iter_kernel<M, N, 1, 256><<<g, 256, 0, s>>>(T, dim, C, a, a3);  \
     else if (C.rows == 128) coded_iter_kernel<M, N, 2, 256><<<g, 256, 0, s>>>(T, dim, C, a, a3);  \
-    else if (C.rows == 256) coded_iter_kernel<M, N, 4, 256><<<g, 256, 0, s>>>(T, dim, C, a, a3);  \
     else coded_iter_kernel<M, N, 4, 256><<<g, 256, 0, s>>>(T, dim, C, a, a3);               \
     return hipGetLastError();                                                               \
   } while (0)

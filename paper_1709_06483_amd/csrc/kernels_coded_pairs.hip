@@ -407,10 +407,26 @@ __global__ void frechet_pairs_init_kernel(const double2* __restrict__ u, const d
 
 }  // namespace
 
-int code_pair_rows(int dim, int npairs, int min_rows) {
-  int r = std::max(min_rows, code_rows(dim));
-  // about 2,048 workgroups over all pairs, and partial sums of at most kFuseMaxGrid blocks each
-  while ((long long)((dim + r - 1) / r) * npairs > 2048 && r < 1024) r *= 2;
+// A block's dictionary is read by every workgroup that takes the block, 8 KiB for
+// as little as 64 rows, so blocks grow until about three workgroups to a CU are
+// left, past 256 rows (where a wave takes its four slices more than once) until
+// four are, and past 512 only where rows are short.  Against blocks that leave
+// 2,048 workgroups, batches of 16 on 16,384 rows of 7 / 15 / 21 entries are 1.45,
+// 1.45 and 1.36 times as fast, of 8 on the ring of 15 sites 1.32, of 4 on 65,535
+// rows of 21 entries 1.30 times; 512 to 1,024 rows per block, 16 states on 90,001
+// rows of 7 / 15 / 21 entries 1.10, 1.12 and 1.04, 8 on 200,003 rows of 31 0.88.
+// A single state that is left over runs on the same blocks and wants small ones.
+int code_pair_rows(int dim, int npairs, int min_rows, long long nnz, bool single_too) {
+  int r = std::max(min_rows, code_rows(dim));  // (partial sums of at most kFuseMaxGrid blocks each)
+  auto grow = [&](int limit, long long target) {
+    while (r < limit && (long long)((dim + r - 1) / r) * npairs > target) r *= 2;
+  };
+  if (!single_too) {
+    grow(256, 768);
+    grow(512, 1024);
+    if (nnz < 16LL * dim) grow(1024, 1024);
+  }
+  grow(1024, 2048);
   return r;
 }
 

@@ -116,7 +116,7 @@ def test_autotune_decides_between_the_coded_form_and_the_arrays(stub, slow):
     for name in (b"coded_iter", b"coded_pair"):
         stub.stub_cost(name, {50.0 if slow == "coded" else 0.01})
     ctx = context(2 * N, 8)
-    h = ham(ctx, N)
+    h = ham(ctx, N, 10)
     fast = {slow == "arrays"}
     us = np.zeros(7)
     v, g = C.c_int32(), C.c_int32()
@@ -235,3 +235,31 @@ def test_m6_keeps_its_commutators_only_where_iterations_read_them(stub, N, two):
     B._check(L.magnus_destroy(ctx))
     assert stub.stub_live() == 0
     """, MAGNUS_CODED="0")
+
+
+# either side of each line: rows, entries a row of each term, steps of two exponentials, coded
+@pytest.mark.parametrize("N,per,steps,coded", [
+    (16383, 20, 30, False), (16384, 9, 30, False), (16384, 10, 5, False), (16384, 10, 6, True), (16384, 14, 2, False),
+    (16384, 14, 3, True), (28671, 10, 5, False), (28672, 5, 30, False), (28672, 6, 1, False), (28672, 6, 2, True),
+    (49152, 6, 1, False), (49152, 6, 2, True), (49153, 1, 1, True), (65536, 1, 1, True)])
+def test_when_one_state_is_coded(stub, N, per, steps, coded):
+    run(stub, f"""
+    ctx = context({N})
+    h = ham(ctx, {N}, {per})
+    names = launched(lambda: propagate(ctx, h, steps={steps}))
+    assert any("coded_iter" in n for n in names) == {coded}, names
+    """)
+
+
+# rows, entries a row of each term, states, coded
+@pytest.mark.parametrize("N,per,batch,pairs", [
+    (5000, 3, 16, True), (8191, 3, 16, True), (8192, 3, 16, False), (65536, 3, 16, False), (65537, 3, 16, True),
+    (65537, 2, 16, False), (8192, 3, 12, True), (8192, 4, 16, True), (4096, 3, 48, False), (70000, 3, 3, True),
+    (70000, 3, 2, False), (150001, 3, 2, True), (160000, 2, 20, True), (187500, 2, 16, False), (187501, 2, 16, True)])
+def test_when_a_batch_runs_as_pairs(stub, N, per, batch, pairs):
+    run(stub, f"""
+    ctx = context({N}, {batch})
+    h = ham(ctx, {N}, {per})
+    names = launched(lambda: propagate(ctx, h, steps=3, batch={batch}))
+    assert any("coded_pair_kernel" in n for n in names) == {pairs}, names
+    """, MAGNUS_PERSIST="0")
