@@ -110,6 +110,8 @@ struct magnus_ctx {
   hipGraph_t graph_g = nullptr;
   hipGraphExec_t graph_x = nullptr;
   hipEvent_t graph_done = nullptr;  // recorded after the last replay of the current graph
+  Slot* seen = nullptr;             // pinned: the slots as of seen_at (copy_slots)
+  hipEvent_t seen_at = nullptr;
   std::vector<magnus::IterCoef> graph_table;  // host side of the last uploaded table chunk
   double2* assembled = nullptr;  // magnus_reserve_dense
   int64_t assembled_dim = 0;
@@ -1009,6 +1011,23 @@ int read_slots(magnus_ctx* ctx, hipStream_t s, long long* iters, int* status) {
     *iters += x.iters_total;
     *status |= x.status;
   }
+  return MAGNUS_OK;
+}
+
+// The slots as they are here in the stream, for await_slots; what is enqueued
+// between the two runs while the host waits for what came before.
+int copy_slots(magnus_ctx* ctx, hipStream_t s) {
+  if (!ctx->seen) HIP_TRY(hipHostMalloc(&ctx->seen, sizeof(Slot) * ctx->nslots, 0));
+  if (!ctx->seen_at) HIP_TRY(hipEventCreateWithFlags(&ctx->seen_at, hipEventDisableTiming));
+  HIP_TRY(hipMemcpyAsync(ctx->seen, ctx->slots, sizeof(Slot) * ctx->nslots, hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipEventRecord(ctx->seen_at, s));
+  return MAGNUS_OK;
+}
+
+int await_slots(magnus_ctx* ctx) {
+  HIP_TRY(hipEventSynchronize(ctx->seen_at));
+  for (int k = 0; k < ctx->nslots; ++k)
+    if (ctx->seen[k].status & 1) return fail(MAGNUS_ENAN, "non-finite vector norm met during the call");
   return MAGNUS_OK;
 }
 
@@ -2766,6 +2785,11 @@ int magnus_destroy(magnus_ctx* ctx) {
     graph_release(ctx);
   }
   if (ctx->graph_done) (void)hipEventDestroy(ctx->graph_done);
+  if (ctx->seen_at) {
+    (void)hipEventSynchronize(ctx->seen_at);
+    (void)hipEventDestroy(ctx->seen_at);
+  }
+  if (ctx->seen) (void)hipHostFree(ctx->seen);
   if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
   if (ctx->gctr) (void)hipFree(ctx->gctr);
   release_coded(ctx);
@@ -3313,16 +3337,15 @@ int magnus_propagate_ragged(magnus_ctx* ctx, const magnus_problem* probs, int32_
   }
   // on coded terms the problems run as pairs of states
   std::vector<RagProblem> coded;
+  bool report = false;
   if (ctx->ragged_joint && !S.commutator && !big.empty() && nsteps > 0 && tau != 0.0)
     if ((rc = code_ragged(ctx, probs, big, S, nsteps, (int)sst.size(), &coded, s))) return rc;
   if (!coded.empty()) {
     if ((rc = ragged_joint_steps(ctx, coded, S, tau, nsteps, tol_e, opts, &acc, s))) return rc;
-    if (!joint) {  // batched propagations otherwise, each with a host wait that reports a non-finite norm
-      long long it = 0;
-      int st = 0;
-      if ((rc = read_slots(ctx, s, &it, &st))) return rc;
-      if (st & 1) return fail(MAGNUS_ENAN, "non-finite vector norm met during the call");
-    }
+    // batched propagations otherwise, each with a host wait that reports a
+    // non-finite norm; here the small states are planned and launched before it
+    if (!joint && (rc = copy_slots(ctx, s))) return rc;
+    report = !joint;
     big.clear();
   } else if (joint && nsteps > 0) {
     std::vector<RagProblem> R;
@@ -3378,6 +3401,7 @@ int magnus_propagate_ragged(magnus_ctx* ctx, const magnus_problem* probs, int32_
       if ((rc = persist_steps(ctx, hs, part, S, tau, 0, nsteps, tol_e, opts, &acc, s))) return rc;
     }
   }
+  if (report && (rc = await_slots(ctx))) return rc;
   return end_call(ctx, acc, tol_e, stats, s);
 }
 

@@ -119,6 +119,14 @@ int hipFree(void* p) {
   free(p);
   return 0;
 }
+int hipHostMalloc(void** p, size_t n, unsigned) {
+  *p = calloc(n, 1);
+  return 0;
+}
+int hipHostFree(void* p) {
+  free(p);
+  return 0;
+}
 int hipMemcpyAsync(void* dst, const void* src, size_t n, int, void*) {
   memmove(dst, src, n);
   return 0;
@@ -151,7 +159,10 @@ int hipEventRecord(void* e, void*) {
   *static_cast<double*>(e) = clock_us;
   return 0;
 }
-int hipEventSynchronize(void*) { return 0; }
+int hipEventSynchronize(void*) {
+  log_text += "event_wait\n";
+  return 0;
+}
 int hipEventElapsedTime(float* ms, void* a, void* b) {
   *ms = (float)(1e-3 * (*static_cast<double*>(b) - *static_cast<double*>(a)));
   return 0;

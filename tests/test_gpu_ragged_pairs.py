@@ -112,3 +112,28 @@ def test_problems_that_do_not_run_jointly_report_at_once(sizes, batch, monkeypat
             ctx.close()
 
     assert both_ways(monkeypatch, run) == [B.ENAN, B.ENAN]
+
+
+@pytest.mark.parametrize("bad", [None, 0, 1])
+def test_a_report_beside_small_states(bad, monkeypatch):
+    """A problem of pairs that reports at once beside one in the one-workgroup kernel, launched before the wait."""
+    monkeypatch.setenv("MAGNUS_PERSIST", "1")
+
+    def run():
+        ctx = B.Context(max_dim=6000, max_batch=4)
+        probs = [problem(ctx, 300, 4), problem(ctx, 5500, 4)]
+        if bad is not None:
+            probs[bad][1][2, 7] = float("nan")
+        try:
+            B.magnus_propagate_ragged(ctx, probs, B.CF4, 0.1)
+            return [p[1].cpu().numpy() for p in probs] if bad is None else 0
+        except B.MagnusError as e:
+            return e.code
+        finally:
+            ctx.close()
+
+    a, b = both_ways(monkeypatch, run)
+    if bad is None:
+        assert all(rel(x, y) < 1e-9 for x, y in zip(a, b))
+    else:
+        assert [a, b] == [B.ENAN if bad else 0] * 2

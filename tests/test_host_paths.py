@@ -263,3 +263,20 @@ def test_when_a_batch_runs_as_pairs(stub, N, per, batch, pairs):
     names = launched(lambda: propagate(ctx, h, steps=3, batch={batch}))
     assert any("coded_pair_kernel" in n for n in names) == {pairs}, names
     """, MAGNUS_PERSIST="0")
+
+
+def test_small_states_are_launched_before_a_ragged_call_waits(stub):
+    """One problem of pairs, whose norms the call reports, beside one in the one-workgroup kernel: that one is
+    on its way when the host waits for the pairs."""
+    run(stub, """
+    ctx = context(9000, 4)
+    small, large = ham(ctx, 300), ham(ctx, 8000)
+    f = np.full(4, 0.3)
+    P = (B.Problem * 2)(*[B.Problem(h, vector(4 * h.H1.dim), 4, 1, B._dptr(f)) for h in (small, large)])
+    before = stub.stub_waits()
+    names = launched(lambda: L.magnus_propagate_ragged(ctx, P, 2, B.CF4, 0.1, 2, opts(), None, None))
+    at = lambda what: [k for k, n in enumerate(names) if what in n]
+    assert at("coded_pair") and at("persist") and at("event_wait") == [len(names) - 1], names
+    assert stub.stub_waits() == before
+    B._check(L.magnus_destroy(ctx))
+    """, MAGNUS_CODED="2")
