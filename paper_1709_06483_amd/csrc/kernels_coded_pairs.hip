@@ -416,12 +416,18 @@ __global__ void frechet_pairs_init_kernel(const double2* __restrict__ u, const d
 // rows of 21 entries 1.30 times; 512 to 1,024 rows per block, 16 states on 90,001
 // rows of 7 / 15 / 21 entries 1.10, 1.12 and 1.04, 8 on 200,003 rows of 31 0.88.
 // A single state that is left over runs on the same blocks and wants small ones.
+// So does a single pair whose rows reach over 4 MB of states, an XCD's L2, and
+// more: 512 workgroups hide too little of the gathers that miss it.  Two states,
+// 3 steps, 128 / 256 rows per block, chain of 17 sites 838 / 872 us, ring 773 /
+// 797; columns near the rows (lattices of no power of two) gain instead, 150,001
+// rows of 15 entries 494 / 477.
 int code_pair_rows(int dim, int npairs, int min_rows, long long nnz, bool single_too) {
   int r = std::max(min_rows, code_rows(dim));  // (partial sums of at most kFuseMaxGrid blocks each)
   auto grow = [&](int limit, long long target) {
     while (r < limit && (long long)((dim + r - 1) / r) * npairs > target) r *= 2;
   };
-  if (!single_too) {
+  const bool reaches = npairs == 1 && dim >= 1 << 17 && (dim & (dim - 1)) == 0;  // (as flips of spins do)
+  if (!single_too && !reaches) {
     grow(256, 768);
     grow(512, 1024);
     if (nnz < 16LL * dim) grow(1024, 1024);

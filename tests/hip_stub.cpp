@@ -38,6 +38,7 @@ struct Call {
   void* stream;
 };
 std::vector<Call> calls;
+std::map<std::string, unsigned> grids;
 }  // namespace
 
 extern "C" {
@@ -45,6 +46,11 @@ extern "C" {
 size_t stub_live() { return live; }
 int stub_failures() { return failures; }
 int stub_waits() { return waits; }  // waits of the host for the device
+unsigned stub_grid(const char* what) {  // workgroups of the last launch of the first kernel so named
+  for (const auto& g : grids)
+    if (g.first.find(what) != std::string::npos) return g.second;
+  return 0;
+}
 void stub_limit(size_t bytes) { limit = bytes; }
 const char* stub_log() { return log_text.c_str(); }
 void stub_clear() { log_text.clear(); }
@@ -79,8 +85,9 @@ int __hipPopCallConfiguration(Dim3* grid, Dim3* block, size_t* lds, void** strea
   *stream = c.stream;
   return 0;
 }
-int hipLaunchKernel(const void* host, Dim3, Dim3, void** args, size_t, void*) {
+int hipLaunchKernel(const void* host, Dim3 grid, Dim3, void** args, size_t, void*) {
   const std::string& name = kernels[host];
+  grids[name] = grid.x;
   log_text += name + "\n";
   double us = 1.0;
   for (const auto& c : costs)

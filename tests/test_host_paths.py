@@ -265,6 +265,19 @@ def test_when_a_batch_runs_as_pairs(stub, N, per, batch, pairs):
     """, MAGNUS_PERSIST="0")
 
 
+# rows, entries a row of each term, states, workgroups of an iteration
+@pytest.mark.parametrize("N,per,batch,blocks", [
+    (65536, 4, 2, 512), (100003, 4, 2, 392), (131072, 4, 2, 1024), (150001, 4, 2, 592), (131072, 4, 3, 1024), (131072, 4, 4, 1024),
+    (16384, 4, 16, 512), (131072, 8, 8, 1024), (131072, 7, 12, 768), (131072, 8, 12, 1536)])
+def test_blocks_of_pairs(stub, N, per, batch, blocks):
+    run(stub, f"""
+    ctx = context({N}, {batch})
+    h = ham(ctx, {N}, {per})
+    launched(lambda: propagate(ctx, h, steps=3, batch={batch}))
+    assert stub.stub_grid(b"coded_pair_kernel") == {blocks}, stub.stub_grid(b"coded_pair_kernel")
+    """, MAGNUS_PERSIST="0")
+
+
 def test_small_states_are_launched_before_a_ragged_call_waits(stub):
     """One problem of pairs, whose norms the call reports, beside one in the one-workgroup kernel: that one is
     on its way when the host waits for the pairs."""
