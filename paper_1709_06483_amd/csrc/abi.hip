@@ -17,6 +17,7 @@
 #include <set>
 #include <string>
 #include <tuple>
+#include <utility>
 #include <vector>
 
 #include "../../include/magnus.h"
@@ -229,33 +230,41 @@ int check_opts(const magnus_leja_opts* o) {
 }
 
 void release_coded(magnus_ctx* ctx) {
-  magnus::CodedDev& C = ctx->coded;
-  for (void* p : {(void*)C.codes, (void*)C.more, (void*)C.head, (void*)C.dict, (void*)C.block, (void*)C.diag})
-    if (p) (void)hipFree(p);
-  C = magnus::CodedDev{};
+  if (ctx->coded.dict) (void)hipFree(ctx->coded.dict);  // (the first of its arrays)
+  ctx->coded = magnus::CodedDev{};
 }
 
 // The buffers of the coded form, when CSR terms are first looked at for it: 153
 // bytes per row of max_dim, and 8 KiB per block of rows (of 64 up to 65,536 rows,
-// then 1,024 blocks).  Without them every call reads the CSR arrays.
+// then 1,024 blocks), in one allocation (magnus_spectral_bounds of a new
+// context, 65,536 / 262,144 rows, 112 / 302 us; with six allocations 134 / 338).  Without them every call reads the CSR arrays.
 void reserve_coded(magnus_ctx* ctx) {
   if (ctx->coded_tried || !ctx->coding || ctx->max_dim > magnus::kCodeMaxDim) return;
   ctx->coded_tried = true;
   const int64_t n = ctx->max_dim;
   const size_t slices = ctx->coded_slices = ((size_t)n + 63) / 64 * 4;
   const size_t blocks = ctx->coded_blocks = (size_t)std::min<int64_t>(magnus::kFuseMaxGrid, (n + 63) / 64);
-  magnus::CodedDev& C = ctx->coded;
-  C.diag_stride = n;
-  hipError_t e = hipMalloc(&C.codes, sizeof(unsigned) * 64 * magnus::kCodeAhead * slices);
-  if (e == hipSuccess) e = hipMalloc(&C.more, sizeof(unsigned) * 64 * magnus::kCodeMore * slices);
-  if (e == hipSuccess) e = hipMalloc(&C.head, sizeof(unsigned) * magnus::kCodeHead * slices);
-  if (e == hipSuccess) e = hipMalloc(&C.dict, sizeof(magnus::CodeEntry) * (magnus::kCodeMax + 1) * blocks);
-  if (e == hipSuccess) e = hipMalloc(&C.block, sizeof(int) * blocks);
-  if (e == hipSuccess) e = hipMalloc(&C.diag, sizeof(double) * magnus::kCodeTerms * (size_t)n);
-  if (e != hipSuccess) {
-    release_coded(ctx);
+  size_t bytes = 0;
+  auto place = [&](size_t size) { return std::exchange(bytes, bytes + (size + 255) / 256 * 256); };
+  const size_t dict = place(sizeof(magnus::CodeEntry) * (magnus::kCodeMax + 1) * blocks);
+  const size_t codes = place(sizeof(unsigned) * 64 * magnus::kCodeAhead * slices);
+  const size_t more = place(sizeof(unsigned) * 64 * magnus::kCodeMore * slices);
+  const size_t head = place(sizeof(unsigned) * magnus::kCodeHead * slices);
+  const size_t block = place(sizeof(int) * blocks);
+  const size_t diag = place(sizeof(double) * magnus::kCodeTerms * (size_t)n);
+  char* at = nullptr;
+  if (hipMalloc(&at, bytes) != hipSuccess) {
     (void)hipGetLastError();  // (the next launch would report it)
+    return;
   }
+  magnus::CodedDev& C = ctx->coded;
+  C.dict = reinterpret_cast<magnus::CodeEntry*>(at + dict);
+  C.codes = reinterpret_cast<unsigned*>(at + codes);
+  C.more = reinterpret_cast<unsigned*>(at + more);
+  C.head = reinterpret_cast<unsigned*>(at + head);
+  C.block = reinterpret_cast<int*>(at + block);
+  C.diag = reinterpret_cast<double*>(at + diag);
+  C.diag_stride = n;
 }
 
 int launch_probe(magnus_ctx* ctx, const magnus_hamiltonian* h, bool with_k, int* bad_dev, const double* flags,

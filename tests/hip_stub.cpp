@@ -17,7 +17,7 @@ struct Dim3 {
 std::map<const void*, std::string> kernels;
 std::map<void*, size_t> blocks;
 size_t live = 0, limit = ~size_t(0);
-int last_error = 0, failures = 0, waits = 0;
+int last_error = 0, failures = 0, waits = 0, allocations = 0;
 std::string log_text;
 std::vector<std::pair<std::string, double>> costs;
 double clock_us = 0.0;
@@ -45,6 +45,7 @@ extern "C" {
 // ---- control ----
 size_t stub_live() { return live; }
 int stub_failures() { return failures; }
+int stub_allocations() { return allocations; }
 int stub_waits() { return waits; }  // waits of the host for the device
 unsigned stub_grid(const char* what) {  // workgroups of the last launch of the first kernel so named
   for (const auto& g : grids)
@@ -104,6 +105,7 @@ int hipLaunchKernel(const void* host, Dim3 grid, Dim3, void** args, size_t, void
   return 0;
 }
 int hipMalloc(void** p, size_t n) {
+  ++allocations;
   *p = nullptr;
   if (live + n > limit) {
     ++failures;

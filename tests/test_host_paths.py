@@ -265,6 +265,19 @@ def test_when_a_batch_runs_as_pairs(stub, N, per, batch, pairs):
     """, MAGNUS_PERSIST="0")
 
 
+def test_the_coded_form_takes_one_allocation(stub):
+    run(stub, """
+    ctx = context(70001)
+    before, held = stub.stub_allocations(), stub.stub_live()
+    ham(ctx, 5000)
+    ham(ctx, 70001)
+    assert stub.stub_allocations() == before + 1
+    assert stub.stub_live() - held <= 153 * 70001 + (8 << 20) + 64 * 153 + 6 * 256
+    B._check(L.magnus_destroy(ctx))
+    assert stub.stub_live() == 0
+    """)
+
+
 # rows, entries a row of each term, states, workgroups of an iteration
 @pytest.mark.parametrize("N,per,batch,blocks", [
     (65536, 4, 2, 512), (100003, 4, 2, 392), (131072, 4, 2, 1024), (150001, 4, 2, 592), (131072, 4, 3, 1024), (131072, 4, 4, 1024),
