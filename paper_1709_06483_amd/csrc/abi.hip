@@ -236,8 +236,9 @@ void release_coded(magnus_ctx* ctx) {
 
 // The buffers of the coded form, when CSR terms are first looked at for it: 153
 // bytes per row of max_dim, and 8 KiB per block of rows (of 64 up to 65,536 rows,
-// then 1,024 blocks), in one allocation (magnus_spectral_bounds of a new
-// context, 65,536 / 262,144 rows, 112 / 302 us; with six allocations 134 / 338).  Without them every call reads the CSR arrays.
+// then 1,024 blocks), in one allocation (magnus_spectral_bounds of a new context,
+// 65,536 / 262,144 rows, 112 / 302 us; with six 134 / 338).  Without them every
+// call reads the CSR arrays.
 void reserve_coded(magnus_ctx* ctx) {
   if (ctx->coded_tried || !ctx->coding || ctx->max_dim > magnus::kCodeMaxDim) return;
   ctx->coded_tried = true;

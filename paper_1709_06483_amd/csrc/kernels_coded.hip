@@ -12,12 +12,13 @@
 // entry with an imaginary part) is marked and read from the CSR arrays by the
 // same kernel.  Nothing is kept between calls: each codes its terms as they are.
 //
-// Measured, Cf4 on spin chains, us per iteration, the kernels on the CSR arrays
-// / coded (and the coding, once per call): n = 14 6.8 / 6.0 (15), n = 16 15.8 /
-// 8.1 (21), n = 17 22.9 / 10.2 (36), n = 18 35 / 15 (53), n = 20 151 / 46 (200).
-// At n = 20 an iteration moves 240 MB past the L2s (850 before); what bounds
-// it there is the latency of the gathers that leave the L2, at four waves per
-// SIMD.  Measured slower: non-temporal loads and stores of the operands used
+// Measured, Cf4 on spin chains, a call's time over its iterations, us, with the
+// CSR mapping that each size takes by default / coded (and the coding, once per
+// call): n = 14 6.0 / 5.8 (15), n = 15 7.4 / 6.5, n = 16 14.9 / 8.1 (22),
+// n = 17 22.9 / 9.9 (36), n = 18 35 / 15 (53), n = 20 152 / 45 (194).  At n = 20 an
+// iteration moves 243 MB past the L2s (counted; 847 streamed from the CSR arrays);
+// what bounds it there is the latency of the gathers that leave the L2, at four
+// waves per SIMD.  Measured slower: non-temporal loads and stores of the operands used
 // once (48 us; they give up the MALL), 2,048 workgroups (47), a row to a lane
 // (52), all code paths unrolled by the number of rounds (code of 28 KB, fetched
 // cold by every launch: the three-term iteration at n = 14 20 us, 6.4 now).

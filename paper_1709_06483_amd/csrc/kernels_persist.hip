@@ -14,11 +14,11 @@
 // every iteration took most of the time.  Chains, us per iteration, the matrix
 // re-read (term 1 from LDS) / in registers: n = 6 2.1 / 0.9, n = 8 2.9 / 1.1,
 // n = 9 3.3 / 1.5, n = 10 5.2 / 2.4.  What bounds it then is the number of
-// instructions a SIMD issues in turn (n = 10: about 590 per wave and iteration,
-// two waves) and below n = 9 the latency of their chain.  Two rows to each of
-// 512 threads: the part of an iteration that every wave repeats (the sums, two
-// square roots, the verdict) is then done by 8 waves; 1,024 threads with a row
-// each took 3.2 us at n = 10.
+// instructions a SIMD issues in turn (n = 10: 363 vector, 79 scalar and 50 LDS
+// instructions per wave and iteration, counted, of two waves) and below n = 9 the
+// latency of their chain.  Two rows to each of 512 threads: the part of an
+// iteration that every wave repeats (the sums, two square roots, the verdict) is
+// then done by 8 waves; 1,024 threads with a row each took 3.2 us at n = 10.
 #include "device_common.h"
 
 #include <cstddef>
