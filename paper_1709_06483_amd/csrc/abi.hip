@@ -517,16 +517,31 @@ int64_t coding_pays(const magnus_hamiltonian* h, int npairs, CodeUse use) {
 }
 
 // Whether groups of states on the CSR arrays are faster than pairs on the coded
-// terms: short rows, and groups of a power of two states.  Measured, pairs' time
-// over groups': 3 / 5 / 7 entries a row, batches of 16, 16,384 rows 1.06 / 1.04 /
-// 1.04, 40,009 rows 1.23 / 1.16 / 1.09, 90,001 rows 1.11 / 1.03 / 0.99; batches of
-// 4, 65,535 rows 1.12 / 1.10 / 1.05; of 2, 90,001 rows 1.10 / 1.04 / 1.04; past the
-// upper lines, 200,003 rows, batches of 16 0.90 / 0.83 / 0.79, of 2 1.06 / 0.93 / 0.83;
-// batches of 3, 5, 12 and 24 0.6 to 1.0; 9 entries a row and more 0.5 to 1.02.
-bool pairs_slower(const magnus_hamiltonian* h, int batch) {
+// terms: short rows, and groups of a power of two states.  Measured, groups' time
+// over pairs', terms of 3 / 5 / 7 entries a row, by the states times their rows
+// (calls of 2, 4 and 8 exponentials where they differ):
+//   60,000          0.97 / 0.99 / 1.0, 1.0 / 1.03 / 1.03 and 1.0 / 1.04 / 1.08
+//   90,000..131,070 0.90 / 0.93 / 0.94, 0.93 / 0.96 / 0.99 and 0.95 / 0.97 (two and
+//                   four states) 1.02 (more) / 1.02
+//   2^18            batches of 16 0.94 / 0.96 / 0.96, of 4 0.89 / 0.91 / 0.95
+//   640,000         batches of 16 0.81 / 0.86 / 0.92; 1,440,000 0.90 / 0.97 / 1.01
+//   3,200,000       batches of 16 1.1 / 1.2 / 1.27
+// Two states, 8 exponentials: 300,000 0.83 / 0.89 / 0.98, 330,000 0.95 / 1.03 / 1.18,
+// 360,000 0.96 / 1.06 / 1.23, 640,000 0.88 / 1.02, 1,200,000 0.86 / 0.99 (2 exponentials
+// 360,000 0.90 / 0.98 / 1.12).  Batches of 3, 6, 7, 12 and 20 1.0 to 2.1 (5 at 150,000
+// 0.93 / 0.96 / 1.0).  9 / 11 / 15 entries a row, 2 exponentials, batches of 4, 8 and
+// 16 at 130,000 0.97 / 1.0 / 1.03, 160,000 to 320,000 0.88 to 0.98 / 0.88 to 0.97 / 0.90
+// to 1.0, 360,000 1.05 / 1.03 / 1.1 (4 exponentials 0.93 to 1.0 / 0.90 to 0.97 / 0.94 to
+// 1.0, 8 and more even), two states and more entries 1.0 to 2.
+bool pairs_slower(const magnus_hamiltonian* h, int batch, int64_t exponentials) {
   const int64_t dim = h->H1.dim, nnz = h->H1.nnz + h->H2.nnz, states = dim * std::min(batch, 32);
-  if (nnz >= 8 * dim || (batch < 32 && (batch & (batch - 1)))) return false;
-  return states >= 1 << 17 && states <= (batch == 2 ? 300000 : nnz < 6 * dim ? 3000000 : 1 << 20);
+  if ((batch < 32 && (batch & (batch - 1))) || states < 62000) return false;
+  if (nnz >= 8 * dim)
+    return nnz < 14 * dim && batch > 2 && exponentials < 4 && states >= 1 << 17 && states <= 340000;
+  const bool least = 2 * nnz < 9 * dim, few = nnz < 6 * dim;
+  if (states < 1 << 17) return exponentials < 8 || least || (few && batch <= 4);
+  if (batch == 2 && !least) return states <= (few ? 360000 : 310000);
+  return states <= (few ? 3000000 : 1 << 20);
 }
 
 // Whether magnus_autotune found a mapping of the CSR arrays (for batches a group
@@ -556,7 +571,7 @@ int begin_coded(magnus_ctx* ctx, const magnus_hamiltonian* h, bool with_k, int64
     return MAGNUS_OK;
   if (ctx->coding < 2) {
     if (with_k ? !ctx->kc_codable : !ctx->codable.count(pair_key(h))) return MAGNUS_OK;
-    if (exponentials < coding_pays(h, npairs, use) || (npairs > 0 && pairs_slower(h, batch))) return MAGNUS_OK;
+    if (exponentials < coding_pays(h, npairs, use) || (npairs > 0 && pairs_slower(h, batch, exponentials))) return MAGNUS_OK;
     if (use == CodeUse::kM6 && dim < 16384 && m6_two_passes(ctx, h)) return MAGNUS_OK;
     // (the tuner times none of M6's iterations)
     if (use != CodeUse::kM6 && tuned_uncoded(ctx, h, npairs > 0)) return MAGNUS_OK;

@@ -251,16 +251,34 @@ def test_when_one_state_is_coded(stub, N, per, steps, coded):
     """)
 
 
-# rows, entries a row of each term, states, coded
-@pytest.mark.parametrize("N,per,batch,pairs", [
-    (5000, 3, 16, True), (8191, 3, 16, True), (8192, 3, 16, False), (65536, 3, 16, False), (65537, 3, 16, True),
-    (65537, 2, 16, False), (8192, 3, 12, True), (8192, 4, 16, True), (4096, 3, 48, False), (70000, 3, 3, True),
-    (70000, 3, 2, False), (150001, 3, 2, True), (160000, 2, 20, True), (187500, 2, 16, False), (187501, 2, 16, True)])
-def test_when_a_batch_runs_as_pairs(stub, N, per, batch, pairs):
+# rows, entries a row of each term, states, steps of two exponentials, as pairs
+@pytest.mark.parametrize("N,per,batch,steps,pairs", [
+    (3874, 3, 16, 1, True), (3875, 3, 16, 3, False), (3875, 3, 16, 4, True), (8191, 3, 16, 4, True), (8191, 2, 16, 4, False),
+    (5000, 2, 12, 3, True), (8192, 3, 16, 4, False), (65536, 3, 16, 3, False), (65537, 3, 16, 3, True), (65537, 2, 16, 3, False),
+    (8192, 3, 12, 3, True), (8192, 4, 16, 3, True), (8192, 4, 16, 1, False), (8191, 4, 16, 1, True),
+    (21250, 5, 16, 1, False), (21251, 5, 16, 1, True), (21250, 5, 16, 2, True), (21250, 7, 16, 1, True), (80000, 4, 2, 1, True), (4096, 3, 48, 4, False), (70000, 3, 3, 3, True), (70000, 3, 2, 4, False),
+    (155000, 3, 2, 3, False), (155001, 3, 2, 3, True), (160000, 2, 20, 3, True), (187500, 2, 16, 3, False),
+    (187501, 2, 16, 3, True)])
+def test_when_a_batch_runs_as_pairs(stub, N, per, batch, steps, pairs):
     run(stub, f"""
     ctx = context({N}, {batch})
     h = ham(ctx, {N}, {per})
-    names = launched(lambda: propagate(ctx, h, steps=3, batch={batch}))
+    names = launched(lambda: propagate(ctx, h, steps={steps}, batch={batch}))
+    assert any("coded_pair_kernel" in n for n in names) == {pairs}, names
+    """, MAGNUS_PERSIST="0")
+
+
+# five entries a row of both terms together, two and four states
+@pytest.mark.parametrize("N,batch,steps,pairs", [
+    (30999, 2, 1, True), (32000, 2, 6, False), (180000, 2, 3, False), (180001, 2, 1, True), (20000, 4, 6, False), (10000, 8, 4, True)])
+def test_when_a_batch_of_short_rows_runs_as_pairs(stub, N, batch, steps, pairs):
+    run(stub, f"""
+    ctx = context({N}, {batch})
+    h = B.Hamiltonian(term({N}, 2), term({N}, 3), -1.0, 1.0)
+    B._check(L.magnus_spectral_bounds(ctx, C.byref(h), None))
+    for t in (h.H1, h.H2):
+        t.lam_min, t.lam_max = -1.0, 1.0
+    names = launched(lambda: propagate(ctx, h, steps={steps}, batch={batch}))
     assert any("coded_pair_kernel" in n for n in names) == {pairs}, names
     """, MAGNUS_PERSIST="0")
 
