@@ -1040,9 +1040,17 @@ int read_slots(magnus_ctx* ctx, hipStream_t s, long long* iters, int* status) {
 }
 
 // The slots as they are here in the stream, for await_slots; what is enqueued
-// between the two runs while the host waits for what came before.
+// between the two runs while the host waits for what came before.  Without pinned
+// memory the wait is here.
 int copy_slots(magnus_ctx* ctx, hipStream_t s) {
-  if (!ctx->seen) HIP_TRY(hipHostMalloc(&ctx->seen, sizeof(Slot) * ctx->nslots, 0));
+  if (!ctx->seen && hipHostMalloc(&ctx->seen, sizeof(Slot) * ctx->nslots, 0) != hipSuccess) {
+    (void)hipGetLastError();
+    ctx->seen = nullptr;
+    long long iters = 0;
+    int status = 0;
+    if (int rc = read_slots(ctx, s, &iters, &status)) return rc;
+    return status & 1 ? fail(MAGNUS_ENAN, "non-finite vector norm met during the call") : MAGNUS_OK;
+  }
   if (!ctx->seen_at) HIP_TRY(hipEventCreateWithFlags(&ctx->seen_at, hipEventDisableTiming));
   HIP_TRY(hipMemcpyAsync(ctx->seen, ctx->slots, sizeof(Slot) * ctx->nslots, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipEventRecord(ctx->seen_at, s));
@@ -1050,6 +1058,7 @@ int copy_slots(magnus_ctx* ctx, hipStream_t s) {
 }
 
 int await_slots(magnus_ctx* ctx) {
+  if (!ctx->seen) return MAGNUS_OK;
   HIP_TRY(hipEventSynchronize(ctx->seen_at));
   for (int k = 0; k < ctx->nslots; ++k)
     if (ctx->seen[k].status & 1) return fail(MAGNUS_ENAN, "non-finite vector norm met during the call");

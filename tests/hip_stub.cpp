@@ -129,6 +129,7 @@ int hipFree(void* p) {
   return 0;
 }
 int hipHostMalloc(void** p, size_t n, unsigned) {
+  if (live + n > limit) return last_error = 2;
   *p = calloc(n, 1);
   return 0;
 }

@@ -318,6 +318,11 @@ def test_small_states_are_launched_before_a_ragged_call_waits(stub):
     f = np.full(4, 0.3)
     P = (B.Problem * 2)(*[B.Problem(h, vector(4 * h.H1.dim), 4, 1, B._dptr(f)) for h in (small, large)])
     before = stub.stub_waits()
+    stub.stub_limit(stub.stub_live())  # without pinned memory: a wait of its own before them
+    names = launched(lambda: L.magnus_propagate_ragged(ctx, P, 2, B.CF4, 0.1, 2, opts(), None, None))
+    assert stub.stub_waits() == before + 1 and "event_wait" not in names
+    stub.stub_limit(1 << 40)
+    before = stub.stub_waits()
     names = launched(lambda: L.magnus_propagate_ragged(ctx, P, 2, B.CF4, 0.1, 2, opts(), None, None))
     at = lambda what: [k for k, n in enumerate(names) if what in n]
     assert at("coded_pair") and at("persist") and at("event_wait") == [len(names) - 1], names
